@@ -1,0 +1,669 @@
+"""The workloads of this library that are timed, and how each one is run.
+
+A case is a dict of plain values. listed() gives the fixed ones, draw(rng) one
+more of the same ranges, prepare(case, seed) the inputs a program holds before
+the call (on the GPU, a function of the seed alone), run(state) one pass
+through the public entry points, work(case) the bytes and operations a pass
+cannot do without, exact(case, seed) the same outputs in float64 from plain
+torch.
+
+Populations are made as NEAT grows them: from the minimal fully connected
+genome by add-node and add-connection mutations in the ratio 1 : 2, a split of
+the same connection giving the same key in every genome, biases and weights
+N(0, 1), responses 1, sum aggregation. The uneven population is made of random
+acyclic graphs of log-uniform size.
+"""
+import copy
+import math
+
+import torch
+
+import paper_2504_08339_amd as tn
+from paper_2504_08339_amd import autograd
+
+DEVICE = "cuda"
+IDENTITY, SIGMOID, TANH, RELU, SIN, GAUSSIAN, ABS = range(7)
+
+# Hidden and output activations of the populations in use.
+ACTS = {
+    "control": ((TANH, SIGMOID, RELU, IDENTITY), (TANH, SIGMOID, RELU, IDENTITY)),
+    "sigmoid": ((SIGMOID,), (SIGMOID,)),
+    "tanh": ((TANH,), (IDENTITY,)),
+    "cppn": ((SIN, GAUSSIAN, TANH, ABS), (TANH,)),
+}
+MIN_HIDDEN, MAX_HIDDEN, MAX_UNEVEN_CONNS = 10, 500, 2000  # uneven population
+
+
+def _population(genomes, n_in, n_out, nodes, conns, mutations, acts, disabled=0.15):
+    return dict(genomes=genomes, n_in=n_in, n_out=n_out, nodes=nodes, conns=conns, mutations=mutations,
+                acts=acts, disabled=disabled)
+
+
+def _control(genomes, mutations=50, n_in=17, n_out=6):
+    """Control policies: 17 observations, 6 actions, row capacities 64 / 256."""
+    return _population(genomes, n_in, n_out, 64, 256, mutations, "control")
+
+
+def _cppn(genomes, mutations=30):
+    return _population(genomes, 5, 1, 32, 96, mutations, "cppn", 0.0)
+
+
+def listed():
+    return [
+        # the smallest whole evaluation: XOR, 150 genomes on the four rows, transformed and scored each generation
+        dict(name="xor_fitness", kind="fitness", batch=4, **_population(150, 3, 1, 16, 32, 20, "sigmoid", 0.0)),
+        # one environment step of a rollout: every policy acts on the one observation of its own environment
+        dict(name="rollout_step", kind="forward", batch=1, **_control(10000)),
+        # policies on a batch of observations each, with the transformation that a new generation needs
+        dict(name="control_eval", kind="evaluate", batch=1000, **_control(1000)),
+        # genomes of very uneven size: the transformation after a change of weights, then the tuned plan
+        dict(name="uneven_eval", kind="uneven", batch=256, genomes=10000, n_in=27, n_out=8),
+        # gradient refinement of small regression networks on samples that all genomes share
+        dict(name="regression_grad", kind="mse", batch=1024, **_population(4096, 4, 2, 64, 256, 50, "tanh")),
+        # policy gradient through torch's autograd: transformation, outputs and the gradient of a given dL/dy
+        dict(name="policy_grad", kind="autograd", batch=256, **_control(1000)),
+        # indirect encoding: the substrate weights of every CPPN, as an evaluation needs them
+        dict(name="cppn_query", kind="query", grid=32, outputs=8, **_cppn(200)),
+        # the substrate network itself, both directions
+        dict(name="substrate_train", kind="substrate", genomes=200, grid=32, outputs=8, batch=128),
+        # the gradient of the substrate's weights carried back to the CPPNs
+        dict(name="cppn_grad", kind="cppn_grad", grid=32, outputs=8, **_cppn(50)),
+        # recurrent controllers, ten sweeps for each observation
+        dict(name="recurrent", kind="recurrent", batch=1000, sweeps=10, **_control(1000)),
+        # speciation, offspring counts and reproduction of one generation of control policies
+        dict(name="generation", kind="generation", species=10, threshold=3.5, **_control(5000)),
+        # the speciation distance of every pair, over node and connection genes
+        dict(name="distances", kind="distance", node_genes=True, **_control(1000)),
+    ]
+
+
+def _between(rng, lo, hi):
+    """A whole number in [lo, hi], uniform in its logarithm."""
+    return max(lo, min(hi, round(math.exp(rng.uniform(math.log(lo), math.log(hi + 1))))))
+
+
+def draw(rng):
+    kind = rng.choice(["fitness", "forward", "evaluate", "uneven", "mse", "autograd", "query", "substrate",
+                       "cppn_grad", "recurrent", "generation", "distance"])
+    between = lambda lo, hi: _between(rng, lo, hi)
+    policies = lambda lo, hi: _control(between(lo, hi), rng.randint(5, 60), rng.randint(3, 20), rng.randint(1, 6))
+    if kind == "fitness":
+        return dict(kind=kind, batch=between(4, 64),
+                    **_population(between(50, 2000), rng.randint(2, 4), rng.randint(1, 2), 16, 32,
+                                  rng.randint(5, 20), "sigmoid", 0.0))
+    if kind == "forward":
+        return dict(kind=kind, batch=between(1, 48), **policies(100, 8000))
+    if kind == "evaluate":
+        return dict(kind=kind, batch=between(50, 1000), **policies(100, 1000))
+    if kind == "uneven":
+        return dict(kind=kind, batch=between(16, 256), genomes=between(500, 8000), n_in=rng.randint(4, 27),
+                    n_out=rng.randint(1, 8))
+    if kind == "mse":
+        return dict(kind=kind, batch=between(64, 1024),
+                    **_population(between(100, 4000), rng.randint(2, 6), rng.randint(1, 3), 64, 256,
+                                  rng.randint(10, 50), "tanh"))
+    if kind == "autograd":
+        return dict(kind=kind, batch=between(20, 256), **policies(50, 1000))
+    if kind == "query":
+        return dict(kind=kind, grid=rng.choice([8, 16, 24, 32]), outputs=rng.randint(1, 10),
+                    **_cppn(between(10, 200), rng.randint(5, 30)))
+    if kind == "substrate":
+        return dict(kind=kind, genomes=between(5, 200), grid=rng.choice([8, 16, 24, 32]),
+                    outputs=rng.randint(1, 10), batch=between(8, 128))
+    if kind == "cppn_grad":
+        return dict(kind=kind, grid=rng.choice([8, 16, 24, 32]), outputs=rng.randint(1, 10),
+                    **_cppn(between(5, 50), rng.randint(5, 30)))
+    if kind == "recurrent":
+        return dict(kind=kind, batch=between(1, 1000), sweeps=rng.randint(1, 10), **policies(50, 1000))
+    if kind == "generation":
+        return dict(kind=kind, species=rng.randint(5, 30), threshold=round(rng.uniform(0.6, 3.5), 2),
+                    **policies(150, 4000))
+    return dict(kind=kind, node_genes=rng.random() < 0.5, **policies(100, 1000))
+
+
+# ---------------------------------------------------------------- populations
+
+
+def _generator(seed, salt):
+    return torch.Generator(device=DEVICE).manual_seed(1000003 * int(seed) + salt)
+
+
+def _choice(options, shape, gen):
+    t = torch.tensor(options, dtype=torch.uint8, device=DEVICE)
+    return t[torch.randint(len(options), shape, generator=gen, device=DEVICE)]
+
+
+def _grown(case, seed):
+    """Padded rows of a grown population: the library's arrays, and the rows (src, dst) of every connection."""
+    gen = _generator(seed, 1)
+    P, I, O, N, C = case["genomes"], case["n_in"], case["n_out"], case["nodes"], case["conns"]
+    nio = I + O
+    rand = lambda *shape: torch.rand(shape, generator=gen, device=DEVICE)
+    ids = dict(dtype=torch.int64, device=DEVICE)
+    # one spare column takes the writes of the genomes that a step leaves alone
+    key = torch.full((P, N + 1), -1, **ids)
+    rank = torch.zeros((P, N + 1), dtype=torch.float64, device=DEVICE)
+    src, dst = torch.full((P, C + 1), -1, **ids), torch.full((P, C + 1), -1, **ids)
+    en = torch.zeros((P, C + 1), dtype=torch.bool, device=DEVICE)
+    key[:, :nio] = torch.arange(nio, device=DEVICE)
+    rank[:, I:nio] = 1.0
+    src[:, :I * O] = torch.arange(I, device=DEVICE).repeat_interleave(O)
+    dst[:, :I * O] = I + torch.arange(O, device=DEVICE).repeat(I)
+    en[:, :I * O] = True
+    n, m = torch.full((P,), nio, **ids), torch.full((P,), I * O, **ids)
+    g = torch.arange(P, device=DEVICE)
+    connect = lambda ok, a, b: _connect(g, ok, a, b, src, dst, en, m, C)
+    present = lambda a, b: ((src[:, :C] == a[:, None]) & (dst[:, :C] == b[:, None])).any(1)
+    below = lambda count: (rand(P) * count).long().clamp_(max=count - 1) if isinstance(count, int) else \
+        torch.minimum((rand(P) * count).long(), count - 1)
+    # XOR-sized genomes have had any number of mutations, the others all of them
+    steps = torch.randint(case["mutations"] + 1, (P,), generator=gen, device=DEVICE) if N <= 16 else \
+        torch.full((P,), case["mutations"], **ids)
+    for step in range(case["mutations"]):
+        active = steps > step
+        split = active & (rand(P) < 1.0 / 3.0)
+        at = rand(P, C).masked_fill_(~en[:, :C], -1.0).argmax(1)
+        a, b = src[g, at].clamp_(min=0), dst[g, at].clamp_(min=0)
+        k = key[g, a] * 1000003 + key[g, b] * 8191 + 12345
+        k = nio + ((k ^ (k >> 15)) * 0x2C1B3C6D % 2147483647) % (1 << 23)
+        ok = split & en[g, at] & (n < N) & (m + 2 <= C) & ~(key[:, :N] == k[:, None]).any(1)
+        row = torch.where(ok, n, N)
+        key[g, row] = k
+        rank[g, row] = 0.5 * (rank[g, a] + rank[g, b])
+        en[g, torch.where(ok, at, C)] = False
+        connect(ok, a, n)
+        connect(ok, n, b)
+        n += ok
+        todo = active & ~split
+        for _ in range(6):
+            s = below(I + n - nio)
+            s = torch.where(s < I, s, s + O)
+            d = I + below(n - I)
+            fits = todo & (m < C) & (rank[g, s] < rank[g, d]) & ~present(s, d)
+            connect(fits, s, d)
+            todo &= ~fits
+    if case["kind"] == "recurrent":  # edges against the growth order and self-loops
+        for _ in range(12):
+            d = I + below(n - I)
+            s = torch.where(rand(P) < 0.25, d, below(n))
+            connect((m < C) & ~present(s, d), s, d)
+    rows = torch.arange(N, device=DEVICE)
+    node = rows < n[:, None]
+    conn = torch.arange(C, device=DEVICE) < m[:, None]
+    hidden, output = ACTS[case["acts"]]
+    act = torch.where(rows < nio, _choice(output, (P, N), gen), _choice(hidden, (P, N), gen))
+    on = en[:, :C] & conn & (rand(P, C) >= case["disabled"])
+    weight = torch.randn((P, C), generator=gen, device=DEVICE)
+    if case["kind"] == "recurrent":
+        weight *= 0.5
+    arrays = dict(
+        node_key=torch.where(node, key[:, :N], -1).int(),
+        node_bias=torch.randn((P, N), generator=gen, device=DEVICE) * node,
+        node_resp=node.float(),
+        node_act=act * (node & (rows >= I)),
+        node_agg=torch.zeros((P, N), dtype=torch.uint8, device=DEVICE),
+        conn_in=torch.where(conn, key.gather(1, src[:, :C].clamp(min=0)), -1).int(),
+        conn_out=torch.where(conn, key.gather(1, dst[:, :C].clamp(min=0)), -1).int(),
+        conn_w=weight * conn,
+        conn_en=on.byte())
+    return {k: v.contiguous() for k, v in arrays.items()}, src[:, :C], dst[:, :C]
+
+
+def _connect(g, ok, a, b, src, dst, en, m, C):
+    """An enabled connection a -> b in the first free row of the genomes of `ok`."""
+    row = torch.where(ok, m, C)
+    src[g, row], dst[g, row] = a, b
+    en[g, row] = True
+    m += ok
+
+
+def _uneven(case, seed):
+    """Ragged rows of random acyclic graphs: hidden nodes log-uniform in 10 .. 500, two to four connections for each.
+    The sizes belong to the case, the graphs and their values to the seed."""
+    P, I, O = case["genomes"], case["n_in"], case["n_out"]
+    size = _generator(P, 15)
+    H = torch.exp(math.log(MIN_HIDDEN) + torch.rand(P, generator=size, device=DEVICE) *
+                  math.log(MAX_HIDDEN / MIN_HIDDEN)).round().long()
+    want = ((2 + 2 * torch.rand(P, generator=size, device=DEVICE)) * H).round().long().clamp(max=MAX_UNEVEN_CONNS)
+    gen = _generator(seed, 2)
+    rand = lambda *shape: torch.rand(shape, generator=gen, device=DEVICE)
+    n = I + O + H
+    node_off = torch.cat([n.new_zeros(1), n.cumsum(0)])
+    total = int(node_off[-1])
+    of = torch.repeat_interleave(torch.arange(P, device=DEVICE), n)
+    row = torch.arange(total, device=DEVICE) - node_off[of]
+    place = torch.where(row < I, 0.0, torch.where(row < I + O, 2.0, 0.5 + rand(total)))  # order of the graph
+    # distinct connections to a later node: more candidates than are wanted, in random order
+    more = 8 * want + 64
+    cg = torch.repeat_interleave(torch.arange(P, device=DEVICE), more)
+    s = (rand(cg.numel()) * (I + H[cg])).long()
+    s = torch.where(s < I, s, s + O)
+    d = I + (rand(cg.numel()) * (O + H[cg])).long()
+    fits = place[node_off[cg] + s] < place[node_off[cg] + d]
+    pairs = torch.unique((cg[fits] << 20) | (s[fits] << 10) | d[fits])
+    order = torch.argsort((pairs >> 20).double() + rand(pairs.numel()).double())
+    pairs = pairs[order]
+    cg = pairs >> 20
+    first = torch.searchsorted(cg, torch.arange(P, device=DEVICE))
+    pairs = pairs[torch.arange(pairs.numel(), device=DEVICE) - first[cg] < want[cg]]
+    cg, s, d = pairs >> 20, (pairs >> 10) & 1023, pairs & 1023
+    counts = torch.bincount(cg, minlength=P)
+    conn_off = torch.cat([counts.new_zeros(1), counts.cumsum(0)])
+    acts = ACTS["control"][0]
+    arrays = dict(
+        node_key=row.int(),
+        node_bias=torch.randn(total, generator=gen, device=DEVICE),
+        node_resp=torch.ones(total, device=DEVICE),
+        node_act=_choice(acts, (total,), gen) * (row >= I),
+        node_agg=torch.zeros(total, dtype=torch.uint8, device=DEVICE),
+        conn_in=s.int(), conn_out=d.int(),
+        conn_w=torch.randn(cg.numel(), generator=gen, device=DEVICE),
+        conn_en=(rand(cg.numel()) >= 0.15).byte())
+    return arrays, node_off, conn_off, node_off[cg] + s, node_off[cg] + d
+
+
+def _made(case, seed):
+    """The library's population of a case."""
+    if case["kind"] == "uneven":
+        arrays, node_off, conn_off, _, _ = _uneven(case, seed)
+        return tn.Population(case["n_in"], case["n_out"], int((node_off[1:] - node_off[:-1]).max()),
+                             int((conn_off[1:] - conn_off[:-1]).max()), arrays, node_off, conn_off)
+    arrays, _, _ = _grown(case, seed)
+    return tn.Population(case["n_in"], case["n_out"], case["nodes"], case["conns"], arrays)
+
+
+def _normal(shape, seed, salt):
+    return torch.randn(shape, generator=_generator(seed, salt), device=DEVICE)
+
+
+def _observations(case, seed):
+    """N(0, 1) observations for each genome; the XOR-sized and regression cases share theirs."""
+    if case["kind"] == "fitness":
+        return torch.randint(2, (case["batch"], case["n_in"]), generator=_generator(seed, 3), device=DEVICE).float()
+    if case["kind"] == "mse":
+        return 2.0 * torch.rand((case["batch"], case["n_in"]), generator=_generator(seed, 3), device=DEVICE) - 1.0
+    return _normal((case["genomes"], case["batch"], case["n_in"]), seed, 3)
+
+
+def _targets(case, seed):
+    """Parity of the bits (XOR), or a smooth function of the samples."""
+    x = _observations(case, seed)
+    if case["kind"] == "fitness":
+        return (x.sum(1, keepdim=True) % 2).repeat(1, case["n_out"])
+    mix = _normal((case["n_in"], case["n_out"]), seed, 4)
+    return torch.tanh(x @ mix) + 0.3 * torch.sin(3.0 * (x @ mix))
+
+
+def _upstream(case, seed):
+    """Gradients of the substrate's weights with a common direction, as a loss over many samples gives them."""
+    P, S = case["genomes"], case["grid"] ** 2
+    return 1.0 + _normal((P, S, S), seed, 9), 1.0 + _normal((P, case["outputs"], S), seed, 10)
+
+
+# ------------------------------------------------------------------- one pass
+
+
+def prepare(case, seed):
+    kind, s = case["kind"], dict(case=case)
+    if kind == "substrate":
+        P, S, B, m = case["genomes"], case["grid"] ** 2, case["batch"], case["outputs"]
+        # tanh-bounded weights with the small ones pruned, as a CPPN query leaves them
+        weights = lambda shape, salt: (lambda w: torch.where(w.abs() < 0.2, 0.0, w))(
+            torch.tanh(_normal(shape, seed, salt))).bfloat16()
+        s.update(w1=weights((P, S, S), 5), w2=weights((P, m, S), 6), x=_normal((P, B, S), seed, 7).bfloat16(),
+                 dy=_normal((P, B, m), seed, 8))
+        return s
+    pop = s["pop"] = _made(case, seed)
+    P = case["genomes"]
+    if kind in ("fitness", "evaluate", "uneven"):
+        s["tr"] = tn.Transformed(pop)
+    if kind in ("forward", "mse", "query", "cppn_grad", "uneven"):
+        s["tr"] = tn.transform(pop)
+    if kind in ("fitness", "forward", "evaluate", "uneven", "mse", "autograd", "recurrent"):
+        s["obs"] = _observations(case, seed)
+    if kind in ("fitness", "mse"):
+        s["target"] = _targets(case, seed)
+    if kind in ("forward", "evaluate", "uneven", "recurrent"):
+        s["out"] = torch.empty((P, case["batch"], case["n_out"]), device=DEVICE)
+    if kind == "uneven":
+        s["plan"] = tn.Plan(pop, s["tr"], case["batch"])
+        s["plan"].tune(s["obs"], s["out"])
+    if kind == "autograd":
+        s["w"], s["b"] = (pop.t[k].clone().requires_grad_() for k in ("conn_w", "node_bias"))
+        s["dy"] = _normal((P, case["batch"], case["n_out"]), seed, 8)
+    if kind == "cppn_grad":
+        S = case["grid"] ** 2
+        s["dw1"], s["dw2"] = _upstream(case, seed)
+    if kind == "generation":
+        nu, nz = tn.reproduce_draws(case["nodes"], case["conns"])
+        uniform = lambda shape, salt: torch.rand(shape, generator=_generator(seed, salt), device=DEVICE)
+        s["params"] = tn.NeatParams(max_species=case["species"], compatibility_threshold=case["threshold"])
+        s["table"] = tn.SpeciesTable(case["species"], case["nodes"], case["conns"], torch.device(DEVICE, 0))
+        s.update(sel=uniform((P, 2), 11), U=uniform((P, nu), 12), Z=_normal((P, nz), seed, 13),
+                 fitness=_normal((P,), seed, 14))
+        # the species of the generation before this one
+        tn.neat_generation(pop, s["fitness"].flip(0), 0, s["table"], s["sel"], s["U"], s["Z"], 1 << 24, s["params"])
+    return s
+
+
+TRANSFORMED = ("status", "n_valid", "order", "level", "row_ptr", "edge_src", "edge_row", "edge_w", "pos_bias",
+               "pos_resp", "pos_fn", "io_pos", "pos_row", "n_rows", "prog_node", "prog_edge", "prog_rows", "prog_rec")
+
+
+def _transformed(tr):
+    return {k: getattr(tr, k) for k in TRANSFORMED}
+
+
+def run(s):
+    case = s["case"]
+    kind = case["kind"]
+    if kind == "fitness":
+        tr = tn.transform(s["pop"], s["tr"])
+        loss, y = tn.forward_loss(s["pop"], tr, s["obs"], s["target"], scale=-1.0,
+                                  offset=float(case["batch"] * case["n_out"]))
+        return {"fitness": loss, "y": y}
+    if kind == "forward":
+        return {"y": tn.forward(s["pop"], s["tr"], s["obs"], s["out"])}
+    if kind == "evaluate":
+        tr = tn.transform(s["pop"], s["tr"])
+        return {"y": tn.forward(s["pop"], tr, s["obs"], s["out"]), **_transformed(tr)}
+    if kind == "uneven":
+        tr = tn.transform(s["pop"], s["tr"])
+        return {"y": s["plan"].forward(s["obs"], s["out"]), **_transformed(tr)}
+    if kind == "mse":
+        loss, dw, db = tn.forward_backward_mse(s["pop"], s["tr"], s["obs"], s["target"])
+        return {"loss": loss, "dw": dw, "db": db}
+    if kind == "autograd":
+        y = autograd.TNForward.apply(s["pop"], s["obs"], s["w"], s["b"])
+        dw, db = torch.autograd.grad(y, (s["w"], s["b"]), s["dy"])
+        return {"y": y, "dw": dw, "db": db}
+    if kind == "query":
+        w1, w2 = tn.cppn_query(s["pop"], s["tr"], case["grid"], case["outputs"])
+        return {"w1": w1, "w2": w2}
+    if kind == "substrate":
+        h, y = tn.substrate_forward(s["w1"], s["w2"], s["x"], case["grid"], case["outputs"])
+        dw1, dw2 = tn.substrate_backward(s["w2"], s["x"], h, s["dy"], case["grid"], case["outputs"])
+        return {"h": h, "y": y, "dw1": dw1, "dw2": dw2}
+    if kind == "cppn_grad":
+        dw, db = tn.cppn_backward(s["pop"], s["tr"], s["dw1"], s["dw2"], case["grid"], case["outputs"])
+        return {"dw": dw, "db": db}
+    if kind == "recurrent":
+        return {"y": tn.forward_recurrent(s["pop"], s["obs"], case["sweeps"], s["out"])}
+    if kind == "generation":
+        t = s["table"]
+        children, species, parents, next_key = tn.neat_generation(
+            s["pop"], s["fitness"], 1, t, s["sel"], s["U"], s["Z"], 1 << 24, s["params"])
+        return {"children": children.t, "species": species, "parents": parents, "next_key": next_key,
+                "reps": t.reps, "table": [t.alive, t.best, t.last_improved, t.size]}
+    if case["node_genes"]:
+        return list(tn.distance_nodes(s["pop"]))
+    return list(tn.distance(s["pop"]))
+
+
+# ----------------------------------------------------------- bytes, operations
+
+
+def _sizes(case):
+    """Expected node rows, connection rows and enabled connections of one genome."""
+    if case["kind"] == "uneven":
+        hidden = (MAX_HIDDEN - MIN_HIDDEN) / math.log(MAX_HIDDEN / MIN_HIDDEN)
+        return case["n_in"] + case["n_out"] + hidden, 3 * hidden, 0.85 * 3 * hidden
+    steps = case["mutations"] * (0.5 if case["nodes"] <= 16 else 1.0)
+    nodes = min(case["nodes"], case["n_in"] + case["n_out"] + steps / 3)
+    conns = min(case["conns"], case["n_in"] * case["n_out"] + 4 * steps / 3)
+    if case["kind"] == "recurrent":
+        conns = min(case["conns"], conns + 12)
+    return nodes, conns, (conns - steps / 3) * (1 - case["disabled"])
+
+
+def work(case):
+    kind, P = case["kind"], case["genomes"]
+    if kind == "substrate":
+        S, B, m = case["grid"] ** 2, case["batch"], case["outputs"]
+        return {"bytes": P * (2 * S * S + 2 * S * m + 2 * B * S + 4 * B * S + 4 * B * m + 4 * B * m + 4 * S * S + 4 * S * m),
+                "flops": P * 2 * B * (2 * S * S + 3 * S * m)}
+    nodes, conns, edges = _sizes(case)
+    rows = 14 * nodes + 13 * conns          # the population's rows
+    program = 16 * nodes + 8 * edges        # what an evaluation reads of a transformed genome
+    arrays = 44 * nodes + 20 * conns + 64 * nodes  # what the transformation writes
+    if kind in ("query", "cppn_grad"):
+        S, m = case["grid"] ** 2, case["outputs"]
+        q = S * S + S * m
+        if kind == "query":
+            return {"bytes": P * (program + 2 * q), "flops": P * 2 * q * edges}
+        return {"bytes": P * (program + 4 * q + 4 * nodes + 4 * conns), "flops": P * 6 * q * edges}
+    if kind == "generation":
+        draws = 4 * (20 + 9 * case["nodes"] + 3 * case["conns"])
+        return {"bytes": P * (2 * rows + draws + 16), "flops": P * case["species"] * (nodes + conns)}
+    if kind == "distance":
+        return {"bytes": P * rows + 12 * P * P, "flops": P * P / 2 * (nodes + conns)}
+    B, I, O = case["batch"], case["n_in"], case["n_out"]
+    x = 4 * B * I * (1 if kind in ("fitness", "mse") else P)
+    if kind == "fitness":
+        return {"bytes": P * (rows + 4 * B * O + 4) + x, "flops": 2 * P * B * edges}
+    if kind == "forward":
+        return {"bytes": P * (program + 4 * B * O) + x, "flops": 2 * P * B * edges}
+    if kind in ("evaluate", "uneven"):
+        return {"bytes": P * (rows + arrays + 4 * B * O) + x, "flops": 2 * P * B * edges}
+    if kind == "mse":
+        return {"bytes": P * (program + 4 * nodes + 4 * conns) + x, "flops": 6 * P * B * edges}
+    if kind == "autograd":
+        return {"bytes": P * (rows + 8 * B * O + 4 * nodes + 4 * conns) + x, "flops": 6 * P * B * edges}
+    return {"bytes": P * (rows + 4 * B * O) + x, "flops": 2 * P * B * edges * case["sweeps"]}
+
+
+# ------------------------------------------------------------- in 64 bits
+
+
+def _activate(act, z):
+    """act [n], z [n][B]"""
+    out = z.clone()
+    for code, f in ((SIGMOID, torch.sigmoid), (TANH, torch.tanh), (RELU, torch.relu), (SIN, torch.sin),
+                    (GAUSSIAN, lambda v: torch.exp(-v * v)), (ABS, torch.abs)):
+        at = (act == code).nonzero()[:, 0]
+        if at.numel():
+            out[at] = f(z[at])
+    return out
+
+
+def _slope(act, z, v):
+    """d act / dz at z, where v = act(z)."""
+    out = torch.ones_like(z)
+    for code, f in ((SIGMOID, lambda z, v: v * (1 - v)), (TANH, lambda z, v: 1 - v * v),
+                    (RELU, lambda z, v: (z > 0).double()), (SIN, lambda z, v: torch.cos(z)),
+                    (GAUSSIAN, lambda z, v: -2 * z * v), (ABS, lambda z, v: torch.sign(z))):
+        at = (act == code).nonzero()[:, 0]
+        if at.numel():
+            out[at] = f(z[at], v[at])
+    return out
+
+
+class _Net:
+    """All genomes' networks as one graph: nodes numbered over the population, enabled connections with their row."""
+
+    def __init__(self, case, seed):
+        if case["kind"] == "uneven":
+            arrays, off, _, src, dst = _uneven(case, seed)
+            self.base = off[:-1]
+            every = torch.arange(src.numel(), device=DEVICE)
+        else:
+            arrays, src, dst = _grown(case, seed)
+            self.base = torch.arange(case["genomes"], device=DEVICE) * case["nodes"]
+            src, dst = ((t + self.base[:, None]).reshape(-1) for t in (src, dst))
+            every = torch.arange(src.numel(), device=DEVICE)
+        self.case, self.shape = case, arrays["conn_w"].shape
+        self.edge = every[arrays["conn_en"].reshape(-1) != 0]
+        self.src, self.dst = src[self.edge], dst[self.edge]
+        self.w = arrays["conn_w"].reshape(-1)[self.edge].double()
+        self.bias, self.act = arrays["node_bias"].reshape(-1).double(), arrays["node_act"].reshape(-1)
+        self.n = self.bias.numel()
+        self.node_shape = arrays["node_bias"].shape
+        self.inputs = (self.base[:, None] + torch.arange(case["n_in"], device=DEVICE)).reshape(-1)
+        self.outputs = (self.base[:, None] + case["n_in"] + torch.arange(case["n_out"], device=DEVICE)).reshape(-1)
+        self.computed = arrays["node_key"].reshape(-1) >= case["n_in"]
+
+    def genome(self, g):
+        """Genome g of a padded population on its own."""
+        N, C, one = self.case["nodes"], self.case["conns"], copy.copy(self)
+        e = (self.edge // C == g).nonzero()[:, 0]
+        rows = slice(g * N, (g + 1) * N)
+        one.case, one.n, one.shape, one.node_shape = dict(self.case, genomes=1), N, (C,), (N,)
+        one.src, one.dst, one.w, one.edge = self.src[e] - g * N, self.dst[e] - g * N, self.w[e], self.edge[e] - g * C
+        one.bias, one.act, one.computed = self.bias[rows], self.act[rows], self.computed[rows]
+        one.inputs = torch.arange(self.case["n_in"], device=DEVICE)
+        one.outputs = self.case["n_in"] + torch.arange(self.case["n_out"], device=DEVICE)
+        return one
+
+    def order(self):
+        """The graph's levels: for each the computed nodes and the enabled connections into them."""
+        level = torch.zeros(self.n, dtype=torch.int64, device=DEVICE)
+        while True:
+            new = level.scatter_reduce(0, self.dst, level[self.src] + 1, "amax")
+            if torch.equal(new, level):
+                break
+            level = new
+        into = level[self.dst]
+        return [(((level == k) & self.computed).nonzero()[:, 0], (into == k).nonzero()[:, 0])
+                for k in range(int(level.max()) + 1)]
+
+    def forward(self, x):
+        """Pre-activations and values [n][B] for x [P][B][I]."""
+        v = torch.zeros((self.n, x.shape[1]), dtype=torch.float64, device=DEVICE)
+        v[self.inputs] = x.double().transpose(1, 2).reshape(-1, x.shape[1])
+        z = torch.zeros_like(v)
+        z[:] = self.bias[:, None]
+        for nodes, edges in self.order():
+            for e in edges.split(1 << 18):
+                z.index_add_(0, self.dst[e], self.w[e, None] * v[self.src[e]])
+            v[nodes] = _activate(self.act[nodes], z[nodes])
+        return z, v
+
+    def out(self, v):
+        return v[self.outputs].view(self.case["genomes"], self.case["n_out"], -1).transpose(1, 2)
+
+    def backward(self, z, v, dy):
+        """Gradients shaped as the connection and the node rows for dy [P][B][O]."""
+        d = torch.zeros_like(v)
+        d[self.outputs] = dy.double().transpose(1, 2).reshape(-1, dy.shape[1])
+        dw = torch.zeros(math.prod(self.shape), dtype=torch.float64, device=DEVICE)
+        db = torch.zeros(self.n, dtype=torch.float64, device=DEVICE)
+        for nodes, edges in reversed(self.order()):
+            d[nodes] *= _slope(self.act[nodes], z[nodes], v[nodes])
+            db[nodes] = d[nodes].sum(1)
+            for e in edges.split(1 << 18):
+                dw[self.edge[e]] = (d[self.dst[e]] * v[self.src[e]]).sum(1)
+                d.index_add_(0, self.src[e], self.w[e, None] * d[self.dst[e]])
+        return dw.view(self.shape), db.view(self.node_shape)
+
+
+def _queries(case):
+    """The CPPN inputs (x_s, y_s, x_t, y_t, 1) of w1t's and w2t's entries, [5][Q]."""
+    n, m = case["grid"], case["outputs"]
+    at = lambda k: -1.0 + 2.0 * torch.arange(k, dtype=torch.float64, device=DEVICE) / max(k - 1, 1)
+    sx, sy = at(n).repeat(n), at(n).repeat_interleave(n)
+    ox = at(m) if m > 1 else torch.zeros(1, dtype=torch.float64, device=DEVICE)
+    tx, ty = torch.cat([sx, ox]), torch.cat([sy, torch.zeros_like(ox)])
+    S, T = n * n, n * n + m
+    q = [sx.repeat(T), sy.repeat(T), tx.repeat_interleave(S), ty.repeat_interleave(S)]
+    return torch.stack(q + [torch.ones_like(q[0])])
+
+
+def _exact_query(case, seed, upstream=None):
+    net, S = _Net(case, seed), case["grid"] ** 2
+    x = _queries(case).t()[None]
+    values, grads = [], []
+    for g in range(case["genomes"]):
+        one = net.genome(g)
+        z, v = one.forward(x)
+        y = one.out(v)[0, :, 0]
+        if upstream is None:
+            values.append(torch.where(y.abs() < 0.2, 0.0, y).float())
+        else:
+            u = torch.cat([upstream[0][g].reshape(-1), upstream[1][g].reshape(-1)]).double()
+            grads.append(one.backward(z, v, torch.where(y.abs() < 0.2, 0.0, u)[None, :, None]))
+    if upstream is not None:
+        return {"dw": torch.stack([a for a, _ in grads]), "db": torch.stack([b for _, b in grads])}
+    w = torch.stack(values)
+    return {"w1": w[:, :S * S].reshape(-1, S, S).double(), "w2": w[:, S * S:].reshape(-1, case["outputs"], S).double()}
+
+
+def _exact_substrate(s):
+    w1, w2, x, dy = (s[k].double() for k in ("w1", "w2", "x", "dy"))
+    h = torch.empty((x.shape[0], x.shape[1], w1.shape[1]), dtype=torch.float64, device=DEVICE)
+    dw1, dw2, y = torch.empty_like(w1), torch.empty_like(w2), torch.empty_like(dy)
+    rounded = lambda t: t.float().bfloat16().double()  # where the substrate rounds to bfloat16
+    for g in range(x.shape[0]):
+        h[g] = torch.tanh(x[g] @ w1[g].t())
+        y[g] = rounded(h[g]) @ w2[g].t()
+        dw2[g] = dy[g].t() @ h[g]
+        dw1[g] = rounded((dy[g] @ w2[g]) * (1 - h[g] * h[g])).t() @ x[g]
+    return {"h": h, "y": y, "dw1": dw1, "dw2": dw2}
+
+
+def _exact_distances(case, seed):
+    a, _, _ = _grown(case, seed)
+    P, I = case["genomes"], case["n_in"]
+    kinds = [((a["conn_in"].long() << 32) | a["conn_out"].long(), a["conn_in"] >= 0, (a["conn_w"],), (a["conn_en"],))]
+    if case["node_genes"]:
+        kinds.insert(0, (a["node_key"].long(), a["node_key"] >= I, (a["node_bias"], a["node_resp"]),
+                         (a["node_act"], a["node_agg"])))
+    total, differing = 0.0, []
+    for key, valid, floats, codes in kinds:
+        names, col = torch.unique(key[valid], return_inverse=True)
+        row = valid.nonzero()[:, 0]
+        table = lambda t: torch.zeros((P, names.numel()), dtype=torch.float64, device=DEVICE).index_put_(
+            (row, col), t[valid].double())
+        has = table(torch.ones_like(floats[0]))
+        shared, apart = has @ has.t(), torch.zeros((P, P), dtype=torch.float64, device=DEVICE)
+        n = has.sum(1)
+        larger = torch.maximum(n[:, None], n)
+        floats, codes = [table(t) for t in floats], [table(t) for t in codes] if case["node_genes"] else []
+        for i in range(P):
+            off = sum((t - t[i]).abs() for t in floats) + sum((t != t[i]).double() for t in codes)
+            apart[i] = (off * has * has[i]).sum(1)
+        alone = n[:, None] + n - 2 * shared
+        differing.append(alone)
+        if case["node_genes"]:
+            total = total + torch.where(larger > 0, (alone + 0.5 * apart) / larger.clamp(min=1), 0.0)
+        else:
+            total = alone / larger.clamp(min=1) + 0.4 * torch.where(shared > 0, apart / shared.clamp(min=1), 0.0)
+    return [total, None, None]
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind == "generation":  # rows of the parents, and draws added in 32 bits by the rules of the call
+        return None
+    if kind == "substrate":
+        return _exact_substrate(prepare(case, seed))
+    if kind == "distance":
+        return _exact_distances(case, seed)
+    if kind == "query":
+        return _exact_query(case, seed)
+    if kind == "cppn_grad":
+        return _exact_query(case, seed, _upstream(case, seed))
+    net, x = _Net(case, seed), _observations(case, seed)
+    x = x.expand(case["genomes"], *x.shape[-2:])
+    if kind == "recurrent":
+        v = torch.zeros((net.n, case["batch"]), dtype=torch.float64, device=DEVICE)
+        v[net.inputs] = x.double().transpose(1, 2).reshape(-1, case["batch"])
+        at = net.computed.nonzero()[:, 0]
+        for _ in range(case["sweeps"]):
+            z = net.bias[:, None].repeat(1, case["batch"])
+            for e in torch.arange(net.src.numel(), device=DEVICE).split(1 << 17):
+                z.index_add_(0, net.dst[e], net.w[e, None] * v[net.src[e]])
+            v[at] = _activate(net.act[at], z[at])
+        return {"y": net.out(v)}
+    z, v = net.forward(x)
+    y = net.out(v)
+    if kind == "fitness":
+        t = _targets(case, seed).double()
+        return {"fitness": case["batch"] * case["n_out"] - (y - t).square().sum((1, 2)), "y": y}
+    if kind == "mse":
+        t = _targets(case, seed).double()
+        dw, db = net.backward(z, v, 2 * (y - t) / (case["batch"] * case["n_out"]))
+        return {"loss": (y - t).square().mean((1, 2)), "dw": dw, "db": db}
+    if kind == "autograd":
+        dw, db = net.backward(z, v, _normal((case["genomes"], case["batch"], case["n_out"]), seed, 8))
+        return {"y": y, "dw": dw, "db": db}
+    return {"y": y, **{k: None for k in TRANSFORMED}} if kind != "forward" else {"y": y}
