@@ -70,8 +70,9 @@ def listed():
         dict(name="cppn_grad", kind="cppn_grad", grid=32, outputs=8, **_cppn(50)),
         # recurrent controllers, ten sweeps for each observation
         dict(name="recurrent", kind="recurrent", batch=1000, sweeps=10, **_control(1000)),
-        # speciation, offspring counts and reproduction of one generation of control policies
-        dict(name="generation", kind="generation", species=10, threshold=3.5, **_control(5000)),
+        # speciation, offspring counts and reproduction of one generation of control policies; their distances lie
+        # around 2.7, so the population spreads over every slot of its species table
+        dict(name="generation", kind="generation", species=10, threshold=2.5, **_control(5000)),
         # the speciation distance of every pair, over node and connection genes
         dict(name="distances", kind="distance", node_genes=True, **_control(1000)),
     ]
@@ -116,8 +117,8 @@ def draw(rng):
     if kind == "recurrent":
         return dict(kind=kind, batch=between(1, 1000), sweeps=rng.randint(1, 10), **policies(50, 1000))
     if kind == "generation":
-        return dict(kind=kind, species=rng.randint(5, 30), threshold=round(rng.uniform(0.6, 3.5), 2),
-                    **policies(150, 4000))
+        return dict(kind=kind, species=rng.randint(5, 30), threshold=round(rng.uniform(2.3, 3.5), 2),
+                    **policies(150, 2000))
     return dict(kind=kind, node_genes=rng.random() < 0.5, **policies(100, 1000))
 
 
@@ -241,7 +242,7 @@ def _uneven(case, seed):
     d = I + (rand(cg.numel()) * (O + H[cg])).long()
     fits = place[node_off[cg] + s] < place[node_off[cg] + d]
     pairs = torch.unique((cg[fits] << 20) | (s[fits] << 10) | d[fits])
-    order = torch.argsort((pairs >> 20).double() + rand(pairs.numel()).double())
+    order = torch.argsort((pairs >> 20).double() + rand(pairs.numel()).double(), stable=True)
     pairs = pairs[order]
     cg = pairs >> 20
     first = torch.searchsorted(cg, torch.arange(P, device=DEVICE))
@@ -338,9 +339,10 @@ def prepare(case, seed):
         nu, nz = tn.reproduce_draws(case["nodes"], case["conns"])
         uniform = lambda shape, salt: torch.rand(shape, generator=_generator(seed, salt), device=DEVICE)
         s["params"] = tn.NeatParams(max_species=case["species"], compatibility_threshold=case["threshold"])
-        s["table"] = tn.SpeciesTable(case["species"], case["nodes"], case["conns"], torch.device(DEVICE, 0))
         s.update(sel=uniform((P, 2), 11), U=uniform((P, nu), 12), Z=_normal((P, nz), seed, 13),
                  fitness=_normal((P,), seed, 14))
+        s["table"] = tn.neat_init(1, case["n_in"], case["n_out"], case["nodes"], case["conns"], s["Z"][:1],
+                                  max_species=case["species"])[1]
         # the species of the generation before this one
         tn.neat_generation(pop, s["fitness"].flip(0), 0, s["table"], s["sel"], s["U"], s["Z"], 1 << 24, s["params"])
     return s
