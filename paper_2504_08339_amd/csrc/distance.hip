@@ -304,6 +304,11 @@ __device__ __forceinline__ float attr_distance(Gene p, float a0, float a1, uint3
   return t;
 }
 
+__global__ __launch_bounds__(kWave) void prep_nodes_kernel(PopView pop, WsN ws, int SN, int SC) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  prep_genes<false>(pop, ws, blockIdx.x, SN, SC, smem);
+}
+
 // Inserts row genome i's genes of one kind into an LDS hash of HC slots.
 __device__ __forceinline__ void fill_hash(const GeneList& l, int P, int i, int n, int HC,
                                           long long* hk, Gene* hv) {
@@ -486,8 +491,7 @@ size_t distance_nodes_workspace_bytes(int P, int N_max, int C_max) {
 
 int launch_distance_nodes(const tn_population& p, float c_d, float c_h, void* workspace,
                           float* dist, int32_t* DN, int32_t* DC, hipStream_t stream) {
-  const int S = next_pow2(std::max(p.N_max, p.C_max));
-  const size_t prep_lds = (sizeof(long long) + sizeof(int32_t)) * (size_t)S;
+  const size_t prep_lds = prep_nodes_lds(p.N_max, p.C_max);
   const int HN = next_pow2(2 * p.N_max), HC = next_pow2(2 * p.C_max);
   const size_t per_row = (sizeof(long long) + sizeof(Gene)) * (size_t)(HN + HC);
   const int R = (int)std::max<size_t>(1, std::min<size_t>(kMaxRows, (64 * 1024) / per_row));
@@ -497,7 +501,7 @@ int launch_distance_nodes(const tn_population& p, float c_d, float c_h, void* wo
   if (rc != TN_OK || p.P == 0) return rc;
   WsN ws = carve_nodes(workspace, p.P, p.N_max, p.C_max);
   hipLaunchKernelGGL(prep_nodes_kernel, dim3(p.P), dim3(kWave), prep_lds, stream, make_view(p),
-                     ws, S);
+                     ws, gene_pow2(p.N_max), gene_pow2(p.C_max));
   rc = check_launch();
   if (rc != TN_OK) return rc;
   dim3 grid((p.P + kPairBlock - 1) / kPairBlock, (p.P + R - 1) / R);

@@ -35,8 +35,8 @@ inline int gene_pow2(int x) {
 }
 
 struct GeneList {
-  long long* keyT;   // [cap][P]
-  int32_t* hT;       // [cap][P] hash_mark of the key
+  long long* keyT;   // [cap][P], or [P][cap] (see prep_genes), as the others
+  int32_t* hT;       // [cap][P] hash of the key (position-major lists only)
   float* a0T;        // [cap][P]
   float* a1T;        // [cap][P]
   uint32_t* codeT;   // [cap][P] c0 | c1 << 8
@@ -111,11 +111,19 @@ __device__ void wave_bitonic(long long* key, int32_t* row, int S) {
   }
 }
 
-__global__ __launch_bounds__(kWave) void prep_nodes_kernel(PopView pop, WsN ws, int S) {
-  extern __shared__ __align__(16) unsigned char smem[];
+// Sorted gene lists of genome g by one wavefront; SN / SC: powers of two
+// holding the node / connection row capacities, smem: prep_nodes_lds bytes.
+// Position-major lists (entry k of genome g at k * P + g, with each key's
+// hash) let 64 genomes' k-th genes be read as consecutive words; kByGenome
+// stores genome-major lists (g * capacity + k, no hashes) for readers that
+// take one genome's genes across their lanes, and its own stores are then
+// consecutive words instead of one cache line each.
+template <bool kByGenome>
+__device__ __forceinline__ void prep_genes(const PopView& pop, const WsN& ws, int g, int SN, int SC,
+                                           unsigned char* smem) {
+  const int S = SN > SC ? SN : SC;
   long long* key = (long long*)smem;               // [S]
   int32_t* row = (int32_t*)(smem + sizeof(long long) * S);  // [S]
-  const int g = blockIdx.x;
   const int lane = lane_id();
   const int P = pop.P;
   const int64_t nb = pop.node_base(g), cb = pop.conn_base(g);
@@ -141,12 +149,12 @@ __global__ __launch_bounds__(kWave) void prep_nodes_kernel(PopView pop, WsN ws, 
     }
     n += __popcll(m);
   }
-  for (int i = n + lane; i < S; i += kWave) {
+  for (int i = n + lane; i < SN; i += kWave) {
     key[i] = kGenePad;
     row[i] = -1;
   }
   wave_sync();
-  wave_bitonic(key, row, S);
+  wave_bitonic(key, row, SN);
   bool dup = false;
   for (int i = lane + 1; i < n; i += kWave) dup |= key[i] == key[i - 1];
   int n_inputs = 0;
@@ -157,9 +165,9 @@ __global__ __launch_bounds__(kWave) void prep_nodes_kernel(PopView pop, WsN ws, 
   for (int k = lane; k < nn; k += kWave) {
     const long long kk = key[n_inputs + k];
     const int r = row[n_inputs + k];
-    const int64_t o = (int64_t)k * P + g;
+    const int64_t o = kByGenome ? (int64_t)g * pop.N_max + k : (int64_t)k * P + g;
     ws.nodes.keyT[o] = kk;
-    ws.nodes.hT[o] = (int32_t)gene_hash(kk);
+    if (!kByGenome) ws.nodes.hT[o] = (int32_t)gene_hash(kk);
     ws.nodes.a0T[o] = pop.node_bias[nb + r];
     ws.nodes.a1T[o] = pop.node_resp[nb + r];
     ws.nodes.codeT[o] = (uint32_t)pop.node_act[nb + r] | ((uint32_t)pop.node_agg[nb + r] << 8);
@@ -182,21 +190,21 @@ __global__ __launch_bounds__(kWave) void prep_nodes_kernel(PopView pop, WsN ws, 
     }
     n += __popcll(m);
   }
-  for (int i = n + lane; i < S; i += kWave) {
+  for (int i = n + lane; i < SC; i += kWave) {
     key[i] = kGenePad;
     row[i] = -1;
   }
   wave_sync();
-  wave_bitonic(key, row, S);
+  wave_bitonic(key, row, SC);
   dup = false;
   for (int i = lane + 1; i < n; i += kWave) dup |= key[i] == key[i - 1];
   const bool dup_c = __ballot(dup) != 0;
   for (int k = lane; k < n; k += kWave) {
     const long long kk = key[k];
     const int r = row[k];
-    const int64_t o = (int64_t)k * P + g;
+    const int64_t o = kByGenome ? (int64_t)g * pop.C_max + k : (int64_t)k * P + g;
     ws.conns.keyT[o] = kk;
-    ws.conns.hT[o] = (int32_t)gene_hash(kk);
+    if (!kByGenome) ws.conns.hT[o] = (int32_t)gene_hash(kk);
     ws.conns.a0T[o] = pop.conn_w[cb + r];
     ws.conns.a1T[o] = 0.0f;
     ws.conns.codeT[o] = (uint32_t)(pop.conn_en[cb + r] != 0);
@@ -208,7 +216,7 @@ __global__ __launch_bounds__(kWave) void prep_nodes_kernel(PopView pop, WsN ws, 
   }
 }
 
-// LDS bytes of prep_nodes_kernel for capacities N, C.
+// LDS bytes of prep_genes for capacities N, C.
 inline size_t prep_nodes_lds(int N, int C) {
   return (sizeof(long long) + sizeof(int32_t)) * (size_t)gene_pow2(N > C ? N : C);
 }

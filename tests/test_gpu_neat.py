@@ -116,6 +116,17 @@ def test_many_species_and_odd_sizes():
     assert len(seen) >= 4
 
 
+@pytest.mark.parametrize("P", [1, 16, 17, 512, 513])
+def test_founding_rounds_at_the_edges(P):
+    """A partial and a full tile of 16 genomes, and both forms of the founding
+    rounds (one workgroup up to 512 genomes, one launch per round above): a low
+    threshold founds several species and fills the table."""
+    prm = on.NeatParams(compatibility_threshold=0.9, max_species=5,
+                        mutation=orp.MutationParams(act_default=1, node_add=0.4, conn_add=0.6))
+    seen = _chain(P, prm, 3, seed=7 + P)
+    assert P < 16 or len(seen) == 5
+
+
 def test_gpu_loop_on_xor_improves():
     """The loop with the fitness on the GPU (tn_forward_loss: 4 - SSE over the
     four XOR rows): every generation's parents are valid, the best fitness
