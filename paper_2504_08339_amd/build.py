@@ -79,8 +79,9 @@ def _rf_base(kernel: str) -> int:
 
 
 # kernels that keep an explicit register file (names as they appear mangled)
-RF_KERNELS = ("forward_rf", "cppn_query_kernel", "cppn_backward_kernel", "backward_rf_kernel")
-RF_SOURCES = ("forward_reg.hip", "hyperneat.hip", "backward.hip")
+RF_KERNELS = ("forward_rf", "cppn_query_kernel", "cppn_backward_kernel", "backward_rf_kernel",
+              "recurrent_rf_kernel")
+RF_SOURCES = ("forward_reg.hip", "hyperneat.hip", "backward.hip", "recurrent.hip")
 
 
 def check_register_file(src: str, extra=()) -> None:

@@ -112,6 +112,27 @@ __device__ __forceinline__ void rfk_set(int r, const float (&x)[rf_tiles(R)]) {
   }
 }
 
+// Rows r of register files f0 .. f0 + P - 1 := x[0 .. P-1] (P = K: one window
+// for all; two of four: one window for the pair; else one window each).
+template <int R>
+__device__ __forceinline__ void rf_set_part(int P, int f0, int r, const float (&x)[rf_tiles(R)]) {
+  constexpr int K = rf_tiles(R);
+  if (P == K) {
+    rfk_set<R>(r, x);
+  } else if (K == 4 && P == 2) {
+    if (f0 == 0)
+      asm volatile("s_set_gpr_idx_on %2, gpr_idx(DST)\n\ts_nop 1\n\tv_mov_b32 v56, %0\n\t"
+                   "v_mov_b32 v106, %1\n\ts_set_gpr_idx_off" ::"v"(x[0]),
+                   "v"(x[1]), "s"(r) : "m0");
+    else
+      asm volatile("s_set_gpr_idx_on %2, gpr_idx(DST)\n\ts_nop 1\n\tv_mov_b32 v156, %0\n\t"
+                   "v_mov_b32 v206, %1\n\ts_set_gpr_idx_off" ::"v"(x[0]),
+                   "v"(x[1]), "s"(r) : "m0");
+  } else {
+    for (int p = 0; p < P; ++p) rf_set((f0 + p) * R + r, x[p]);
+  }
+}
+
 // x[k] := row r of tile k for the rf_tiles(R) tiles, under one window.
 template <int R>
 __device__ __forceinline__ void rfk_get(int r, float (&x)[rf_tiles(R)]) {

@@ -148,3 +148,41 @@ def test_limits():
         tn.forward_recurrent(to_device(big), tensor(np.ones((3, 1), np.float32)), 2)
     Y = tn.forward_recurrent(dp, tensor(np.zeros((4, 0, 17), np.float32)), 3)
     assert Y.shape == (4, 0, 6)
+
+
+@pytest.mark.parametrize("n_in,computed", [(5, 15), (6, 15), (10, 30), (8, 31), (17, 61), (18, 61),
+                                           (3, 62), (70, 10)])
+@pytest.mark.parametrize("copies,B", [(33, 4100), (1, 70)])
+def test_register_form_at_its_edges(n_in, computed, copies, B):
+    """File rows n_in + 3 x computed of 50 / 51, 100 / 101, 200 / 201, 61 / 62
+    computed nodes and nodes of more than 64 in-edges, in launches of four tiles
+    per wavefront and of one: nodes with leading input in-edges, acyclic ones
+    that settle and cycles, every activation and aggregation."""
+    rng = np.random.default_rng(n_in * 100 + computed)
+    genomes = []
+    for g in range(4):
+        keys = list(range(n_in + 2)) + [200 + h for h in range(computed - 2)]
+        agg = lambda: 0 if rng.random() < 0.7 else int(rng.integers(0, 6))
+        nodes = [[k, float(rng.normal()), float(rng.choice([1.0, 0.5])), int(rng.integers(0, 7)),
+                  agg()] for k in keys]
+        conns = [[i, o, float(rng.normal() * 0.2), int(rng.random() < 0.9)]
+                 for i in range(n_in) for o in (n_in, n_in + 1)]
+        seen = {(c[0], c[1]) for c in conns}
+        for i, k in enumerate(keys[n_in + 2:]):  # some nodes read inputs alone, some earlier nodes
+            pool = keys[:n_in] + (keys[n_in + 2:n_in + 2 + i] if g % 2 else [])
+            for a in {int(a) for a in rng.choice(pool, size=3)}:
+                conns.append([a, k, float(rng.normal() * 0.4), 1])
+                seen.add((a, k))
+        for _ in range(computed // 3):
+            a, b = int(rng.choice(keys)), int(rng.choice(keys[n_in:]))
+            if (a, b) not in seen:
+                seen.add((a, b))
+                conns.append([a, b, float(rng.normal() * 0.4), 1])
+        genomes.append((nodes, conns))
+    pop = population_from_rows(genomes * copies, n_in, 2)
+    obs = rng.normal(size=(B, n_in)).astype(np.float32)
+    Y, st = gpu_recurrent(pop, obs, 5)
+    assert np.array_equal(Y[:4].view(np.uint32), Y[-4:].view(np.uint32))
+    rows = np.concatenate([np.arange(40), np.arange(B - 30, B)])  # first and last tiles
+    ref, cond, rst = oracle.recurrent_population(pop, obs[rows], 5, genomes=range(4), with_cond=True)
+    compare(Y[:4][:, rows], st[:4], ref, cond, rst)
