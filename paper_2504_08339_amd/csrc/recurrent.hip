@@ -19,7 +19,7 @@
 // (their partial sum is kept in a third row: the same additions in the same
 // order), and nodes whose value has settled (all sources inputs, or settled a
 // sweep earlier: copied once to the other row, then left alone).
-// recurrent_kernel takes the others: two LDS value buffers of N_max rows x 64,
+// recurrent_kernel takes the others and short runs: two LDS value buffers of N_max rows x 64,
 // the computed rows' records dealt round-robin to the wavefronts, one barrier
 // per sweep.
 // The sum aggregation accumulates with fused multiply-adds in ascending
@@ -808,8 +808,18 @@ int launch_forward_recurrent(const tn_population& p, const float* obs, int64_t o
   const size_t rf_lds = tables + kWaves * sizeof(float) * (size_t)stage;
   // The register form takes every genome it can hold (connection capacities
   // whose tables exceed the LDS leave it out); the LDS form is launched where
-  // a genome of these capacities could be too large for it.
-  rc = allow_lds((const void*)recurrent_rf_kernel, rf_lds);
+  // a genome of these capacities could be too large for it. A genome's tables
+  // and partial sums cost the register form more, and its wavefronts do not
+  // share a tile's nodes: short runs stay on the LDS form. 200 genomes (17 ->
+  // 6): 10 sweeps of 64 / 128 observations 40 / 73 us on the LDS form, 61 / 62 us
+  // on registers (256: 137 and 63), one sweep 13 / 18 against 32 / 33; 1000
+  // genomes (two rounds of register workgroups): 10 sweeps of 64 / 128 / 256
+  // 45 / 81 / 155 against 90 / 123 / 125, four sweeps of 256 / 500 72 / 137
+  // against 88 / 124. The lines lie where genomes of five inputs (fewer terms to
+  // keep) break even too.
+  const int64_t per = (B + kWave - 1) / kWave;
+  const bool pays = p.P <= 512 ? per * (T + 3) >= 28 : per * (T - 1) >= 32;
+  rc = pays ? allow_lds((const void*)recurrent_rf_kernel, rf_lds) : TN_EUNSUPPORTED;
   const bool rf = rc == TN_OK;
   if (rf) {
     hipLaunchKernelGGL(recurrent_rf_kernel, dim3(p.P), dim3(kBlock), rf_lds, stream, make_view(p),

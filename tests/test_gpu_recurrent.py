@@ -152,7 +152,7 @@ def test_limits():
 
 @pytest.mark.parametrize("n_in,computed", [(5, 15), (6, 15), (10, 30), (8, 31), (17, 61), (18, 61),
                                            (3, 62), (70, 10)])
-@pytest.mark.parametrize("copies,B", [(33, 4100), (1, 70)])
+@pytest.mark.parametrize("copies,B", [(33, 4100), (1, 270)])
 def test_register_form_at_its_edges(n_in, computed, copies, B):
     """File rows n_in + 3 x computed of 50 / 51, 100 / 101, 200 / 201, 61 / 62
     computed nodes and nodes of more than 64 in-edges, in launches of four tiles
