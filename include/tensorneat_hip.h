@@ -341,7 +341,9 @@ int tn_forward(const tn_population* pop, const tn_transformed* tr,
  *                  64. waves_per_genome (1..8) wavefronts share a workgroup;
  *                  genomes whose prog_rows exceeds `rows` get NaN outputs.
  *   TN_ENGINE_AUTO the library's choice for every genome (the other fields
- *                  are ignored): TN_ENGINE_REG for prog_rows <= 200 (rows
+ *                  are ignored): for N_max > 32 and B <= 16 (<= 32 for at most
+ *                  2048 genomes) one wavefront per genome with its lanes over the nodes of
+ *                  a level and the observations; else TN_ENGINE_REG for prog_rows <= 200 (rows
  *                  50, 100, 128, 160, 200 when B spans at least 4 tiles of
  *                  64; 100, 128, 160, 200 for 2 or 3 tiles; 32, 64, 96, 128,
  *                  160, 200 for one; each launch takes the genomes the

@@ -50,8 +50,8 @@ def sources():
 _UNIFORM = ["-mllvm", "-structurizecfg-skip-uniform-regions=true"]
 _ALIGN = ["-mllvm", "-align-all-nofallthru-blocks=5"]
 FILE_FLAGS = {f: _UNIFORM for f in ("transform.hip", "distance.hip")}
-FILE_FLAGS.update({f: _UNIFORM + _ALIGN for f in ("forward.hip", "forward_reg.hip", "hyperneat.hip",
-                                                  "backward.hip", "recurrent.hip")})
+FILE_FLAGS.update({f: _UNIFORM + _ALIGN for f in ("forward.hip", "forward_reg.hip", "forward_small.hip",
+                                                  "hyperneat.hip", "backward.hip", "recurrent.hip")})
 
 
 def _compile(src: str, extra) -> str:

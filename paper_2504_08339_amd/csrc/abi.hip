@@ -204,14 +204,17 @@ int tn_transform(const tn_population* pop, const tn_transformed* tr, hipStream_t
 }  // extern "C"
 
 namespace {
-
-// TN_ENGINE_AUTO: the register engine for every genome whose packed program
+// TN_ENGINE_AUTO: small batches take their own kernel (forward_small.hip);
+// otherwise the register engine for every genome whose packed program
 // fits in a 200-row register file, one launch per register-file size of
 // tn::reg_classes (smallest first, each skipping what an earlier one took),
 // and the level-parallel LDS engine for the rest (prog_rows <= N_max, so small
 // populations need fewer launches).
 int forward_auto(const tn_population& p, const tn_transformed& t, const float* obs,
                  int64_t stride, int B, float* out, hipStream_t stream) {
+  if (tn::small_batch(p, B))
+    return tn::launch_forward_small(p, t, obs, stride, B, nullptr, 0, 0.0f, 0.0f, out, nullptr,
+                                    stream);
   int cls[6];
   const int n = tn::reg_classes(B, cls);
   int lo = -1;
@@ -297,6 +300,9 @@ int tn_forward_loss(const tn_population* pop, const tn_transformed* tr, const fl
   rc = check_transformed(tr);
   if (rc != TN_OK) return rc;
   if (!loss || (B > 0 && !target)) return TN_EINVAL;
+  if (tn::small_batch(*pop, B))
+    return tn::launch_forward_small(*pop, *tr, obs, obs_genome_stride, B, target,
+                                    target_genome_stride, scale, offset, out, loss, stream);
   // the register files of the automatic choice, smallest first (each taking
   // the genomes the smaller ones could not; prog_rows <= N_max, so a small
   // population needs one launch), then the LDS engine above 200 rows

@@ -75,6 +75,22 @@ int launch_forward_loss(const tn_population& p, const tn_transformed& t, const f
                         int64_t obs_stride, int B, const float* target, int64_t target_stride,
                         float scale, float offset, float* out, float* loss, int skip_le,
                         hipStream_t stream);
+// Small batches (forward_small.hip): one wavefront per genome, lanes over
+// (node, observation) pairs; loss null: outputs only, else out may be null.
+// Taken up to 16 observations: at 10,000 genomes of 40 nodes 17 us against the
+// register engine's 51 at B = 1 and 28 against 54 at B = 16; at 2000 genomes of
+// up to 535 nodes 32 against 356 us and 137 against 359. Up to 32 where the
+// genomes alone do not fill the register engine's 2048 wavefronts: 15 against
+// 24 us at 1000 genomes (but 61 against 55 at 10,000, and 22 against 25 at B = 48).
+// Not where one launch of the smallest register file takes every genome
+// (N_max <= 32): 150 genomes of 16 rows 6.7 against 4.6 us, 10,000 12.2 against
+// 10.7.
+constexpr bool small_batch(const tn_population& p, int B) {
+  return p.N_max > 32 && B > 0 && (B <= 16 || (B <= 32 && p.P <= 2048));
+}
+int launch_forward_small(const tn_population& p, const tn_transformed& t, const float* obs,
+                         int64_t obs_stride, int B, const float* target, int64_t target_stride,
+                         float scale, float offset, float* out, float* loss, hipStream_t stream);
 // Largest row count the LDS engine holds at one observation per lane.
 int lds_rows_cap(const tn_population& p);
 // LDS bytes of one workgroup of the LDS engine (0 if the tile does not fit).

@@ -361,3 +361,43 @@ def test_auto_split_equals_single_engine(name):
     assert np.array_equal(Y.view(np.uint32), auto.view(np.uint32))
     ref = 1.0 + 0.5 * ((auto.astype(np.float64) - T) ** 2).sum(axis=(1, 2))
     np.testing.assert_allclose(loss, ref, rtol=2e-5)
+
+
+@pytest.mark.parametrize("B", [1, 2, 3, 8, 9, 16, 17, 32, 33])
+def test_small_batches_equal_the_lds_engine(B):
+    """The automatic choice at small batches (lanes over nodes and observations
+    up to 16, up to 32 for few genomes) gives the LDS engine's bits on uneven
+    ragged genomes and on wide nodes of every aggregation and activation with a
+    flagged genome among them; the fused loss agrees with the outputs."""
+    import paper_2504_08339_amd as tn
+    rng = np.random.default_rng(B)
+    keys = list(range(9))
+    genomes = []
+    for g in range(14):
+        nodes = [[k, float(rng.normal()), float(rng.choice([1.0, 0.5, -0.75])),
+                  int(rng.integers(0, 7)), g % 6 if k >= 5 else 0] for k in keys]
+        nodes += [[20 + h, float(rng.normal()), 1.0, int(rng.integers(0, 7)), (g + h) % 6]
+                  for h in range(70)]
+        conns = [[i, 20 + h, float(rng.normal() * 0.5), 1] for h in range(70) for i in range(5)
+                 if (h + i) % 3]
+        conns += [[20 + h, 5 + h % 4, float(rng.normal() * 0.5), int(h % 7 > 0)] for h in range(70)]
+        genomes.append((nodes, conns if g else conns + [[5, 20, 1.0, 1], [20, 5, 1.0, 1]]))
+    for pop in (population_from_rows(genomes, 5, 4),
+                synth.random_dag_population(30, 27, 8, np.random.default_rng(3))):
+        dp = to_device(pop)
+        tr = tn.transform(dp)
+        obs = tensor(rng.normal(size=(pop.P, B, pop.n_in)).astype(np.float32))
+        ref = host(tn.forward(dp, tr, obs, engine=tn.TN_ENGINE_LDS))
+        Y = host(tn.forward(dp, tr, obs))
+        flagged = host(tr.status)[:pop.P] != 0
+        assert np.isnan(Y[flagged]).all() and flagged.sum() == (1 if pop.n_in == 5 else 0)
+        assert np.array_equal(Y[~flagged].view(np.uint32), ref[~flagged].view(np.uint32))
+        target = rng.normal(size=(B, pop.n_out)).astype(np.float32)
+        loss, out = tn.forward_loss(dp, tr, obs, tensor(target), scale=-1.0, offset=4.0)
+        assert np.array_equal(host(out).view(np.uint32)[~flagged], ref[~flagged].view(np.uint32))
+        sse = ((ref[~flagged].astype(np.float64) - target) ** 2).sum((1, 2))
+        assert np.allclose(host(loss)[~flagged], 4.0 - sse, rtol=1e-5, atol=1e-5 * sse.max())
+        only, none = tn.forward_loss(dp, tr, obs, tensor(target), scale=-1.0, offset=4.0,
+                                     store_outputs=False)
+        assert none is None and np.array_equal(host(only).view(np.uint32), host(loss).view(np.uint32))
+        assert np.isnan(host(loss)[flagged]).all()
