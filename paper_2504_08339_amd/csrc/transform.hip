@@ -846,6 +846,11 @@ __global__ __launch_bounds__(kWave * kW) void transform_kernel(PopView pop, TrVi
 }
 
 }  // namespace
+}  // namespace tn
+
+#include "transform_small.hpp"
+
+namespace tn {
 
 size_t transform_lds_bytes(int N_max, int C_max) { return make_layout(N_max, C_max).bytes; }
 
@@ -905,8 +910,21 @@ int class_lds(const Layout& L) {
                    L.bytes);
 }
 
+// Whether a class of these capacities takes the one-wavefront mask kernel: 150
+// genomes of 16 / 32 rows 7.7 us (25.7 with transform_kernel), 1000 of 64 / 256
+// 17.9 us (40.1). As a first class of a large uneven ragged population, beside
+// the larger ones' launches, it changed nothing (1.40 ms with and without).
+bool small_class(const Layout& L) { return L.n_cap <= kSmallNodes && L.c_cap <= kSmallConns; }
+
 int launch_class(const tn_population& p, const tn_transformed& t, const Layout& L,
                  hipStream_t stream) {
+  if (small_class(L)) {
+    const auto kern = L.c_cap <= kWave ? transform_small_kernel<1>
+                      : L.c_cap <= 2 * kWave ? transform_small_kernel<2>
+                                             : transform_small_kernel<4>;
+    hipLaunchKernelGGL(kern, dim3(p.P), dim3(kWave), 0, stream, make_view(p), make_view(t), L);
+    return check_launch();
+  }
   const int waves = class_waves(L);
   const int rc = class_lds(L);
   if (rc != TN_OK) return rc;

@@ -249,6 +249,72 @@ def _malformed():
     return population_from_rows(cases, 2, 1, N_max=8, C_max=6)
 
 
+@pytest.mark.parametrize("N,C", [(8, 9), (63, 64), (64, 64), (64, 65), (64, 128), (64, 129),
+                                 (64, 256)])
+def test_small_genomes_equal_the_general_kernel(N, C):
+    """Genomes of at most 64 node and 256 connection rows (the mask kernel, with
+    one, two or four connection rows per lane): dense acyclic ones that fill
+    their rows, in shuffled rows with holes, and every defect. Each field equals
+    the oracle's and that of the same rows in larger capacities, which the
+    general kernel takes."""
+    rng = np.random.default_rng(1000 * N + C)
+    n_in, n_out = (2, 1) if N < 16 else (9, 3)
+    genomes = []
+    for g in range(40):
+        n = N if g % 4 == 0 else int(rng.integers(n_in + n_out, N + 1))
+        hidden = [500 + 7 * h for h in range(n - n_in - n_out)]
+        if g % 3 == 0:
+            hidden = [int(x) for x in rng.choice(2 ** 31 - 1000, size=len(hidden), replace=False) + 900]
+        ranked = list(range(n_in)) + hidden + list(range(n_in, n_in + n_out))
+        pairs = [(a, b) for i, a in enumerate(ranked) for b in ranked[i + 1:]
+                 if b >= n_in and not n_in <= a < n_in + n_out]
+        take = rng.permutation(len(pairs))[:C if g % 4 < 2 else max(1, C // 3)]
+        conns = [[*pairs[i], float(rng.normal()), int(rng.random() < 0.85)] for i in take]
+        nodes = [[k, float(rng.normal()), 1.0, int(rng.integers(0, 7)) * (k >= n_in),
+                  int(rng.integers(0, 6)) * (k >= n_in)] for k in ranked]
+        nodes = [nodes[i] for i in rng.permutation(n)]
+        while len(conns) < C and g % 2:
+            conns.insert(int(rng.integers(0, len(conns) + 1)), None)
+        if g >= 28 and conns[0] is not None and len(conns) > 2:
+            live = [i for i, c in enumerate(conns) if c is not None]
+            a, b = live[0], live[-1]
+            conns[b] = {0: [*conns[a][:2], 1.0, 0],                  # repeated marking
+                        1: [77777777, ranked[-1], 1.0, 1],           # dangling
+                        2: [77777777, 88888888, 1.0, 0],             # disabled dangling: fine
+                        3: [conns[a][1], 0, 1.0, 1],                 # ends at an input
+                        4: [conns[a][1], conns[a][1], 1.0, 1],       # a cycle
+                        5: conns[b]}[g % 6]
+            if g % 6 == 2 and len(live) > 3 and g > 32:
+                conns[live[1]] = [77777777, 88888888, 2.0, 0]        # the same twice: repeated
+            if g % 6 == 5:
+                nodes[0] = [nodes[-1][0], 0.0, 1.0, 0, 0] if g < 36 else [nodes[0][0], 0., 1., 9, 0]
+        genomes.append((nodes, conns))
+    genomes.append(([], []))
+    pop = population_from_rows(genomes, n_in, n_out, N_max=N, C_max=C)
+    got = run_transform(pop)
+    assert compare(pop, got) > 20
+    for g in range(pop.P):
+        if got["status"][g] == 0:
+            _check_rows(pop, got, g)
+            _check_prog(pop, got, g)
+    big = population_from_rows(genomes, n_in, n_out, N_max=N + 70, C_max=C + 260)
+    ref = run_transform(big)
+    for g in range(pop.P):
+        (ns, rb, cs), (nt, rc, ct) = blocks(pop, g), blocks(big, g)
+        for k in ("status", "n_valid", "n_rows", "prog_rows"):
+            assert got[k][g] == ref[k][g], (k, g)
+        nio = n_in + n_out
+        assert np.array_equal(got["io_pos"][g * nio:(g + 1) * nio], ref["io_pos"][g * nio:(g + 1) * nio])
+        assert np.array_equal(got["row_ptr"][rb:rb + N + 1], ref["row_ptr"][rc:rc + N + 1])
+        for k in ("order", "level", "pos_bias", "pos_resp", "pos_fn", "pos_row"):
+            assert np.array_equal(got[k][ns], ref[k][nt][:N]), (k, g)
+        for k in ("edge_src", "edge_row", "edge_w"):
+            assert np.array_equal(got[k][cs], ref[k][ct][:C]), (k, g)
+        for k, w, a, b, n in (("prog_node", 4, ns, nt, N), ("prog_rec", 16, ns, nt, N),
+                              ("prog_edge", 2, cs, ct, C)):
+            assert np.array_equal(got[k][w * a.start:w * a.stop], ref[k][w * b.start:w * (b.start + n)]), (k, g)
+
+
 def test_malformed_status_bits():
     pop = _malformed()
     got = run_transform(pop)
