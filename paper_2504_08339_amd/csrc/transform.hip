@@ -152,14 +152,6 @@ constexpr int kTfMaxWaves = 8;
 // Ragged populations of at least this many genomes are transformed by size class.
 constexpr int kTfClassMinGenomes = 2048;
 
-// Workgroup barrier that orders LDS accesses only: the kernel never reads back
-// what it stores to global memory, so its stores stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Workgroup-wide steps of the transform for workgroups of up to kW
 // wavefronts, over the threads in index order; with kW == 1 everything stays
 // inside the wavefront (no workgroup barrier). The multi-wavefront forms wait

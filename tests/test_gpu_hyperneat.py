@@ -432,3 +432,47 @@ def test_cppn_backward_through_the_substrate():
         want = np.concatenate([rw, rb])
         got = np.concatenate([dW[g], db[g]]).astype(np.float64)
         assert np.all(np.abs(got - want) <= 2.0 ** -5 * np.abs(want).max() + 1e-12), g
+
+
+@pytest.mark.parametrize("grid", [8, 16, 24])
+@pytest.mark.parametrize("B,m,shared,shift", [(1, 1, False, 0), (31, 8, True, 0), (33, 9, False, 0),
+                                              (128, 32, False, 0), (129, 8, False, 0),
+                                              (40, 17, False, 1)])
+def test_substrate_tiles_and_remainders(grid, B, m, shared, shift):
+    """Substrate forward and backward against float64 at the edges of their
+    tiles: S = 64, 256, 576, batches around 32 and 128 (the fused gradient's
+    largest), outputs around 8, 16 and 32, shared inputs, and weights and inputs
+    that are only 2-byte aligned. Bars of the substrate tests: K float32
+    additions of exact bfloat16 products, dz rounded to bfloat16."""
+    import paper_2504_08339_amd as tn
+    S, P = grid * grid, 3
+    gen = torch.Generator().manual_seed(grid * 1000 + B + m)
+    normal = lambda *shape: torch.randn(shape, generator=gen)
+
+    def placed(t):  # on the device, `shift` elements off an aligned start
+        flat = torch.zeros(t.numel() + shift, dtype=t.dtype, device="cuda")
+        flat[shift:] = t.reshape(-1).cuda()
+        return flat[shift:].view(t.shape)
+
+    w1 = torch.tanh(normal(P, S, S)).bfloat16()
+    w2 = torch.tanh(normal(P, m, S)).bfloat16()
+    x = normal(*((B, S) if shared else (P, B, S))).bfloat16()
+    dy = normal(P, B, m)
+    dw1, dw2 = placed(w1), placed(w2)
+    h, y = tn.substrate_forward(dw1, dw2, placed(x), grid, m)
+    g1, g2 = tn.substrate_backward(dw2, placed(x), h, dy.cuda(), grid, m)
+    h, y, g1, g2 = (t.cpu().double() for t in (h, y, g1, g2))
+    xd, w1d, w2d, d = x.double().expand(P, B, S), w1.double(), w2.double(), dy.double()
+    z = xd @ w1d.transpose(1, 2).contiguous()
+    scale = xd.abs() @ w1d.abs().transpose(1, 2).contiguous()
+    assert ((h - torch.tanh(z)).abs() <= 2.0 ** -14 * scale + 2.0 ** -21).all()
+    hb = h.float().bfloat16().double()
+    terms = hb.abs() @ w2d.abs().transpose(1, 2).contiguous()
+    assert ((y - hb @ w2d.transpose(1, 2).contiguous()).abs() <= 2.0 ** -14 * terms).all()
+    ht, dt = h.transpose(1, 2).contiguous(), d.transpose(1, 2).contiguous()
+    assert ((g2 - dt @ h).abs() <= 2.0 ** -17 * (dt.abs() @ h.abs()) + 2.0 ** -126).all()
+    dz = (d @ w2d) * (1 - h * h)
+    dz_terms = (d.abs() @ w2d.abs()) * (1 - h * h)
+    dzt = dz.transpose(1, 2).contiguous()
+    bar = 2.0 ** -8 * (dz_terms.transpose(1, 2).contiguous() @ xd.abs()) + 2.0 ** -126
+    assert ((g1 - dzt @ xd).abs() <= bar).all()
