@@ -111,35 +111,34 @@ __device__ void wave_bitonic(long long* key, int32_t* row, int S) {
   }
 }
 
-// Sorted gene lists of genome g by one wavefront; SN / SC: powers of two
-// holding the node / connection row capacities, smem: prep_nodes_lds bytes.
+// Sorted gene lists of consecutive genomes from g0 on, one wavefront of the
+// workgroup each (every thread calls it); SN / SC: powers of two holding the
+// node / connection row capacities, smem: prep_nodes_lds bytes per genome.
 // Position-major lists (entry k of genome g at k * P + g, with each key's
-// hash) let 64 genomes' k-th genes be read as consecutive words; kByGenome
-// stores genome-major lists (g * capacity + k, no hashes) for readers that
-// take one genome's genes across their lanes, and its own stores are then
-// consecutive words instead of one cache line each.
+// hash) let 64 genomes' k-th genes be read as consecutive words; they are
+// stored with consecutive threads on consecutive genomes. kByGenome stores
+// genome-major lists (g * capacity + k, no hashes) for readers that take one
+// genome's genes across their lanes.
 template <bool kByGenome>
-__device__ __forceinline__ void prep_genes(const PopView& pop, const WsN& ws, int g, int SN, int SC,
+__device__ __forceinline__ void prep_genes(const PopView& pop, const WsN& ws, int g0, int SN, int SC,
                                            unsigned char* smem) {
+  __shared__ int count[16];  // genes of each wavefront's genome
   const int S = SN > SC ? SN : SC;
-  long long* key = (long long*)smem;               // [S]
-  int32_t* row = (int32_t*)(smem + sizeof(long long) * S);  // [S]
-  const int lane = lane_id();
-  const int P = pop.P;
-  const int64_t nb = pop.node_base(g), cb = pop.conn_base(g);
-  const int64_t nrows = pop.node_rows(g), crows = pop.conn_rows(g);
-  if (nrows > pop.N_max || nrows < 0 || crows > pop.C_max || crows < 0) {
-    if (lane == 0) {
-      ws.cnt_n[g] = -1;
-      ws.cnt_c[g] = -1;
-    }
-    return;
-  }
+  const int lane = lane_id(), wave = wave_id(), G = blockDim.x / kWave;
+  const int P = pop.P, g = g0 + wave;
+  long long* keys = (long long*)smem;              // [G][S]
+  int32_t* rows = (int32_t*)(keys + (size_t)G * S);  // [G][S]
+  long long* key = keys + (size_t)wave * S;
+  int32_t* row = rows + (size_t)wave * S;
+  const bool real = g < P;
+  const int64_t nb = real ? pop.node_base(g) : 0, cb = real ? pop.conn_base(g) : 0;
+  const int64_t nrows = real ? pop.node_rows(g) : 0, crows = real ? pop.conn_rows(g) : 0;
+  const bool fits = nrows <= pop.N_max && nrows >= 0 && crows <= pop.C_max && crows >= 0;
   // node genes: every valid key is sorted (a repeated input key also leaves
-  // the genome without a gene set); the inputs, keys 0 .. n_in-1, come first
-  // and are skipped when storing
+  // the genome without a gene set); the inputs, keys 0 .. n_in-1, sort first
+  // and are dropped
   int n = 0;
-  for (int base = 0; base < (int)nrows; base += kWave) {
+  for (int base = 0; fits && base < (int)nrows; base += kWave) {
     const int r = base + lane;
     const int32_t k = r < nrows ? pop.node_key[nb + r] : -1;
     const uint64_t m = __ballot(k >= 0);
@@ -162,20 +161,32 @@ __device__ __forceinline__ void prep_genes(const PopView& pop, const WsN& ws, in
   const bool dup_n = __ballot(dup) != 0;
   n_inputs = wave_sum_int(n_inputs);
   const int nn = n - n_inputs;
-  for (int k = lane; k < nn; k += kWave) {
-    const long long kk = key[n_inputs + k];
-    const int r = row[n_inputs + k];
-    const int64_t o = kByGenome ? (int64_t)g * pop.N_max + k : (int64_t)k * P + g;
-    ws.nodes.keyT[o] = kk;
-    if (!kByGenome) ws.nodes.hT[o] = (int32_t)gene_hash(kk);
-    ws.nodes.a0T[o] = pop.node_bias[nb + r];
-    ws.nodes.a1T[o] = pop.node_resp[nb + r];
-    ws.nodes.codeT[o] = (uint32_t)pop.node_act[nb + r] | ((uint32_t)pop.node_agg[nb + r] << 8);
+  __shared__ int skipped[16];
+  if (lane == 0) {
+    count[wave] = nn;
+    skipped[wave] = n_inputs;
   }
-  wave_sync();
+  __syncthreads();
+  {
+    const int gi = kByGenome ? wave : threadIdx.x % G;
+    const int gg = g0 + gi;
+    const int64_t base = gg < P ? pop.node_base(gg) : 0;
+    for (int k = kByGenome ? lane : threadIdx.x / G; k < count[gi]; k += kWave) {
+      const size_t at = (size_t)gi * S + skipped[gi] + k;
+      const long long kk = keys[at];
+      const int64_t r = base + rows[at];
+      const int64_t o = kByGenome ? (int64_t)gg * pop.N_max + k : (int64_t)k * P + gg;
+      ws.nodes.keyT[o] = kk;
+      if (!kByGenome) ws.nodes.hT[o] = (int32_t)gene_hash(kk);
+      ws.nodes.a0T[o] = pop.node_bias[r];
+      ws.nodes.a1T[o] = pop.node_resp[r];
+      ws.nodes.codeT[o] = (uint32_t)pop.node_act[r] | ((uint32_t)pop.node_agg[r] << 8);
+    }
+  }
+  __syncthreads();
   // connection genes
   n = 0;
-  for (int base = 0; base < (int)crows; base += kWave) {
+  for (int base = 0; fits && base < (int)crows; base += kWave) {
     const int r = base + lane;
     int32_t a = -1, b = -1;
     if (r < crows) {
@@ -199,24 +210,34 @@ __device__ __forceinline__ void prep_genes(const PopView& pop, const WsN& ws, in
   dup = false;
   for (int i = lane + 1; i < n; i += kWave) dup |= key[i] == key[i - 1];
   const bool dup_c = __ballot(dup) != 0;
-  for (int k = lane; k < n; k += kWave) {
-    const long long kk = key[k];
-    const int r = row[k];
-    const int64_t o = kByGenome ? (int64_t)g * pop.C_max + k : (int64_t)k * P + g;
-    ws.conns.keyT[o] = kk;
-    if (!kByGenome) ws.conns.hT[o] = (int32_t)gene_hash(kk);
-    ws.conns.a0T[o] = pop.conn_w[cb + r];
-    ws.conns.a1T[o] = 0.0f;
-    ws.conns.codeT[o] = (uint32_t)(pop.conn_en[cb + r] != 0);
-  }
   if (lane == 0) {
-    const bool bad = dup_n || dup_c;
-    ws.cnt_n[g] = bad ? -1 : nn;
-    ws.cnt_c[g] = bad ? -1 : n;
+    count[wave] = n;
+    if (real) {
+      const bool bad = dup_n || dup_c || !fits;
+      ws.cnt_n[g] = bad ? -1 : nn;
+      ws.cnt_c[g] = bad ? -1 : n;
+    }
+  }
+  __syncthreads();
+  {
+    const int gi = kByGenome ? wave : threadIdx.x % G;
+    const int gg = g0 + gi;
+    const int64_t base = gg < P ? pop.conn_base(gg) : 0;
+    for (int k = kByGenome ? lane : threadIdx.x / G; k < count[gi]; k += kWave) {
+      const size_t at = (size_t)gi * S + k;
+      const long long kk = keys[at];
+      const int64_t r = base + rows[at];
+      const int64_t o = kByGenome ? (int64_t)gg * pop.C_max + k : (int64_t)k * P + gg;
+      ws.conns.keyT[o] = kk;
+      if (!kByGenome) ws.conns.hT[o] = (int32_t)gene_hash(kk);
+      ws.conns.a0T[o] = pop.conn_w[r];
+      ws.conns.a1T[o] = 0.0f;
+      ws.conns.codeT[o] = (uint32_t)(pop.conn_en[r] != 0);
+    }
   }
 }
 
-// LDS bytes of prep_genes for capacities N, C.
+// LDS bytes of prep_genes per genome for capacities N, C.
 inline size_t prep_nodes_lds(int N, int C) {
   return (sizeof(long long) + sizeof(int32_t)) * (size_t)gene_pow2(N > C ? N : C);
 }

@@ -126,3 +126,37 @@ def test_more_genomes_than_one_block():
     rng = np.random.default_rng(11)
     pairs = [tuple(p) for p in rng.integers(0, 700, size=(800, 2))] + [(699, 699), (0, 699)]
     check_pairs(pop, d, DN, DC, pairs)
+
+
+@pytest.mark.parametrize("P,N,C", [(1, 16, 40), (7, 24, 256), (514, 24, 64), (9, 64, 257),
+                                   (6, 300, 512), (5, 24, 513)])
+def test_shared_tables_equal_the_per_row_kernels(P, N, C):
+    """Both distances on shared row tables (four rows up to 256 connection rows,
+    two up to 512, then one table per row), partial blocks of rows and columns,
+    against the same genomes in capacities that take the per-row kernels: the
+    same bits and counts, with full and empty genomes and ones without a gene
+    set among them."""
+    import paper_2504_08339_amd as tn
+    rng = np.random.default_rng(P + N + C)
+    genomes = []
+    for g in range(P):
+        n = int(rng.integers(3, N + 1)) if g % 5 else N
+        hidden = rng.choice(4 * N, size=n - 3, replace=False) + 50
+        keys = [0, 1, 2] + [int(k) for k in hidden]
+        nodes = [[k, float(rng.normal()), float(rng.choice([1.0, 0.5])), int(rng.integers(0, 7)),
+                  int(rng.integers(0, 6))] for k in keys]
+        c = C if g % 4 == 1 else int(rng.integers(0, min(C, 60) + 1))
+        marks = rng.choice(40 * 40 if C < 1000 else 10 ** 6, size=c, replace=False)
+        conns = [[int(m) // 40, int(m) % 40, float(rng.normal()), int(rng.random() < 0.8)]
+                 for m in marks]
+        if g % 97 == 3 and c > 1:
+            conns[1] = list(conns[0])
+        if g % 89 == 4:
+            nodes[-1][0] = nodes[0][0]
+        genomes.append((nodes, conns))
+    pop = to_device(population_from_rows(genomes, 2, 1, N_max=N, C_max=C))
+    big = to_device(population_from_rows(genomes, 2, 1, N_max=max(N, 64), C_max=700))
+    for call in (tn.distance_nodes, tn.distance):
+        for got, ref in zip(call(pop), call(big)):
+            got, ref = host(got), host(ref)
+            assert np.array_equal(got.view(np.uint32), ref.view(np.uint32))
