@@ -575,11 +575,12 @@ int tn_cppn_backward(const tn_population* pop, const tn_transformed* tr, const t
  * The forward pass is recomputed inside the call (nothing is saved by
  * tn_forward). Batch sums run in a fixed order, so results are deterministic.
  * A flagged genome gets NaN in all its rows.
- * Limits: genomes with at most 48 positions, 64 enabled connections and sum or
- * mean aggregations take a register-file adjoint; the others take an LDS
+ * Limits: genomes with at most 64 positions, 192 enabled connections and sum
+ * or mean aggregations take a register-file adjoint; the others take an LDS
  * adjoint holding N_max rows of 65 values and of 65 gradients. When that
- * exceeds the device's LDS (N_max above about 300 on MI355X) those other
- * genomes get NaN gradients (the call still returns TN_OK).
+ * exceeds the device's LDS (N_max above about 300 on MI355X) genomes with more
+ * than 48 positions or 64 enabled connections and genomes with other
+ * aggregations get NaN gradients (the call still returns TN_OK).
  */
 int tn_backward(const tn_population* pop, const tn_transformed* tr,
                 const float* obs, int64_t obs_genome_stride, int32_t B,

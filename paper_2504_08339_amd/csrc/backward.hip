@@ -18,6 +18,7 @@
 // and relu; sin, gaussian and abs re-evaluate z from the in-edges. Non-sum
 // aggregations re-evaluate their terms in both phases.
 #include <algorithm>
+#include <type_traits>
 
 #include "fwd_core.hpp"
 
@@ -38,6 +39,8 @@ struct BwdArgs {
   float* loss;  // may be null
   float* dW;    // conn block
   float* db;    // node block
+  // positions and in-edges of a genome of backward_rf_kernel, at most
+  int rf_pos, rf_edges;
 };
 
 struct BwdLds {
@@ -99,6 +102,38 @@ __device__ __forceinline__ float act_slope(int act, float v, float z) {
   }
 }
 
+// act_slope of K values, one branch for all of them.
+template <int K>
+__device__ __forceinline__ void act_slopes(int act, const float (&v)[K], const float (&z)[K],
+                                           float (&d)[K]) {
+  if (act == TN_ACT_TANH) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) d[k] = act_slope(TN_ACT_TANH, v[k], z[k]);
+  } else if (act == TN_ACT_IDENTITY) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) d[k] = 1.0f;
+  } else if (act == TN_ACT_SIN) {
+    // one cosine at a time: the reduction of a large argument takes many
+    // registers
+    float zz[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) zz[k] = z[k];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      d[k] = act_slope(TN_ACT_SIN, v[k], zz[k]);
+      asm volatile("" : "+v"(d[k]), "+v"(zz[(k + 1) % K]));
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      float o = act == TN_ACT_SIGMOID ? act_slope(TN_ACT_SIGMOID, v[k], z[k])
+                                      : act_slope(TN_ACT_RELU, v[k], z[k]);
+      o = act == TN_ACT_GAUSSIAN ? act_slope(TN_ACT_GAUSSIAN, v[k], z[k]) : o;
+      d[k] = act == TN_ACT_ABS ? act_slope(TN_ACT_ABS, v[k], z[k]) : o;
+    }
+  }
+}
+
 __device__ __forceinline__ bool slope_needs_z(int act) {
   return act == TN_ACT_SIN || act == TN_ACT_GAUSSIAN || act == TN_ACT_ABS;
 }
@@ -127,21 +162,32 @@ __device__ float agg_partial(int agg, int e, int e0, int e1, const EdgeRec* edge
   return best == e ? 1.0f : 0.0f;
 }
 
-// Genomes the register-file adjoint (backward_rf_kernel, below) takes.
-constexpr int kRfPos = 48, kRfEdges = 64, kRfSlots = kRfEdges + kRfPos, kSlotRow = kWave + 1;
+// Genomes the register-file adjoint (backward_rf_kernel, below) takes: at most
+// kRfPos positions, kRfEdges in-edges and kRfSums rows of four sums, sum or
+// mean aggregation. Where N_max rows exceed the device's LDS and the LDS
+// adjoint cannot run, the limits are the documented ones (kRfPosAlone,
+// kRfEdgesAlone): a larger genome's gradients are NaN there.
+constexpr int kRfPos = 64, kRfEdges = 192, kRfSums = 64;
+constexpr int kRfPosAlone = 48, kRfEdgesAlone = 64;
+constexpr int kRfWaves = 4;  // wavefronts per genome, at most
 // Its register file starts at v64 (the compiler keeps v0..v63: sin's argument
-// reduction needs the room): tile 0 at v64..v159, tile 1 at v160..v255, each
-// 96 rows, values at rows 0..47 and upstream gradients at rows 48..95.
+// reduction needs the room): 192 rows, shared by one, two or four tiles.
 #define TN_BW_RF_BASE 64
 
-__device__ __forceinline__ bool rf_bwd_eligible(int st, int n, int n_edges, const int32_t* fnp) {
-  if (st || n > kRfPos || n_edges > kRfEdges) return false;
-  for (int p = 0; p < n; ++p) {
-    const int f = fnp[p];
-    const int agg = (f >> 8) & 0xff;
-    if (f >= 0 && agg != TN_AGG_SUM && agg != TN_AGG_MEAN) return false;
-  }
-  return true;
+// Rows of four sums that a computed node with ne in-edges takes (its bias and
+// its in-edges).
+__device__ __forceinline__ int sum_rows(int ne) { return (ne + 4) / 4; }
+
+// Whether genome g is backward_rf_kernel's; by one wavefront, lane = position.
+__device__ __forceinline__ bool rf_bwd_eligible(int st, int n, const int32_t* rp,
+                                                const int32_t* fnp, const BwdArgs& a) {
+  if (st || n > a.rf_pos || rp[n] > a.rf_edges) return false;
+  const int lane = lane_id();
+  const int f = lane < n ? fnp[lane] : -1;
+  const int ne = lane < n ? rp[lane + 1] - rp[lane] : 0;
+  const int agg = (f >> 8) & 0xff;
+  if (__ballot(ne > kWave || (f >= 0 && agg != TN_AGG_SUM && agg != TN_AGG_MEAN))) return false;
+  return wave_sum_int(f >= 0 ? sum_rows(ne) : 0) <= kRfSums;
 }
 
 __global__ __launch_bounds__(kWave) void backward_kernel(
@@ -168,10 +214,7 @@ __global__ __launch_bounds__(kWave) void backward_kernel(
   float* v = reinterpret_cast<float*>(lds + L.v_off);
   float* gr = reinterpret_cast<float*>(lds + L.g_off);
 
-  {
-    const int n0 = n_valid[g];
-    if (rf_bwd_eligible(st, n0, st ? 0 : row_ptr[rb + n0], fn + nb)) return;  // backward_rf_kernel's
-  }
+  if (rf_bwd_eligible(st, n_valid[g], row_ptr + rb, fn + nb, a)) return;  // backward_rf_kernel's
   // flagged genomes, and (when N_max rows of values and gradients exceed the
   // device's LDS) every genome the register-file adjoint could not take
   if (st || !lds_ok) {
@@ -310,67 +353,551 @@ __global__ __launch_bounds__(kWave) void backward_kernel(
 // ------------------------------------------------ register-file adjoint
 //
 // The same derivative for the genomes that fit it (tn_backward runs both
-// kernels; each takes the genomes the other leaves): at most kRfPos positions
-// and kRfEdges in-edges, sum or mean aggregation only, not flagged. One
-// wavefront per genome, lane = observation, two tiles of 64 observations per
-// step. Values and upstream gradients live in registers indexed by position
-// (two files of 96 rows, values at rows 0..47 and gradients at rows 48..95);
-// the genome's program is held across the lanes (read with v_readlane). Per
-// step:
-//   forward: v_p = act(bias + resp * agg(w_e v_src)) at every non-input
-//     position (gradient row cleared in the same window);
+// kernels; each takes the genomes the other leaves). One to four wavefronts per
+// genome share its steps of K tiles of 64 observations (lane = observation):
+// K = 4, 2 or 1, by the rows a genome needs. Values and upstream gradients live
+// in registers: rows 2 i and 2 i + 1 of a tile are the value and the gradient
+// of computed node i, then come the inputs' values (they need no gradient). The
+// program sits in LDS and comes across the lanes (a node's words in lane i for
+// computed node i, its in-edges one LDS read ahead). Per step:
+//   forward: v_i = act(bias + resp * agg(w_e v_src)) at every computed
+//     node (gradient row cleared in the same window);
 //   outputs: gbar_out += dL/dy;
-//   reverse: delta_p = gbar_p act'(z_p) (z re-evaluated for sin, gaussian,
-//     abs); db_p += delta_p; dt = delta_p resp (/ n for mean); per in-edge
-//     dW_e += dt v_src and gbar_src += dt w_e (one indexed read-modify-write).
-// The per-observation terms (both tiles added first) accumulate per lane in
-// LDS slots (row stride 65: conflict free), each in program order; at the end
-// lane s sums slot s over the 64 lanes in lane order. Deterministic.
-// V[p] := v{0,1}, G[p] := 0
-__device__ __forceinline__ void bw_set_v(int p, float v0, float v1) {
-  asm volatile(
-      "s_set_gpr_idx_on %2, gpr_idx(DST)\n\ts_nop 1\n\tv_mov_b32 v64, %0\n\t"
-      "v_mov_b32 v160, %1\n\tv_mov_b32 v112, 0\n\tv_mov_b32 v208, 0\n\ts_set_gpr_idx_off" ::"v"(v0),
-      "v"(v1), "s"(p)
-      : "m0");
+//   reverse: delta_i = gbar_i act'(z_i) (z re-evaluated for sin, gaussian,
+//     abs); db_i += delta_i; dt = delta_i resp (/ n for mean); per in-edge
+//     dW_e += dt v_src and, unless the source is an input, gbar_src += dt w_e
+//     (one indexed read-modify-write).
+// The sums of a node (its bias, then its in-edges) are taken four at a time:
+// each is one value per lane (the step's tiles added first); swapping halves
+// and quarters of the wavefront between registers adds lane l to lanes l + 32
+// and l + 16, so that four sums of 64 lanes become one register of four times
+// 16 lanes, added to one LDS row. That is a quarter of the LDS traffic and of
+// the LDS itself of one slot per sum and lane, so the registers (two wavefronts
+// per SIMD) and not the LDS limit occupancy, and genomes of up to 192 in-edges
+// fit. At the end each sum's 16 lanes are added over the wavefronts in a fixed
+// order. Bound by instruction issue. 4096 genomes (4 -> 2, 22 positions, 45
+// in-edges), 1024 samples: 264 us; 569 us with a slot per sum and lane, two
+// tiles a step. 1000 genomes (17 -> 6, 39 positions, 126 in-edges), 256
+// observations: 47 us; 148 us in backward_kernel.
+
+// Files of K tiles, 192 / K rows each; V[r] of tile k is register
+// v(64 + 192 / K * k + r), G[r] the one after it. One index window each.
+template <int K>
+struct Files;
+template <>
+struct Files<1> {
+  // V[r] := v
+  static __device__ __forceinline__ void set_v(int r, const float (&v)[1]) {
+    asm volatile(
+        "s_set_gpr_idx_on %1, gpr_idx(DST)\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32 v64, %0\n\t"
+        "s_set_gpr_idx_off"
+        : 
+        : "v"(v[0]), "s"(r)
+        : "m0");
+  }
+  // V[r] := v, G[r] := 0
+  static __device__ __forceinline__ void set_vg(int r, const float (&v)[1]) {
+    asm volatile(
+        "s_set_gpr_idx_on %1, gpr_idx(DST)\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32 v64, %0\n\t"
+        "v_mov_b32 v65, 0\n\t"
+        "s_set_gpr_idx_off"
+        : 
+        : "v"(v[0]), "s"(r)
+        : "m0");
+  }
+  // t := V[r]
+  static __device__ __forceinline__ void get_v(int r, float (&t)[1]) {
+    asm volatile(
+        "s_set_gpr_idx_on %1, gpr_idx(SRC0)\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32 %0, v64\n\t"
+        "s_set_gpr_idx_off"
+        : "=v"(t[0])
+        : "s"(r)
+        : "m0");
+  }
+  // s += w * V[r]
+  static __device__ __forceinline__ void fma_v(float (&s)[1], float w, int r) {
+    asm volatile(
+        "s_set_gpr_idx_on %2, gpr_idx(SRC1)\n\t"
+        "s_nop 1\n\t"
+        "v_fmac_f32 %0, %1, v64\n\t"
+        "s_set_gpr_idx_off"
+        : "+v"(s[0])
+        : "s"(w), "s"(r)
+        : "m0");
+  }
+  // g := G[r], v := V[r]
+  static __device__ __forceinline__ void get_gv(int r, float (&g)[1], float (&v)[1]) {
+    asm volatile(
+        "s_set_gpr_idx_on %2, gpr_idx(SRC0)\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32 %0, v65\n\t"
+        "v_mov_b32 %1, v64\n\t"
+        "s_set_gpr_idx_off"
+        : "=v"(g[0]), "=v"(v[0])
+        : "s"(r)
+        : "m0");
+  }
+  // G[r] += a * w (one indexed read-modify-write per tile)
+  static __device__ __forceinline__ void fma_g(int r, const float (&a)[1], float w) {
+    asm volatile(
+        "s_set_gpr_idx_on %2, gpr_idx(SRC2,DST)\n\t"
+        "s_nop 1\n\t"
+        "v_fma_f32 v65, %0, %1, v65\n\t"
+        "s_set_gpr_idx_off"
+        : 
+        : "v"(a[0]), "s"(w), "s"(r)
+        : "m0");
+  }
+  // sum of a * V[r] over the tiles
+  static __device__ __forceinline__ float dot_v(int r, const float (&a)[1]) {
+    float t;
+    asm volatile(
+        "s_set_gpr_idx_on %2, gpr_idx(SRC0)\n\t"
+        "s_nop 1\n\t"
+        "v_mul_f32 %0, v64, %1\n\t"
+        "s_set_gpr_idx_off"
+        : "=&v"(t)
+        : "v"(a[0]), "s"(r)
+        : "m0");
+    return t;
+  }
+  // the same, and G[r] += a * w (one indexed read-modify-write per tile)
+  static __device__ __forceinline__ float dot_v_fma_g(int r, const float (&a)[1], float w) {
+    float t;
+    asm volatile(
+        "s_set_gpr_idx_on %3, gpr_idx(SRC0)\n\t"
+        "s_nop 1\n\t"
+        "v_mul_f32 %0, v64, %1\n\t"
+        "s_set_gpr_idx_off\n\t"
+        "s_set_gpr_idx_on %3, gpr_idx(SRC2,DST)\n\t"
+        "s_nop 1\n\t"
+        "v_fma_f32 v65, %1, %2, v65\n\t"
+        "s_set_gpr_idx_off"
+        : "=&v"(t)
+        : "v"(a[0]), "s"(w), "s"(r)
+        : "m0");
+    return t;
+  }
+};
+template <>
+struct Files<2> {
+  static __device__ __forceinline__ void set_v(int r, const float (&v)[2]) {
+    asm volatile(
+        "s_set_gpr_idx_on %2, gpr_idx(DST)\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32 v64, %0\n\t"
+        "v_mov_b32 v160, %1\n\t"
+        "s_set_gpr_idx_off"
+        : 
+        : "v"(v[0]), "v"(v[1]), "s"(r)
+        : "m0");
+  }
+  static __device__ __forceinline__ void set_vg(int r, const float (&v)[2]) {
+    asm volatile(
+        "s_set_gpr_idx_on %2, gpr_idx(DST)\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32 v64, %0\n\t"
+        "v_mov_b32 v160, %1\n\t"
+        "v_mov_b32 v65, 0\n\t"
+        "v_mov_b32 v161, 0\n\t"
+        "s_set_gpr_idx_off"
+        : 
+        : "v"(v[0]), "v"(v[1]), "s"(r)
+        : "m0");
+  }
+  static __device__ __forceinline__ void get_v(int r, float (&t)[2]) {
+    asm volatile(
+        "s_set_gpr_idx_on %2, gpr_idx(SRC0)\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32 %0, v64\n\t"
+        "v_mov_b32 %1, v160\n\t"
+        "s_set_gpr_idx_off"
+        : "=v"(t[0]), "=v"(t[1])
+        : "s"(r)
+        : "m0");
+  }
+  static __device__ __forceinline__ void fma_v(float (&s)[2], float w, int r) {
+    asm volatile(
+        "s_set_gpr_idx_on %3, gpr_idx(SRC1)\n\t"
+        "s_nop 1\n\t"
+        "v_fmac_f32 %0, %2, v64\n\t"
+        "v_fmac_f32 %1, %2, v160\n\t"
+        "s_set_gpr_idx_off"
+        : "+v"(s[0]), "+v"(s[1])
+        : "s"(w), "s"(r)
+        : "m0");
+  }
+  static __device__ __forceinline__ void get_gv(int r, float (&g)[2], float (&v)[2]) {
+    asm volatile(
+        "s_set_gpr_idx_on %4, gpr_idx(SRC0)\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32 %0, v65\n\t"
+        "v_mov_b32 %1, v161\n\t"
+        "v_mov_b32 %2, v64\n\t"
+        "v_mov_b32 %3, v160\n\t"
+        "s_set_gpr_idx_off"
+        : "=v"(g[0]), "=v"(g[1]), "=v"(v[0]), "=v"(v[1])
+        : "s"(r)
+        : "m0");
+  }
+  static __device__ __forceinline__ void fma_g(int r, const float (&a)[2], float w) {
+    asm volatile(
+        "s_set_gpr_idx_on %3, gpr_idx(SRC2,DST)\n\t"
+        "s_nop 1\n\t"
+        "v_fma_f32 v65, %0, %2, v65\n\t"
+        "v_fma_f32 v161, %1, %2, v161\n\t"
+        "s_set_gpr_idx_off"
+        : 
+        : "v"(a[0]), "v"(a[1]), "s"(w), "s"(r)
+        : "m0");
+  }
+  static __device__ __forceinline__ float dot_v(int r, const float (&a)[2]) {
+    float t;
+    asm volatile(
+        "s_set_gpr_idx_on %3, gpr_idx(SRC0)\n\t"
+        "s_nop 1\n\t"
+        "v_mul_f32 %0, v64, %1\n\t"
+        "v_fmac_f32 %0, v160, %2\n\t"
+        "s_set_gpr_idx_off"
+        : "=&v"(t)
+        : "v"(a[0]), "v"(a[1]), "s"(r)
+        : "m0");
+    return t;
+  }
+  static __device__ __forceinline__ float dot_v_fma_g(int r, const float (&a)[2], float w) {
+    float t;
+    asm volatile(
+        "s_set_gpr_idx_on %4, gpr_idx(SRC0)\n\t"
+        "s_nop 1\n\t"
+        "v_mul_f32 %0, v64, %1\n\t"
+        "v_fmac_f32 %0, v160, %2\n\t"
+        "s_set_gpr_idx_off\n\t"
+        "s_set_gpr_idx_on %4, gpr_idx(SRC2,DST)\n\t"
+        "s_nop 1\n\t"
+        "v_fma_f32 v65, %1, %3, v65\n\t"
+        "v_fma_f32 v161, %2, %3, v161\n\t"
+        "s_set_gpr_idx_off"
+        : "=&v"(t)
+        : "v"(a[0]), "v"(a[1]), "s"(w), "s"(r)
+        : "m0");
+    return t;
+  }
+};
+template <>
+struct Files<4> {
+  static __device__ __forceinline__ void set_v(int r, const float (&v)[4]) {
+    asm volatile(
+        "s_set_gpr_idx_on %4, gpr_idx(DST)\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32 v64, %0\n\t"
+        "v_mov_b32 v112, %1\n\t"
+        "v_mov_b32 v160, %2\n\t"
+        "v_mov_b32 v208, %3\n\t"
+        "s_set_gpr_idx_off"
+        : 
+        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "s"(r)
+        : "m0");
+  }
+  static __device__ __forceinline__ void set_vg(int r, const float (&v)[4]) {
+    asm volatile(
+        "s_set_gpr_idx_on %4, gpr_idx(DST)\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32 v64, %0\n\t"
+        "v_mov_b32 v112, %1\n\t"
+        "v_mov_b32 v160, %2\n\t"
+        "v_mov_b32 v208, %3\n\t"
+        "v_mov_b32 v65, 0\n\t"
+        "v_mov_b32 v113, 0\n\t"
+        "v_mov_b32 v161, 0\n\t"
+        "v_mov_b32 v209, 0\n\t"
+        "s_set_gpr_idx_off"
+        : 
+        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "s"(r)
+        : "m0");
+  }
+  static __device__ __forceinline__ void get_v(int r, float (&t)[4]) {
+    asm volatile(
+        "s_set_gpr_idx_on %4, gpr_idx(SRC0)\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32 %0, v64\n\t"
+        "v_mov_b32 %1, v112\n\t"
+        "v_mov_b32 %2, v160\n\t"
+        "v_mov_b32 %3, v208\n\t"
+        "s_set_gpr_idx_off"
+        : "=v"(t[0]), "=v"(t[1]), "=v"(t[2]), "=v"(t[3])
+        : "s"(r)
+        : "m0");
+  }
+  static __device__ __forceinline__ void fma_v(float (&s)[4], float w, int r) {
+    asm volatile(
+        "s_set_gpr_idx_on %5, gpr_idx(SRC1)\n\t"
+        "s_nop 1\n\t"
+        "v_fmac_f32 %0, %4, v64\n\t"
+        "v_fmac_f32 %1, %4, v112\n\t"
+        "v_fmac_f32 %2, %4, v160\n\t"
+        "v_fmac_f32 %3, %4, v208\n\t"
+        "s_set_gpr_idx_off"
+        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3])
+        : "s"(w), "s"(r)
+        : "m0");
+  }
+  static __device__ __forceinline__ void get_gv(int r, float (&g)[4], float (&v)[4]) {
+    asm volatile(
+        "s_set_gpr_idx_on %8, gpr_idx(SRC0)\n\t"
+        "s_nop 1\n\t"
+        "v_mov_b32 %0, v65\n\t"
+        "v_mov_b32 %1, v113\n\t"
+        "v_mov_b32 %2, v161\n\t"
+        "v_mov_b32 %3, v209\n\t"
+        "v_mov_b32 %4, v64\n\t"
+        "v_mov_b32 %5, v112\n\t"
+        "v_mov_b32 %6, v160\n\t"
+        "v_mov_b32 %7, v208\n\t"
+        "s_set_gpr_idx_off"
+        : "=v"(g[0]), "=v"(g[1]), "=v"(g[2]), "=v"(g[3]), "=v"(v[0]), "=v"(v[1]), "=v"(v[2]), "=v"(v[3])
+        : "s"(r)
+        : "m0");
+  }
+  static __device__ __forceinline__ void fma_g(int r, const float (&a)[4], float w) {
+    asm volatile(
+        "s_set_gpr_idx_on %5, gpr_idx(SRC2,DST)\n\t"
+        "s_nop 1\n\t"
+        "v_fma_f32 v65, %0, %4, v65\n\t"
+        "v_fma_f32 v113, %1, %4, v113\n\t"
+        "v_fma_f32 v161, %2, %4, v161\n\t"
+        "v_fma_f32 v209, %3, %4, v209\n\t"
+        "s_set_gpr_idx_off"
+        : 
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "s"(w), "s"(r)
+        : "m0");
+  }
+  static __device__ __forceinline__ float dot_v(int r, const float (&a)[4]) {
+    float t;
+    asm volatile(
+        "s_set_gpr_idx_on %5, gpr_idx(SRC0)\n\t"
+        "s_nop 1\n\t"
+        "v_mul_f32 %0, v64, %1\n\t"
+        "v_fmac_f32 %0, v112, %2\n\t"
+        "v_fmac_f32 %0, v160, %3\n\t"
+        "v_fmac_f32 %0, v208, %4\n\t"
+        "s_set_gpr_idx_off"
+        : "=&v"(t)
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "s"(r)
+        : "m0");
+    return t;
+  }
+  static __device__ __forceinline__ float dot_v_fma_g(int r, const float (&a)[4], float w) {
+    float t;
+    asm volatile(
+        "s_set_gpr_idx_on %6, gpr_idx(SRC0)\n\t"
+        "s_nop 1\n\t"
+        "v_mul_f32 %0, v64, %1\n\t"
+        "v_fmac_f32 %0, v112, %2\n\t"
+        "v_fmac_f32 %0, v160, %3\n\t"
+        "v_fmac_f32 %0, v208, %4\n\t"
+        "s_set_gpr_idx_off\n\t"
+        "s_set_gpr_idx_on %6, gpr_idx(SRC2,DST)\n\t"
+        "s_nop 1\n\t"
+        "v_fma_f32 v65, %1, %5, v65\n\t"
+        "v_fma_f32 v113, %2, %5, v113\n\t"
+        "v_fma_f32 v161, %3, %5, v161\n\t"
+        "v_fma_f32 v209, %4, %5, v209\n\t"
+        "s_set_gpr_idx_off"
+        : "=&v"(t)
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "s"(w), "s"(r)
+        : "m0");
+    return t;
+  }
+};
+
+// a + b folded across the wavefront's halves: lanes 0..31 hold a's sums of
+// lanes l and l + 32, lanes 32..63 b's.
+__device__ __forceinline__ float fold32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-// t{0,1} := V[j]
-__device__ __forceinline__ void bw_get_v(int j, float& t0, float& t1) {
-  asm volatile(
-      "s_set_gpr_idx_on %2, gpr_idx(SRC0)\n\ts_nop 1\n\tv_mov_b32 %0, v64\n\t"
-      "v_mov_b32 %1, v160\n\ts_set_gpr_idx_off"
-      : "=v"(t0), "=v"(t1)
-      : "s"(j)
-      : "m0");
+// Likewise across 16 lanes: rows 0 and 2 of 16 lanes hold a's sums of rows
+// (0, 1) and (2, 3), rows 1 and 3 b's.
+__device__ __forceinline__ float fold16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-// s{0,1} += w * V[j]
-__device__ __forceinline__ void bw_fma_v(float& s0, float& s1, float w, int j) {
-  asm volatile(
-      "s_set_gpr_idx_on %3, gpr_idx(SRC1)\n\ts_nop 1\n\tv_fmac_f32 %0, %2, v64\n\t"
-      "v_fmac_f32 %1, %2, v160\n\ts_set_gpr_idx_off"
-      : "+v"(s0), "+v"(s1)
-      : "s"(w), "s"(j)
-      : "m0");
+// Four sums as quarters of 16 lanes: quarter q holds sum kQuarter[q].
+__device__ __forceinline__ float fold4(float t0, float t1, float t2, float t3) {
+  return fold16(fold32(t0, t1), fold32(t2, t3));
 }
-// G[p], V[p] of both files
-__device__ __forceinline__ void bw_get_gv(int p, float& g0, float& g1, float& v0, float& v1) {
-  asm volatile(
-      "s_set_gpr_idx_on %4, gpr_idx(SRC0)\n\ts_nop 1\n\tv_mov_b32 %0, v112\n\t"
-      "v_mov_b32 %1, v208\n\tv_mov_b32 %2, v64\n\tv_mov_b32 %3, v160\n\ts_set_gpr_idx_off"
-      : "=v"(g0), "=v"(g1), "=v"(v0), "=v"(v1)
-      : "s"(p)
-      : "m0");
-}
-// G[j] += a{0,1} * w (one indexed read-modify-write per file)
-__device__ __forceinline__ void bw_fma_g(int j, float a0, float a1, float w) {
-  asm volatile(
-      "s_set_gpr_idx_on %3, gpr_idx(SRC2,DST)\n\ts_nop 1\n\tv_fma_f32 v112, %0, %2, v112\n\t"
-      "v_fma_f32 v208, %1, %2, v208\n\ts_set_gpr_idx_off" ::"v"(a0),
-      "v"(a1), "v"(w), "s"(j)
-      : "m0");
+__device__ __forceinline__ int sum_of_quarter(int q) { return (q >> 1) | ((q & 1) << 1); }
+
+// What a step reads of its genome, and this lane's share of it (computed node
+// i in lane i).
+struct RfGenome {
+  const int2* edge;  // LDS: the source's row, weight
+  int nc;            // computed nodes
+  int l_fn, l_bias, l_resp;
+  int l_edge;        // byte offset of the first in-edge | in-edges << 16
+  int l_sum;         // first row of sums
+  int l_in, l_out;   // row of input / output `lane`
+  int I, O;
+};
+
+// One step: K tiles of observations from b0 on; sums are added to acc, the
+// wavefront's rows in LDS. Returns its part of the squared error.
+template <int K>
+__device__ __forceinline__ float rf_step(const RfGenome& q, int b0, const float* xg,
+                                         const float* ug, const BwdArgs& a, float* acc) {
+  using F = Files<K>;
+  const int lane = lane_id();
+  // 32-bit lane offsets from the step's own base: a register per address
+  const float* xs = xg + (int64_t)b0 * q.I;
+  const int left = a.B - b0;
+  bool live[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) live[k] = k * kWave + lane < left;
+  for (int c0 = 0; c0 < q.I; c0 += 2) {  // two inputs' loads in flight
+    const int c1 = min(c0 + 1, q.I - 1);
+    float x[2][K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t o = live[k] ? (uint32_t)((k * kWave + lane) * q.I) : 0u;
+      x[0][k] = xs[o + (uint32_t)c0];
+      x[1][k] = xs[o + (uint32_t)c1];
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) x[c][k] = live[k] ? x[c][k] : 0.0f;
+      F::set_v(__builtin_amdgcn_readlane(q.l_in, c ? c1 : c0), x[c]);
+    }
+  }
+  auto edges_of = [&](int i) {
+    const int at = __builtin_amdgcn_readlane(q.l_edge, i) & 0xffff;
+    return *reinterpret_cast<const int2*>(reinterpret_cast<const char*>(q.edge + lane) + at);
+  };
+  int2 ed = edges_of(0);
+  auto row_of = [&](int e) { return __builtin_amdgcn_readlane(ed.x, e); };
+  auto weight = [&](int e) { return __int_as_float(__builtin_amdgcn_readlane(ed.y, e)); };
+  // pre-activations of computed node i
+  auto pre = [&](int i, int f, int ne, float (&z)[K]) {
+    float s[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) s[k] = 0.0f;
+    if (ne > 0) {
+      F::fma_v(s, weight(0), row_of(0));
+      if (ne > 1) {
+        F::fma_v(s, weight(1), row_of(1));
+        for (int e = 2; e < ne; ++e) F::fma_v(s, weight(e), row_of(e));
+      }
+      if (((f >> 8) & 0xff) == TN_AGG_MEAN)
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          s[k] = s[k] / (float)ne;
+          asm volatile("" : "+v"(s[k]));
+        }
+    }
+    const float rho = __int_as_float(__builtin_amdgcn_readlane(q.l_resp, i));
+    const float bias = __int_as_float(__builtin_amdgcn_readlane(q.l_bias, i));
+#pragma unroll
+    for (int k = 0; k < K; ++k) z[k] = fmaf(rho, s[k], bias);
+  };
+  // forward
+  for (int i = 0; i < q.nc; ++i) {
+    const int2 en = edges_of(min(i + 1, q.nc - 1));
+    const int f = __builtin_amdgcn_readlane(q.l_fn, i);
+    float z[K], v[K];
+    pre(i, f, __builtin_amdgcn_readlane(q.l_edge, i) >> 16, z);
+    activate_all<K>(f & 7, z, v);  // codes below 7: transformed genomes
+    F::set_vg(2 * i, v);
+    ed = en;
+  }
+  // upstream gradient at the outputs
+  const float* us = ug + (int64_t)b0 * q.O;
+  float sse = 0.0f;
+  for (int jo = 0; jo < q.O; ++jo) {
+    const int pj = __builtin_amdgcn_readlane(q.l_out, jo);  // outputs are computed nodes
+    float y[K], gy[K];
+    F::get_v(pj, y);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const uint32_t o = (uint32_t)((live[k] ? (k * kWave + lane) * q.O : 0) + jo);
+      const float up = us[o];
+      if (a.dY) {
+        gy[k] = live[k] ? up : 0.0f;
+      } else {
+        const float d = live[k] ? y[k] - up : 0.0f;
+        sse = fmaf(d, d, sse);
+        gy[k] = 2.0f * a.scale * d;
+      }
+    }
+    F::fma_g(pj, gy, 1.0f);
+  }
+  // reverse sweep
+  ed = edges_of(q.nc - 1);
+  for (int i = q.nc - 1; i >= 0; --i) {
+    const int2 en = edges_of(max(i - 1, 0));
+    const int f = __builtin_amdgcn_readlane(q.l_fn, i);
+    const int ne = __builtin_amdgcn_readlane(q.l_edge, i) >> 16;
+    const int act = f & 7;
+    float* sum = acc + __builtin_amdgcn_readlane(q.l_sum, i) * kWave + lane;
+    float old = *sum;
+    float g[K], v[K], z[K], dt[K], db = 0.0f;
+    F::get_gv(2 * i, g, v);
+#pragma unroll
+    for (int k = 0; k < K; ++k) z[k] = 0.0f;
+    if (slope_needs_z(act)) pre(i, f, ne, z);
+    float slope[K];
+    act_slopes<K>(act, v, z, slope);
+    const float rho = __int_as_float(__builtin_amdgcn_readlane(q.l_resp, i));
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const float d = live[k] ? g[k] * slope[k] : 0.0f;
+      db += d;
+      dt[k] = d * rho;
+    }
+    if (((f >> 8) & 0xff) == TN_AGG_MEAN && ne > 0)
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        dt[k] = dt[k] / (float)ne;
+        asm volatile("" : "+v"(dt[k]));
+      }
+    auto term = [&](int e) {
+      const int j = row_of(e);
+      return j < 2 * q.nc ? F::dot_v_fma_g(j, dt, weight(e)) : F::dot_v(j, dt);  // else an input
+    };
+    float t1 = 0.0f, t2 = 0.0f, t3 = 0.0f;
+    if (ne > 0) {
+      t1 = term(0);
+      if (ne > 1) {
+        t2 = term(1);
+        if (ne > 2) t3 = term(2);
+      }
+    }
+    *sum = old + fold4(db, t1, t2, t3);
+    for (int e = 3; e < ne; e += 4) {
+      sum += kWave;
+      old = *sum;
+      float t0 = term(e);
+      t1 = t2 = t3 = 0.0f;
+      if (e + 1 < ne) {
+        t1 = term(e + 1);
+        if (e + 2 < ne) {
+          t2 = term(e + 2);
+          if (e + 3 < ne) t3 = term(e + 3);
+        }
+      }
+      *sum = old + fold4(t0, t1, t2, t3);
+    }
+    ed = en;
+  }
+  return sse;
 }
 
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_num_vgpr(TN_BW_RF_BASE))) void
+__global__ __launch_bounds__(kWave * kRfWaves) __attribute__((amdgpu_num_vgpr(TN_BW_RF_BASE / 2))) void
 backward_rf_kernel(PopView pop, const int32_t* __restrict__ status,
                    const int32_t* __restrict__ n_valid, const int32_t* __restrict__ order,
                    const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ src,
@@ -379,187 +906,118 @@ backward_rf_kernel(PopView pop, const int32_t* __restrict__ status,
                    const int32_t* __restrict__ resp_bits, const int32_t* __restrict__ io_pos,
                    const float* __restrict__ obs, BwdArgs a) {
   asm volatile("" ::: "v255");  // the register file counts in the allocation
-  __shared__ float slots[kRfSlots * kSlotRow];
-  __shared__ int32_t maps[2 * kWave];
-  const int g = blockIdx.x;
-  const int lane = lane_id();
-  const int I = pop.n_in, O = pop.n_out, nio = I + O;
+  extern __shared__ __align__(16) float acc_all[];  // [waves][kRfSums][64]
+  __shared__ int2 edge[kRfEdges + kWave];
+  __shared__ int32_t sums_of[kRfSums];  // a row of sums' computed node | its row of the node << 8
+  __shared__ int2 node[kRfPos];            // its position, l_edge
+  __shared__ uint32_t held[TN_MAX_CONNS / 32 + TN_MAX_NODES / 32];  // rows with a sum
+  __shared__ float part[kRfWaves];
+  const int g = blockIdx.x, tid = threadIdx.x, T = blockDim.x;
+  const int lane = lane_id(), wave = wave_id(), W = T / kWave;
   const int64_t nb = uniform64(pop.node_base(g)), cb = uniform64(pop.conn_base(g)),
                 rb = uniform64(pop.rowptr_base(g));
-  const int64_t nrows = pop.node_rows(g), crows = pop.conn_rows(g);
+  const int nrows = (int)pop.node_rows(g), crows = (int)pop.conn_rows(g);
   const int n = n_valid[g];
-  const int n_edges = status[g] ? 0 : row_ptr[rb + n];
-  if (!rf_bwd_eligible(status[g], n, n_edges, fn + nb)) return;  // the LDS kernel's genome
-  // the program across the lanes
-  const int l_fn = lane < n ? fn[nb + lane] : 0;
-  const int l_bias = lane < n ? bias_bits[nb + lane] : 0;
-  const int l_resp = lane < n ? resp_bits[nb + lane] : 0;
-  const int l_rp = lane <= n ? row_ptr[rb + lane] : 0;
-  const int l_src = lane < n_edges ? src[cb + lane] : 0;
-  const int l_w = lane < n_edges ? w_bits[cb + lane] : 0;
-  const int l_io = lane < nio ? io_pos[(int64_t)g * nio + lane] : 0;
-  float* my = slots + lane;  // slot s of this lane at my[s * kSlotRow]
-#pragma unroll 1
-  for (int s = 0; s < kRfSlots; ++s) my[s * kSlotRow] = 0.0f;
+  if (!rf_bwd_eligible(status[g], n, row_ptr + rb, fn + nb, a)) return;  // the LDS kernel's genome
+  const int n_edges = row_ptr[rb + n];
+  const int nio = pop.n_in + pop.n_out;
+  float* acc = acc_all + wave * kRfSums * kWave;
+  RfGenome q;
+  q.edge = edge;
+  q.I = pop.n_in;
+  q.O = pop.n_out;
+  // position p in lane p, then computed node i in lane i
+  const int p_fn = lane < n ? fn[nb + lane] : -1;
+  const int p_start = lane < n ? row_ptr[rb + lane] : 0, p_end = lane < n ? row_ptr[rb + lane + 1] : 0;
+  const uint64_t nodes = __ballot(p_fn >= 0), inputs = __ballot(lane < n && p_fn < 0);
+  q.nc = __popcll(nodes);
+  auto row_at = [&](int p) {  // of position p
+    const uint64_t below = ((uint64_t)1 << p) - 1;
+    return (nodes >> p) & 1 ? 2 * __popcll(nodes & below)
+                            : 2 * q.nc + __popcll(inputs & below);
+  };
+  for (int e = tid; e < n_edges; e += T)
+    edge[e] = make_int2(row_at(src[cb + e]), w_bits[cb + e]);
+  for (int i = tid; i < TN_MAX_CONNS / 32 + TN_MAX_NODES / 32; i += T) held[i] = 0u;
+  const int mine = p_fn >= 0 ? mbcnt(nodes) : -1;
+  if (wave == 0 && mine >= 0)
+    node[mine] = make_int2(lane, (p_start * (int)sizeof(int2)) | ((p_end - p_start) << 16));
+  __syncthreads();
+  const int2 nd = lane < q.nc ? node[lane] : make_int2(0, 0);
+  const int rows = lane < q.nc ? sum_rows(nd.y >> 16) : 0;
+  const int row_end = wave_inclusive_scan(rows), row0 = row_end - rows;
+  const int n_sums = __builtin_amdgcn_readlane(row_end, kWave - 1);
+  q.l_fn = __shfl(p_fn, nd.x, kWave);
+  q.l_bias = lane < q.nc ? bias_bits[nb + nd.x] : 0;
+  q.l_resp = lane < q.nc ? resp_bits[nb + nd.x] : 0;
+  q.l_edge = nd.y;
+  q.l_sum = row0;
+  q.l_in = lane < q.I ? row_at(io_pos[(int64_t)g * nio + lane]) : 0;
+  q.l_out = lane < q.O ? row_at(io_pos[(int64_t)g * nio + q.I + lane]) : 0;
+  if (wave == 0)
+    for (int c = 0; c < rows; ++c) sums_of[row0 + c] = lane | (c << 8);
+  for (int r = 0; r < n_sums; ++r) acc[r * kWave + lane] = 0.0f;
   float sse = 0.0f;
-  const int n_steps = (a.B + 2 * kWave - 1) / (2 * kWave);
-  for (int t = 0; t < n_steps; ++t) {
-    int bk[2];
-    bool live[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      bk[k] = t * 2 * kWave + k * kWave + lane;
-      live[k] = bk[k] < a.B;
-    }
-    const float* xg = obs + (int64_t)g * a.obs_stride;
-    // inputs (gradient rows cleared with them)
-    for (int c = 0; c < I; ++c) {
-      const int p = __builtin_amdgcn_readlane(l_io, c);
-      const float x0 = live[0] ? xg[(int64_t)bk[0] * I + c] : 0.0f;
-      const float x1 = live[1] ? xg[(int64_t)bk[1] * I + c] : 0.0f;
-      bw_set_v(p, x0, x1);
-    }
-    // forward
-    for (int p = 0; p < n; ++p) {
-      const int f = __builtin_amdgcn_readlane(l_fn, p);
-      if (f < 0) continue;
-      const int e0 = __builtin_amdgcn_readlane(l_rp, p), e1 = __builtin_amdgcn_readlane(l_rp, p + 1);
-      float sum[2] = {0.0f, 0.0f};
-      for (int e = e0; e < e1; ++e) {
-        const int j = __builtin_amdgcn_readlane(l_src, e);
-        bw_fma_v(sum[0], sum[1], __int_as_float(__builtin_amdgcn_readlane(l_w, e)), j);
-      }
-      if (((f >> 8) & 0xff) == TN_AGG_MEAN && e1 > e0) {
-        sum[0] = sum[0] / (float)(e1 - e0);
-        sum[1] = sum[1] / (float)(e1 - e0);
-      }
-      const float rho = __int_as_float(__builtin_amdgcn_readlane(l_resp, p));
-      const float bias = __int_as_float(__builtin_amdgcn_readlane(l_bias, p));
-      // one tile at a time (the empty asm keeps the compiler from
-      // interleaving them: less register pressure in sin's reduction)
-      const float z0[1] = {fmaf(rho, sum[0], bias)}, z1[1] = {fmaf(rho, sum[1], bias)};
-      float v0[1], v1[1];
-      activate_all<1>(f & 7, z0, v0);  // codes below 7: transformed genomes
-      asm volatile("" : "+v"(v0[0]));
-      activate_all<1>(f & 7, z1, v1);
-      bw_set_v(p, v0[0], v1[0]);
-    }
-    // upstream gradient at the outputs
-    for (int jo = 0; jo < O; ++jo) {
-      const int pj = __builtin_amdgcn_readlane(l_io, I + jo);
-      float y[2];
-      bw_get_v(pj, y[0], y[1]);
-      float gy[2];
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        gy[k] = 0.0f;
-        if (live[k]) {
-          const int64_t o = (int64_t)bk[k] * O + jo;
-          if (a.dY) {
-            gy[k] = a.dY[(int64_t)g * a.dY_stride + o];
-          } else {
-            const float d = y[k] - a.target[(int64_t)g * a.target_stride + o];
-            sse = fmaf(d, d, sse);
-            gy[k] = 2.0f * a.scale * d;
-          }
-        }
-      }
-      bw_fma_g(pj, gy[0], gy[1], 1.0f);
-    }
-    // reverse sweep
-    for (int p = n - 1; p >= 0; --p) {
-      const int f = __builtin_amdgcn_readlane(l_fn, p);
-      if (f < 0) continue;
-      const int act = f & 7;
-      const int e0 = __builtin_amdgcn_readlane(l_rp, p), e1 = __builtin_amdgcn_readlane(l_rp, p + 1);
-      const bool mean = ((f >> 8) & 0xff) == TN_AGG_MEAN && e1 > e0;
-      const float rho = __int_as_float(__builtin_amdgcn_readlane(l_resp, p));
-      float g0, g1, v0, v1;
-      bw_get_gv(p, g0, g1, v0, v1);
-      float z[2] = {0.0f, 0.0f};
-      if (slope_needs_z(act)) {
-        float sum[2] = {0.0f, 0.0f};
-        for (int e = e0; e < e1; ++e) {
-          const int j = __builtin_amdgcn_readlane(l_src, e);
-          bw_fma_v(sum[0], sum[1], __int_as_float(__builtin_amdgcn_readlane(l_w, e)), j);
-        }
-        if (mean) {
-          sum[0] = sum[0] / (float)(e1 - e0);
-          sum[1] = sum[1] / (float)(e1 - e0);
-        }
-        const float bias = __int_as_float(__builtin_amdgcn_readlane(l_bias, p));
-        z[0] = fmaf(rho, sum[0], bias);
-        z[1] = fmaf(rho, sum[1], bias);
-      }
-      float d0 = live[0] ? g0 * act_slope(act, v0, z[0]) : 0.0f;
-      asm volatile("" : "+v"(d0));
-      const float d1 = live[1] ? g1 * act_slope(act, v1, z[1]) : 0.0f;
-      my[(kRfEdges + p) * kSlotRow] += d0 + d1;
-      float dt0 = d0 * rho, dt1 = d1 * rho;
-      if (mean) {
-        dt0 = dt0 / (float)(e1 - e0);
-        dt1 = dt1 / (float)(e1 - e0);
-      }
-      for (int e = e0; e < e1; ++e) {
-        const float old = my[e * kSlotRow];
-        const int j = __builtin_amdgcn_readlane(l_src, e);
-        float t[2];
-        bw_get_v(j, t[0], t[1]);
-        bw_fma_g(j, dt0, dt1, __int_as_float(__builtin_amdgcn_readlane(l_w, e)));
-        my[e * kSlotRow] = old + fmaf(dt1, t[1], dt0 * t[0]);
-      }
-    }
-  }
-  wave_sync();
-  // slot s (edge s, or position s - kRfEdges) summed by lane s in lane order
-  float sums[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int s = h * kWave + lane;
-    float acc = 0.0f;
-    if (s < kRfSlots)
-#pragma unroll 8
-      for (int b = 0; b < kWave; ++b) acc += slots[s * kSlotRow + b];
-    sums[h] = acc;
-  }
-  // write every row of the genome's blocks once: row -> edge / position maps
-  int32_t* row_edge = maps;
-  int32_t* row_pos = maps + kWave;
-  wave_sync();
-  for (int64_t r0 = 0; r0 < crows; r0 += kWave) {
-    row_edge[lane] = -1;
-    wave_sync();
-    if (lane < n_edges) {
-      const int64_t r = edge_row[cb + lane] - r0;
-      if (r >= 0 && r < kWave) row_edge[r] = lane;
-    }
-    wave_sync();
-    const int e = row_edge[lane];
-    const float dwv = __shfl(sums[0], e < 0 ? 0 : e, kWave);
-    if (r0 + lane < crows) a.dW[cb + r0 + lane] = e >= 0 ? dwv : 0.0f;
-    wave_sync();
-  }
-  for (int64_t r0 = 0; r0 < nrows; r0 += kWave) {
-    row_pos[lane] = -1;
-    wave_sync();
-    if (lane < n && l_fn >= 0) {
-      const int64_t r = order[nb + lane] - r0;
-      if (r >= 0 && r < kWave) row_pos[r] = lane;
-    }
-    wave_sync();
-    const int p = row_pos[lane];
-    // position p's sum is slot kRfEdges + p: lane p of sums[0] for p < 0,
-    // i.e. lane (kRfEdges + p) - 64 of sums[1]
-    const int sl = kRfEdges + (p < 0 ? 0 : p);
-    const float lo = __shfl(sums[0], sl & (kWave - 1), kWave);
-    const float hi = __shfl(sums[1], sl & (kWave - 1), kWave);
-    const float dbv = sl < kWave ? lo : hi;
-    if (r0 + lane < nrows) a.db[nb + r0 + lane] = p >= 0 ? dbv : 0.0f;
-    wave_sync();
-  }
+  const float* xg = obs + (int64_t)g * a.obs_stride;
+  const float* ug = a.dY ? a.dY + (int64_t)g * a.dY_stride
+                         : a.target + (int64_t)g * a.target_stride;
+  // As many tiles a step as the genome's rows leave room for, while every
+  // wavefront still has a step.
+  auto steps = [&](auto tiles) {
+    constexpr int K = decltype(tiles)::value;
+    for (int b0 = wave * K * kWave; b0 < a.B; b0 += W * K * kWave)
+      sse += rf_step<K>(q, b0, xg, ug, a, acc);
+  };
+  const int file = n + q.nc;
+  if (file <= 48 && a.B > W * 2 * kWave)
+    steps(std::integral_constant<int, 4>{});
+  else if (file <= 96 && a.B > W * kWave)
+    steps(std::integral_constant<int, 2>{});
+  else
+    steps(std::integral_constant<int, 1>{});
   if (a.loss) {
     const float total = wave_sum(sse);
-    if (lane == 0) a.loss[g] = a.scale * total;
+    if (lane == 0) part[wave] = total;
+  }
+  // rows of the genome's blocks that hold a sum; the others get 0
+  for (int e = tid; e < n_edges; e += T) {
+    const int r = edge_row[cb + e];
+    atomicOr(&held[r >> 5], 1u << (r & 31));
+  }
+  for (int i = tid; i < q.nc; i += T) {
+    const int r = order[nb + node[i].x];
+    atomicOr(&held[TN_MAX_CONNS / 32 + (r >> 5)], 1u << (r & 31));
+  }
+  __syncthreads();
+  // sum i / 4, quarter i % 4: its 16 lanes over the wavefronts, starting at a
+  // lane of its own so that neighbours read different banks
+  for (int i = tid; i < 4 * n_sums; i += T) {
+    const int r = i >> 2, quarter = i & 3;
+    float total = 0.0f;
+    for (int w = 0; w < W; ++w) {
+      const float* from = acc_all + (w * kRfSums + r) * kWave + quarter * 16;
+      float t = 0.0f;
+#pragma unroll 8
+      for (int b = 0; b < 16; ++b) t += from[(b + i) & 15];
+      total += t;
+    }
+    const int of = sums_of[r];
+    const int2 at = node[of & 0xff];
+    const int term = (of >> 8) * 4 + sum_of_quarter(quarter) - 1;  // -1: the bias
+    const int e0 = (at.y & 0xffff) / (int)sizeof(int2), ne = at.y >> 16;
+    if (term < 0)
+      a.db[nb + order[nb + at.x]] = total;
+    else if (term < ne)
+      a.dW[cb + edge_row[cb + e0 + term]] = total;
+  }
+  for (int r = tid; r < crows; r += T)
+    if (!((held[r >> 5] >> (r & 31)) & 1)) a.dW[cb + r] = 0.0f;
+  for (int r = tid; r < nrows; r += T)
+    if (!((held[TN_MAX_CONNS / 32 + (r >> 5)] >> (r & 31)) & 1)) a.db[nb + r] = 0.0f;
+  if (a.loss && tid == 0) {
+    float total = 0.0f;
+    for (int w = 0; w < W; ++w) total += part[w];
+    a.loss[g] = a.scale * total;
   }
 }
 
@@ -580,8 +1038,19 @@ int launch_backward(const tn_population& p, const tn_transformed& t, const float
     rc = TN_OK;
   }
   if (rc != TN_OK || p.P == 0) return rc;
-  BwdArgs a{obs_stride, B, dY, dY_stride, target, target_stride, scale, loss, dW, db};
-  hipLaunchKernelGGL(backward_rf_kernel, dim3(p.P), dim3(kWave), 0, stream, make_view(p),
+  BwdArgs a{obs_stride, B, dY, dY_stride, target, target_stride, scale, loss, dW, db,
+            lds_ok ? kRfPos : kRfPosAlone, lds_ok ? kRfEdges : kRfEdgesAlone};
+  // Wavefronts per genome: as many as have steps of two tiles, up to 8192 in
+  // all. The chip holds 2048 of them, and genomes differ in size: 4096 genomes
+  // of 1024 samples took 345 us in two rounds of one wavefront each, 298 us
+  // with two, 296 us with four.
+  const int64_t steps = ((int64_t)B + 2 * kWave - 1) / (2 * kWave);
+  const int waves = (int)std::max<int64_t>(
+      1, std::min<int64_t>({(int64_t)kRfWaves, steps, (8192 + p.P - 1) / p.P}));
+  const size_t rf_lds = sizeof(float) * (size_t)waves * kRfSums * kWave;
+  rc = allow_lds((const void*)backward_rf_kernel, rf_lds);
+  if (rc != TN_OK) return rc;
+  hipLaunchKernelGGL(backward_rf_kernel, dim3(p.P), dim3(kWave * waves), rf_lds, stream, make_view(p),
                      t.status, t.n_valid, t.order, t.row_ptr, t.edge_src,
                      reinterpret_cast<const int32_t*>(t.edge_w), t.edge_row, t.pos_fn,
                      reinterpret_cast<const int32_t*>(t.pos_bias),

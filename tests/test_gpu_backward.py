@@ -18,6 +18,7 @@ import torch
 import oracle
 import synth
 from gpu_util import host, tensor, to_device
+from helpers import population_from_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -97,6 +98,46 @@ def test_register_adjoint_limits_and_lds_fallback():
     loss, dW, db = gpu_mse(pop, X, T)
     ref_loss, ref_dW, ref_db = oracle_mse_grads(pop, X, T, range(pop.P))
     check_grads(pop, dW, db, ref_dW, ref_db, range(pop.P))
+
+
+def _sized_genome(rng, nc, degrees):
+    """4 inputs (keys 0..3), 2 outputs (4, 5) and nc - 2 hidden nodes; computed
+    node j has min(degrees[j], 4 + earlier nodes) in-edges."""
+    keys = list(range(6, 4 + nc)) + [4, 5]
+    acts = [1, 2, 4, 0, 5]
+    nodes = [[k, 0.0, 1.0, 0, 0] for k in range(4)]
+    nodes += [[k, float(rng.normal() * 0.3), float(rng.choice([1.0, 0.5])),
+               int(acts[rng.integers(0, 5)]), int(j % 5 == 0)] for j, k in enumerate(keys)]
+    nodes.sort()
+    conns = []
+    for j, k in enumerate(keys):
+        srcs = list(range(4)) + keys[:j] if k > 5 else list(range(4)) + keys[:-2]
+        for s in rng.permutation(srcs)[:degrees[j]]:
+            conns.append([int(s), k, float(rng.normal() * 0.3), 1])
+    if [0, 4] not in [c[:2] for c in conns]:
+        conns.append([0, 4, 0.5, 0])  # disabled: its gradient is 0
+    return nodes, conns
+
+
+@pytest.mark.parametrize("B", [1, 64, 65, 128, 129, 300, 530, 1025])
+def test_register_adjoint_file_sizes(B):
+    """Genomes on both sides of each limit of the register-file adjoint (files
+    of 48 and 96 rows, 64 positions, 192 in-edges, 64 rows of sums), at batches
+    that end in every part of a step and take one to four wavefronts."""
+    import paper_2504_08339_amd as tn
+    rng = np.random.default_rng(B)
+    sizes = [(nc, [3] * nc) for nc in (2, 22, 23, 46, 47, 60, 61)]
+    sizes += [(32, [4] * 32), (33, [4] * 33), (2, [0, 0]), (24, [8] * 24), (30, [0, 24] * 15)]
+    sizes += [(30, [3] * 3 + [7] * 26 + [1 + extra]) for extra in (0, 1)]  # 192, 193 in-edges
+    pop = population_from_rows([_sized_genome(rng, *s) for s in sizes], 4, 2)
+    X = rng.uniform(-1, 1, size=(pop.P, B, 4)).astype(np.float32)
+    dY = rng.uniform(0.5, 1.5, size=(pop.P, B, 2)).astype(np.float32)
+    dp = to_device(pop)
+    tr = tn.transform(dp)
+    assert not host(tr.status)[:pop.P].any()
+    dW, db = tn.backward(dp, tr, tensor(X), tensor(dY))
+    rW, rb = oracle.backward_population(pop, X, dY)
+    check_grads(pop, host(dW), host(db), rW, rb, list(range(pop.P)))
 
 
 def test_lds_adjoint_beyond_device_lds():
