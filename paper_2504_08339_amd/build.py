@@ -73,14 +73,16 @@ def _define(header: str, name: str) -> int:
 
 def _rf_base(kernel: str) -> int:
     """First VGPR of the register file of a register-file kernel."""
-    if "backward_rf_kernel" in kernel:
-        return _define("backward.hip", "TN_BW_RF_BASE")
+    if "cppn_map_kernel" in kernel:
+        return _define("rf_file.hpp", "TN_RF_SHORT")
+    if any(k in kernel for k in ("backward_rf_kernel", "cppn_backward_kernel")):
+        return _define("rf_file.hpp", "TN_RF_FILE")
     return _define("fwd_reg.hpp", "TN_RF_BASE")
 
 
 # kernels that keep an explicit register file (names as they appear mangled)
-RF_KERNELS = ("forward_rf", "cppn_query_kernel", "cppn_backward_kernel", "backward_rf_kernel",
-              "recurrent_rf_kernel")
+RF_KERNELS = ("forward_rf", "cppn_query_kernel", "cppn_map_kernel",
+              "cppn_backward_kernel", "backward_rf_kernel", "recurrent_rf_kernel")
 RF_SOURCES = ("forward_reg.hip", "hyperneat.hip", "backward.hip", "recurrent.hip")
 
 

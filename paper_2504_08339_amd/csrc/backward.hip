@@ -20,7 +20,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "fwd_core.hpp"
+#include "rf_file.hpp"
 
 namespace tn {
 
@@ -89,55 +89,6 @@ __device__ float node_z(const NodeRec& rec, int f, const EdgeRec* edges, const f
   return fmaf(rec.resp, s, rec.bias);
 }
 
-// d act / dz at this lane, from the stored value v (and z when needed).
-__device__ __forceinline__ float act_slope(int act, float v, float z) {
-  switch (act) {
-    case TN_ACT_IDENTITY: return 1.0f;
-    case TN_ACT_SIGMOID: return v * (1.0f - v);
-    case TN_ACT_TANH: return fmaf(-v, v, 1.0f);
-    case TN_ACT_RELU: return v > 0.0f ? 1.0f : 0.0f;
-    case TN_ACT_SIN: return cosf(z);
-    case TN_ACT_GAUSSIAN: return -2.0f * z * v;
-    default: return z > 0.0f ? 1.0f : (z < 0.0f ? -1.0f : 0.0f);  // abs
-  }
-}
-
-// act_slope of K values, one branch for all of them.
-template <int K>
-__device__ __forceinline__ void act_slopes(int act, const float (&v)[K], const float (&z)[K],
-                                           float (&d)[K]) {
-  if (act == TN_ACT_TANH) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) d[k] = act_slope(TN_ACT_TANH, v[k], z[k]);
-  } else if (act == TN_ACT_IDENTITY) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) d[k] = 1.0f;
-  } else if (act == TN_ACT_SIN) {
-    // one cosine at a time: the reduction of a large argument takes many
-    // registers
-    float zz[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) zz[k] = z[k];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      d[k] = act_slope(TN_ACT_SIN, v[k], zz[k]);
-      asm volatile("" : "+v"(d[k]), "+v"(zz[(k + 1) % K]));
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      float o = act == TN_ACT_SIGMOID ? act_slope(TN_ACT_SIGMOID, v[k], z[k])
-                                      : act_slope(TN_ACT_RELU, v[k], z[k]);
-      o = act == TN_ACT_GAUSSIAN ? act_slope(TN_ACT_GAUSSIAN, v[k], z[k]) : o;
-      d[k] = act == TN_ACT_ABS ? act_slope(TN_ACT_ABS, v[k], z[k]) : o;
-    }
-  }
-}
-
-__device__ __forceinline__ bool slope_needs_z(int act) {
-  return act == TN_ACT_SIN || act == TN_ACT_GAUSSIAN || act == TN_ACT_ABS;
-}
-
 // d agg / d t_e for in-edge e of a node with a non-sum aggregation, this lane.
 __device__ float agg_partial(int agg, int e, int e0, int e1, const EdgeRec* edges, const float* v,
                              int lane) {
@@ -170,13 +121,6 @@ __device__ float agg_partial(int agg, int e, int e0, int e1, const EdgeRec* edge
 constexpr int kRfPos = 64, kRfEdges = 192, kRfSums = 64;
 constexpr int kRfPosAlone = 48, kRfEdgesAlone = 64;
 constexpr int kRfWaves = 4;  // wavefronts per genome, at most
-// Its register file starts at v64 (the compiler keeps v0..v63: sin's argument
-// reduction needs the room): 192 rows, shared by one, two or four tiles.
-#define TN_BW_RF_BASE 64
-
-// Rows of four sums that a computed node with ne in-edges takes (its bias and
-// its in-edges).
-__device__ __forceinline__ int sum_rows(int ne) { return (ne + 4) / 4; }
 
 // Whether genome g is backward_rf_kernel's; by one wavefront, lane = position.
 __device__ __forceinline__ bool rf_bwd_eligible(int st, int n, const int32_t* rp,
@@ -380,360 +324,6 @@ __global__ __launch_bounds__(kWave) void backward_kernel(
 // tiles a step. 1000 genomes (17 -> 6, 39 positions, 126 in-edges), 256
 // observations: 47 us; 148 us in backward_kernel.
 
-// Files of K tiles, 192 / K rows each; V[r] of tile k is register
-// v(64 + 192 / K * k + r), G[r] the one after it. One index window each.
-template <int K>
-struct Files;
-template <>
-struct Files<1> {
-  // V[r] := v
-  static __device__ __forceinline__ void set_v(int r, const float (&v)[1]) {
-    asm volatile(
-        "s_set_gpr_idx_on %1, gpr_idx(DST)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 v64, %0\n\t"
-        "s_set_gpr_idx_off"
-        : 
-        : "v"(v[0]), "s"(r)
-        : "m0");
-  }
-  // V[r] := v, G[r] := 0
-  static __device__ __forceinline__ void set_vg(int r, const float (&v)[1]) {
-    asm volatile(
-        "s_set_gpr_idx_on %1, gpr_idx(DST)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 v64, %0\n\t"
-        "v_mov_b32 v65, 0\n\t"
-        "s_set_gpr_idx_off"
-        : 
-        : "v"(v[0]), "s"(r)
-        : "m0");
-  }
-  // t := V[r]
-  static __device__ __forceinline__ void get_v(int r, float (&t)[1]) {
-    asm volatile(
-        "s_set_gpr_idx_on %1, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 %0, v64\n\t"
-        "s_set_gpr_idx_off"
-        : "=v"(t[0])
-        : "s"(r)
-        : "m0");
-  }
-  // s += w * V[r]
-  static __device__ __forceinline__ void fma_v(float (&s)[1], float w, int r) {
-    asm volatile(
-        "s_set_gpr_idx_on %2, gpr_idx(SRC1)\n\t"
-        "s_nop 1\n\t"
-        "v_fmac_f32 %0, %1, v64\n\t"
-        "s_set_gpr_idx_off"
-        : "+v"(s[0])
-        : "s"(w), "s"(r)
-        : "m0");
-  }
-  // g := G[r], v := V[r]
-  static __device__ __forceinline__ void get_gv(int r, float (&g)[1], float (&v)[1]) {
-    asm volatile(
-        "s_set_gpr_idx_on %2, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 %0, v65\n\t"
-        "v_mov_b32 %1, v64\n\t"
-        "s_set_gpr_idx_off"
-        : "=v"(g[0]), "=v"(v[0])
-        : "s"(r)
-        : "m0");
-  }
-  // G[r] += a * w (one indexed read-modify-write per tile)
-  static __device__ __forceinline__ void fma_g(int r, const float (&a)[1], float w) {
-    asm volatile(
-        "s_set_gpr_idx_on %2, gpr_idx(SRC2,DST)\n\t"
-        "s_nop 1\n\t"
-        "v_fma_f32 v65, %0, %1, v65\n\t"
-        "s_set_gpr_idx_off"
-        : 
-        : "v"(a[0]), "s"(w), "s"(r)
-        : "m0");
-  }
-  // sum of a * V[r] over the tiles
-  static __device__ __forceinline__ float dot_v(int r, const float (&a)[1]) {
-    float t;
-    asm volatile(
-        "s_set_gpr_idx_on %2, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mul_f32 %0, v64, %1\n\t"
-        "s_set_gpr_idx_off"
-        : "=&v"(t)
-        : "v"(a[0]), "s"(r)
-        : "m0");
-    return t;
-  }
-  // the same, and G[r] += a * w (one indexed read-modify-write per tile)
-  static __device__ __forceinline__ float dot_v_fma_g(int r, const float (&a)[1], float w) {
-    float t;
-    asm volatile(
-        "s_set_gpr_idx_on %3, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mul_f32 %0, v64, %1\n\t"
-        "s_set_gpr_idx_off\n\t"
-        "s_set_gpr_idx_on %3, gpr_idx(SRC2,DST)\n\t"
-        "s_nop 1\n\t"
-        "v_fma_f32 v65, %1, %2, v65\n\t"
-        "s_set_gpr_idx_off"
-        : "=&v"(t)
-        : "v"(a[0]), "s"(w), "s"(r)
-        : "m0");
-    return t;
-  }
-};
-template <>
-struct Files<2> {
-  static __device__ __forceinline__ void set_v(int r, const float (&v)[2]) {
-    asm volatile(
-        "s_set_gpr_idx_on %2, gpr_idx(DST)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 v64, %0\n\t"
-        "v_mov_b32 v160, %1\n\t"
-        "s_set_gpr_idx_off"
-        : 
-        : "v"(v[0]), "v"(v[1]), "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ void set_vg(int r, const float (&v)[2]) {
-    asm volatile(
-        "s_set_gpr_idx_on %2, gpr_idx(DST)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 v64, %0\n\t"
-        "v_mov_b32 v160, %1\n\t"
-        "v_mov_b32 v65, 0\n\t"
-        "v_mov_b32 v161, 0\n\t"
-        "s_set_gpr_idx_off"
-        : 
-        : "v"(v[0]), "v"(v[1]), "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ void get_v(int r, float (&t)[2]) {
-    asm volatile(
-        "s_set_gpr_idx_on %2, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 %0, v64\n\t"
-        "v_mov_b32 %1, v160\n\t"
-        "s_set_gpr_idx_off"
-        : "=v"(t[0]), "=v"(t[1])
-        : "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ void fma_v(float (&s)[2], float w, int r) {
-    asm volatile(
-        "s_set_gpr_idx_on %3, gpr_idx(SRC1)\n\t"
-        "s_nop 1\n\t"
-        "v_fmac_f32 %0, %2, v64\n\t"
-        "v_fmac_f32 %1, %2, v160\n\t"
-        "s_set_gpr_idx_off"
-        : "+v"(s[0]), "+v"(s[1])
-        : "s"(w), "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ void get_gv(int r, float (&g)[2], float (&v)[2]) {
-    asm volatile(
-        "s_set_gpr_idx_on %4, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 %0, v65\n\t"
-        "v_mov_b32 %1, v161\n\t"
-        "v_mov_b32 %2, v64\n\t"
-        "v_mov_b32 %3, v160\n\t"
-        "s_set_gpr_idx_off"
-        : "=v"(g[0]), "=v"(g[1]), "=v"(v[0]), "=v"(v[1])
-        : "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ void fma_g(int r, const float (&a)[2], float w) {
-    asm volatile(
-        "s_set_gpr_idx_on %3, gpr_idx(SRC2,DST)\n\t"
-        "s_nop 1\n\t"
-        "v_fma_f32 v65, %0, %2, v65\n\t"
-        "v_fma_f32 v161, %1, %2, v161\n\t"
-        "s_set_gpr_idx_off"
-        : 
-        : "v"(a[0]), "v"(a[1]), "s"(w), "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ float dot_v(int r, const float (&a)[2]) {
-    float t;
-    asm volatile(
-        "s_set_gpr_idx_on %3, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mul_f32 %0, v64, %1\n\t"
-        "v_fmac_f32 %0, v160, %2\n\t"
-        "s_set_gpr_idx_off"
-        : "=&v"(t)
-        : "v"(a[0]), "v"(a[1]), "s"(r)
-        : "m0");
-    return t;
-  }
-  static __device__ __forceinline__ float dot_v_fma_g(int r, const float (&a)[2], float w) {
-    float t;
-    asm volatile(
-        "s_set_gpr_idx_on %4, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mul_f32 %0, v64, %1\n\t"
-        "v_fmac_f32 %0, v160, %2\n\t"
-        "s_set_gpr_idx_off\n\t"
-        "s_set_gpr_idx_on %4, gpr_idx(SRC2,DST)\n\t"
-        "s_nop 1\n\t"
-        "v_fma_f32 v65, %1, %3, v65\n\t"
-        "v_fma_f32 v161, %2, %3, v161\n\t"
-        "s_set_gpr_idx_off"
-        : "=&v"(t)
-        : "v"(a[0]), "v"(a[1]), "s"(w), "s"(r)
-        : "m0");
-    return t;
-  }
-};
-template <>
-struct Files<4> {
-  static __device__ __forceinline__ void set_v(int r, const float (&v)[4]) {
-    asm volatile(
-        "s_set_gpr_idx_on %4, gpr_idx(DST)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 v64, %0\n\t"
-        "v_mov_b32 v112, %1\n\t"
-        "v_mov_b32 v160, %2\n\t"
-        "v_mov_b32 v208, %3\n\t"
-        "s_set_gpr_idx_off"
-        : 
-        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ void set_vg(int r, const float (&v)[4]) {
-    asm volatile(
-        "s_set_gpr_idx_on %4, gpr_idx(DST)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 v64, %0\n\t"
-        "v_mov_b32 v112, %1\n\t"
-        "v_mov_b32 v160, %2\n\t"
-        "v_mov_b32 v208, %3\n\t"
-        "v_mov_b32 v65, 0\n\t"
-        "v_mov_b32 v113, 0\n\t"
-        "v_mov_b32 v161, 0\n\t"
-        "v_mov_b32 v209, 0\n\t"
-        "s_set_gpr_idx_off"
-        : 
-        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ void get_v(int r, float (&t)[4]) {
-    asm volatile(
-        "s_set_gpr_idx_on %4, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 %0, v64\n\t"
-        "v_mov_b32 %1, v112\n\t"
-        "v_mov_b32 %2, v160\n\t"
-        "v_mov_b32 %3, v208\n\t"
-        "s_set_gpr_idx_off"
-        : "=v"(t[0]), "=v"(t[1]), "=v"(t[2]), "=v"(t[3])
-        : "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ void fma_v(float (&s)[4], float w, int r) {
-    asm volatile(
-        "s_set_gpr_idx_on %5, gpr_idx(SRC1)\n\t"
-        "s_nop 1\n\t"
-        "v_fmac_f32 %0, %4, v64\n\t"
-        "v_fmac_f32 %1, %4, v112\n\t"
-        "v_fmac_f32 %2, %4, v160\n\t"
-        "v_fmac_f32 %3, %4, v208\n\t"
-        "s_set_gpr_idx_off"
-        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3])
-        : "s"(w), "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ void get_gv(int r, float (&g)[4], float (&v)[4]) {
-    asm volatile(
-        "s_set_gpr_idx_on %8, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 %0, v65\n\t"
-        "v_mov_b32 %1, v113\n\t"
-        "v_mov_b32 %2, v161\n\t"
-        "v_mov_b32 %3, v209\n\t"
-        "v_mov_b32 %4, v64\n\t"
-        "v_mov_b32 %5, v112\n\t"
-        "v_mov_b32 %6, v160\n\t"
-        "v_mov_b32 %7, v208\n\t"
-        "s_set_gpr_idx_off"
-        : "=v"(g[0]), "=v"(g[1]), "=v"(g[2]), "=v"(g[3]), "=v"(v[0]), "=v"(v[1]), "=v"(v[2]), "=v"(v[3])
-        : "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ void fma_g(int r, const float (&a)[4], float w) {
-    asm volatile(
-        "s_set_gpr_idx_on %5, gpr_idx(SRC2,DST)\n\t"
-        "s_nop 1\n\t"
-        "v_fma_f32 v65, %0, %4, v65\n\t"
-        "v_fma_f32 v113, %1, %4, v113\n\t"
-        "v_fma_f32 v161, %2, %4, v161\n\t"
-        "v_fma_f32 v209, %3, %4, v209\n\t"
-        "s_set_gpr_idx_off"
-        : 
-        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "s"(w), "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ float dot_v(int r, const float (&a)[4]) {
-    float t;
-    asm volatile(
-        "s_set_gpr_idx_on %5, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mul_f32 %0, v64, %1\n\t"
-        "v_fmac_f32 %0, v112, %2\n\t"
-        "v_fmac_f32 %0, v160, %3\n\t"
-        "v_fmac_f32 %0, v208, %4\n\t"
-        "s_set_gpr_idx_off"
-        : "=&v"(t)
-        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "s"(r)
-        : "m0");
-    return t;
-  }
-  static __device__ __forceinline__ float dot_v_fma_g(int r, const float (&a)[4], float w) {
-    float t;
-    asm volatile(
-        "s_set_gpr_idx_on %6, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mul_f32 %0, v64, %1\n\t"
-        "v_fmac_f32 %0, v112, %2\n\t"
-        "v_fmac_f32 %0, v160, %3\n\t"
-        "v_fmac_f32 %0, v208, %4\n\t"
-        "s_set_gpr_idx_off\n\t"
-        "s_set_gpr_idx_on %6, gpr_idx(SRC2,DST)\n\t"
-        "s_nop 1\n\t"
-        "v_fma_f32 v65, %1, %5, v65\n\t"
-        "v_fma_f32 v113, %2, %5, v113\n\t"
-        "v_fma_f32 v161, %3, %5, v161\n\t"
-        "v_fma_f32 v209, %4, %5, v209\n\t"
-        "s_set_gpr_idx_off"
-        : "=&v"(t)
-        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "s"(w), "s"(r)
-        : "m0");
-    return t;
-  }
-};
-
-// a + b folded across the wavefront's halves: lanes 0..31 hold a's sums of
-// lanes l and l + 32, lanes 32..63 b's.
-__device__ __forceinline__ float fold32(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-// Likewise across 16 lanes: rows 0 and 2 of 16 lanes hold a's sums of rows
-// (0, 1) and (2, 3), rows 1 and 3 b's.
-__device__ __forceinline__ float fold16(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-// Four sums as quarters of 16 lanes: quarter q holds sum kQuarter[q].
-__device__ __forceinline__ float fold4(float t0, float t1, float t2, float t3) {
-  return fold16(fold32(t0, t1), fold32(t2, t3));
-}
-__device__ __forceinline__ int sum_of_quarter(int q) { return (q >> 1) | ((q & 1) << 1); }
-
 // What a step reads of its genome, and this lane's share of it (computed node
 // i in lane i).
 struct RfGenome {
@@ -897,7 +487,7 @@ __device__ __forceinline__ float rf_step(const RfGenome& q, int b0, const float*
   return sse;
 }
 
-__global__ __launch_bounds__(kWave * kRfWaves) __attribute__((amdgpu_num_vgpr(TN_BW_RF_BASE / 2))) void
+__global__ __launch_bounds__(kWave * kRfWaves) __attribute__((amdgpu_num_vgpr(TN_RF_FILE / 2))) void
 backward_rf_kernel(PopView pop, const int32_t* __restrict__ status,
                    const int32_t* __restrict__ n_valid, const int32_t* __restrict__ order,
                    const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ src,
@@ -905,7 +495,7 @@ backward_rf_kernel(PopView pop, const int32_t* __restrict__ status,
                    const int32_t* __restrict__ fn, const int32_t* __restrict__ bias_bits,
                    const int32_t* __restrict__ resp_bits, const int32_t* __restrict__ io_pos,
                    const float* __restrict__ obs, BwdArgs a) {
-  asm volatile("" ::: "v255");  // the register file counts in the allocation
+  rf_file_reserve();
   extern __shared__ __align__(16) float acc_all[];  // [waves][kRfSums][64]
   __shared__ int2 edge[kRfEdges + kWave];
   __shared__ int32_t sums_of[kRfSums];  // a row of sums' computed node | its row of the node << 8

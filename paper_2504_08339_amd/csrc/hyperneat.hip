@@ -6,8 +6,8 @@
 //
 //   query    one lane = one substrate connection (s -> t): the CPPN's inputs
 //            (x_s, y_s, x_t, y_t, 1) are computed from the indices and its
-//            packed program runs in registers (the register engine's walk);
-//            weights are stored transposed, w1t[t][s] and w2t[j][s], so that
+//            program runs in registers, nodes that see only sources or only
+//            targets once for many connections; weights are stored transposed, w1t[t][s] and w2t[j][s], so that
 //            both GEMM operands are contiguous along the reduction index.
 //   hidden   H = tanh(X W1): v_mfma_f32_16x16x32_bf16, a workgroup of four
 //            wavefronts per 128 x 128 tile of H with K staged through LDS,
@@ -18,6 +18,7 @@
 #include <algorithm>
 
 #include "fwd_reg.hpp"
+#include "rf_file.hpp"
 #include "tn_internal.hpp"
 
 namespace tn {
@@ -154,6 +155,387 @@ cppn_query_kernel(PopView pop, const int32_t* __restrict__ status,
         if (R2) R2[qq] = y[k];
       }
     }
+  }
+}
+
+// ------------------------------------------------ CPPN over the substrate
+//
+// The query and its adjoint walk a CPPN at every (source, target) pair. A
+// wavefront takes 64 sources (lane = source) and a run of targets, K targets
+// (the tiles of a register file) at a time, so a node's in-edges say how often
+// it has to be evaluated:
+//   fixed    it depends on no target coordinate: once per wavefront;
+//   target   on no source coordinate: once for up to 64 targets (lane =
+//            target), then read back from LDS, one broadcast per step;
+//   both     at every step.
+// The same operations in the same order give every value its bits.
+struct CppnWave {
+  const int2* edge;  // LDS: the source's row, weight; 64 more are readable
+  uint64_t fixed, target, both;  // positions
+  int l_fn, l_bias, l_resp;      // of position `lane`
+  int l_edge;                    // first in-edge | in-edges << 16
+  int l_row;                     // row in the file
+  int n_rows;                    // rows of computed nodes (inputs come after them), if kGrad
+  int in_row[5];                 // rows of the inputs
+  int op;                        // the output's position
+  int n_kept;                    // target coordinates (2) and target nodes
+};
+
+// An activation whose slope needs the pre-activation keeps it in a row.
+__device__ __forceinline__ int node_width(int f) { return 2 + (slope_needs_z(f & 7) ? 1 : 0); }
+
+// By all threads of a workgroup; n <= 64 positions. kGrad: a node takes
+// node_width rows and the inputs' rows follow; else position p takes row p.
+template <bool kGrad>
+__device__ __forceinline__ CppnWave cppn_program(int n, int n_edges, const int32_t* rp,
+                                                 const int32_t* edge_src, const int32_t* w_bits,
+                                                 const int32_t* fn, const int32_t* bias_bits,
+                                                 const int32_t* resp_bits, const int32_t* io,
+                                                 int slots, int2* edge) {
+  const int lane = lane_id(), tid = threadIdx.x, T = blockDim.x;
+  CppnWave c;
+  c.edge = edge;
+  c.l_fn = lane < n ? fn[lane] : -1;
+  c.l_bias = lane < n ? bias_bits[lane] : 0;
+  c.l_resp = lane < n ? resp_bits[lane] : 0;
+  const int start = lane < n ? rp[lane] : 0, end = lane < n ? rp[lane + 1] : 0;
+  c.l_edge = start | ((end - start) << 16);
+  const uint64_t nodes = __ballot(c.l_fn >= 0);
+  const uint64_t inputs = __ballot(lane < n && c.l_fn < 0);
+  c.n_rows = 0;
+  if (kGrad) {
+    const int width = c.l_fn >= 0 ? node_width(c.l_fn) : 0;
+    const int upto = wave_inclusive_scan(width);
+    c.n_rows = __builtin_amdgcn_readlane(upto, kWave - 1);
+    c.l_row = c.l_fn >= 0 ? upto - width : c.n_rows + mbcnt(inputs);
+  } else {
+    c.l_row = lane;
+  }
+  int first_src = 0;
+  for (int e0 = 0; e0 < n_edges; e0 += T) {  // whole wavefronts: the shuffle
+    const int e = e0 + tid;
+    const int q = e < n_edges ? edge_src[e] : 0;
+    const int row = __shfl(c.l_row, q, kWave);
+    if (e < n_edges) edge[e] = make_int2(row, w_bits[e]);
+  }
+  first_src = lane < n_edges ? edge_src[lane] : 0;  // the first 64 edges' sources
+  uint64_t on_src = 0, on_tgt = 0;
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const int p = io[i];
+    c.in_row[i] = __builtin_amdgcn_readlane(c.l_row, p);
+    if (i < 2) on_src |= (uint64_t)1 << p;
+    else if (i < 4) on_tgt |= (uint64_t)1 << p;
+  }
+  c.op = io[5];
+  for (uint64_t m = nodes; m; m &= m - 1) {
+    const int p = __builtin_ctzll(m);
+    const int le = __builtin_amdgcn_readlane(c.l_edge, p);
+    const int e0 = le & 0xffff, e1 = e0 + (le >> 16);
+    bool s = false, t = false;
+    if (lane >= e0 && lane < e1) {
+      s = (on_src >> first_src) & 1;
+      t = (on_tgt >> first_src) & 1;
+    }
+    for (int e = max(e0, kWave) + lane; e < e1; e += kWave) {
+      const int q = edge_src[e];
+      s |= (on_src >> q) & 1;
+      t |= (on_tgt >> q) & 1;
+    }
+    if (__ballot(s)) on_src |= (uint64_t)1 << p;
+    if (__ballot(t)) on_tgt |= (uint64_t)1 << p;
+  }
+  c.fixed = nodes & ~on_tgt;
+  c.target = nodes & on_tgt & ~on_src;
+  // those that fit the slots, in topological order, are kept in LDS; the others
+  // run at every step
+  uint64_t kept = 0;
+  c.n_kept = 2;
+  for (; c.n_kept < slots && c.target; ++c.n_kept) {
+    kept |= c.target & -c.target;
+    c.target &= c.target - 1;
+  }
+  c.target = kept;
+  c.both = nodes & ~c.fixed & ~c.target;
+  return c;
+}
+
+__device__ __forceinline__ int2 cppn_edges(const CppnWave& c, int p) {
+  return c.edge[(__builtin_amdgcn_readlane(c.l_edge, p) & 0xffff) + lane_id()];
+}
+
+// Pre-activations of the computed position p in K tiles; ed: cppn_edges(p).
+// kAny: every aggregation and any number of in-edges, else sum or mean of at
+// most 64.
+template <class F, int K, bool kAny>
+__device__ __forceinline__ void cppn_pre(const CppnWave& c, int p, int2 ed, float (&z)[K]) {
+  const int f = __builtin_amdgcn_readlane(c.l_fn, p);
+  const int le = __builtin_amdgcn_readlane(c.l_edge, p);
+  const int ne = le >> 16, agg = (f >> 8) & 0xff;
+  auto row = [&](int e) { return __builtin_amdgcn_readlane(ed.x, e); };
+  auto weight = [&](int e) { return __int_as_float(__builtin_amdgcn_readlane(ed.y, e)); };
+  float s[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) s[k] = 0.0f;
+  if (!kAny || agg == TN_AGG_SUM) {
+    const int n0 = kAny ? min(ne, kWave) : ne;
+    if (n0 > 0) {
+      F::fma_v(s, weight(0), row(0));
+      if (n0 > 1) {
+        F::fma_v(s, weight(1), row(1));
+        for (int e = 2; e < n0; ++e) F::fma_v(s, weight(e), row(e));
+      }
+    }
+    if (kAny)
+      for (int b = kWave; b < ne; b += kWave) {
+        ed = c.edge[(le & 0xffff) + b + lane_id()];
+        for (int e = 0; e < min(ne - b, kWave); ++e) F::fma_v(s, weight(e), row(e));
+      }
+    if (!kAny && agg == TN_AGG_MEAN && ne > 0)
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        s[k] = s[k] / (float)ne;
+        asm volatile("" : "+v"(s[k]));
+      }
+  } else if (ne > 0) {
+    // other aggregations: terms in order
+    for (int b = 0; b < ne; b += kWave) {
+      if (b) ed = c.edge[(le & 0xffff) + b + lane_id()];
+      for (int e = 0; e < min(ne - b, kWave); ++e) {
+        float x[K];
+        F::get_v(row(e), x);
+        const float w = weight(e);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          const float t = w * x[k];
+          if (b + e == 0) {
+            s[k] = t;
+            continue;
+          }
+          switch (agg) {
+            case TN_AGG_PRODUCT: s[k] = s[k] * t; break;
+            case TN_AGG_MAX: s[k] = fmaxf(s[k], t); break;
+            case TN_AGG_MIN: s[k] = fminf(s[k], t); break;
+            case TN_AGG_MEAN: s[k] = s[k] + t; break;
+            default: s[k] = fabsf(t) > fabsf(s[k]) ? t : s[k]; break;  // maxabs
+          }
+        }
+      }
+    }
+    if (agg == TN_AGG_MEAN)
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        s[k] = s[k] / (float)ne;
+        asm volatile("" : "+v"(s[k]));
+      }
+  }
+  const float rho = __int_as_float(__builtin_amdgcn_readlane(c.l_resp, p));
+  const float bias = __int_as_float(__builtin_amdgcn_readlane(c.l_bias, p));
+#pragma unroll
+  for (int k = 0; k < K; ++k) z[k] = fmaf(rho, s[k], bias);
+}
+
+// f(p, its in-edges) for every position of `m`, in topological order, the next
+// position's in-edges read ahead.
+template <class Fn>
+__device__ __forceinline__ void cppn_forward(const CppnWave& c, uint64_t m, Fn f) {
+  if (!m) return;
+  int p = __builtin_ctzll(m);
+  int2 ed = cppn_edges(c, p);
+  for (;;) {
+    m &= m - 1;
+    const int next = m ? __builtin_ctzll(m) : p;
+    const int2 en = cppn_edges(c, next);
+    f(p, ed);
+    if (!m) break;
+    p = next;
+    ed = en;
+  }
+}
+template <class Fn>
+__device__ __forceinline__ void cppn_reverse(const CppnWave& c, uint64_t m, Fn f) {
+  if (!m) return;
+  int p = 63 - __builtin_clzll(m);
+  int2 ed = cppn_edges(c, p);
+  for (;;) {
+    m ^= (uint64_t)1 << p;
+    const int next = m ? 63 - __builtin_clzll(m) : p;
+    const int2 en = cppn_edges(c, next);
+    f(p, ed);
+    if (!m) break;
+    p = next;
+    ed = en;
+  }
+}
+
+// Coordinates: source s of the grid, target t of the hidden grid or of the
+// output row.
+__device__ __forceinline__ void source_xy(const SubGeom& sg, int s, float* x, float* y) {
+  const int r = s / sg.grid, c = s - r * sg.grid;
+  *x = fmaf((float)c, sg.step, -1.0f);
+  *y = fmaf((float)r, sg.step, -1.0f);
+}
+__device__ __forceinline__ void target_xy(const SubGeom& sg, bool hidden, int t, float* x,
+                                          float* y) {
+  if (hidden) {
+    source_xy(sg, t, x, y);
+  } else {
+    *x = sg.n_out > 1 ? fmaf((float)t, sg.ostep, -1.0f) : 0.0f;
+    *y = 0.0f;
+  }
+}
+
+// A wavefront's part: sources s0 .. s0 + 63, targets t0 .. t1 - 1 of the
+// hidden grid or the outputs. Items of a genome run over the blocks of sources,
+// then over the runs of `per` targets.
+struct CppnItem {
+  bool hidden;
+  int s0, t0, t1;
+};
+__host__ __device__ inline int cppn_items(const SubGeom& sg, int per) {
+  return (sg.S / kWave) * ((sg.S + per - 1) / per + (sg.n_out + per - 1) / per);
+}
+__device__ __forceinline__ CppnItem cppn_item(const SubGeom& sg, int per, int item) {
+  const int blocks = sg.S / kWave, runs = (sg.S + per - 1) / per;
+  const int run = item / blocks;
+  CppnItem it;
+  it.s0 = (item - run * blocks) * kWave;
+  it.hidden = run < runs;
+  it.t0 = (it.hidden ? run : run - runs) * per;
+  it.t1 = min(it.t0 + per, it.hidden ? sg.S : sg.n_out);
+  return it;
+}
+
+// The query for populations of at most kMapRows node rows (one row of the file
+// each): four targets a step for genomes of up to 20 positions, else two. Bound
+// by instruction issue (activations and in-edge windows). 200 CPPNs (33
+// in-edges, 11 computed nodes) over a 32 x 32 grid and 8 outputs: 1348 us; 2181
+// us in cppn_query_kernel, which evaluates every node at every pair with two
+// wavefronts per SIMD. With this walk on a file of 48 rows for
+// four tiles (two wavefronts per SIMD) 1841 us, of 28 rows (three) 1493 us.
+constexpr int kMapRows = 32, kMapWaves = 4;
+// targets per wavefront (64 measured 1348 us where 128 take 1420: the last
+// round is shorter); table rows
+constexpr int kMapRun = 128, kMapWavesWanted = 32768, kMapSlots = 16;
+
+template <int K>
+__device__ __forceinline__ void cppn_map(const CppnWave& c, const SubGeom& sg, const CppnItem& it,
+                                         float (*table)[kMapRun], uint16_t* __restrict__ W,
+                                         float* __restrict__ R) {
+  using F = ShortFiles<K>;
+  const int lane = lane_id();
+  const int runs = it.t1 - it.t0;
+  // Step -2 evaluates the fixed nodes, step -1 (lane = target, in two tiles) the
+  // target nodes, the others K targets each: one walk in the code for all.
+  for (int step = -2; step * K < runs; ++step) {
+    const int t = step * K;
+    float v[K];
+    uint64_t nodes = c.both;
+    if (step < -1) {
+      float x0, y0, one = 1.0f;
+      asm volatile("" : "+v"(one));
+      source_xy(sg, it.s0 + lane, &x0, &y0);
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = x0;
+      F::set_v(c.in_row[0], v);
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = y0;
+      F::set_v(c.in_row[1], v);
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = one;
+      F::set_v(c.in_row[4], v);
+      nodes = c.fixed;
+    } else if (step < 0) {
+      float x[2], y[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        target_xy(sg, it.hidden, min(it.t0 + k * kWave + lane, it.t1 - 1), &x[k], &y[k]);
+        table[0][k * kWave + lane] = x[k];
+        table[1][k * kWave + lane] = y[k];
+      }
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = x[k % 2];
+      F::set_v(c.in_row[2], v);
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = y[k % 2];
+      F::set_v(c.in_row[3], v);
+      nodes = c.target;
+    } else {
+      uint64_t m = c.target;
+      for (int slot = 0; slot < c.n_kept; ++slot) {
+        const int row = slot == 0 ? c.in_row[2] : slot == 1 ? c.in_row[3] : __builtin_ctzll(m);
+        if (slot >= 2) m &= m - 1;
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = table[slot][t + k];
+        F::set_v(row, v);
+      }
+    }
+    int slot = 2;
+    cppn_forward(c, nodes, [&](int p, int2 ed) __attribute__((always_inline)) {
+      float z[K];
+      cppn_pre<F, K, true>(c, p, ed, z);
+      activate_all<K>(__builtin_amdgcn_readlane(c.l_fn, p) & 7, z, v);
+      F::set_v(p, v);
+      if (step == -1) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) table[slot][k * kWave + lane] = v[k];
+        ++slot;
+      }
+    });
+    if (step < 0) continue;
+    F::get_v(c.op, v);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (t + k >= runs) break;
+      const int64_t q = (int64_t)(t + k) * sg.S + lane;
+      W[q] = bf16_bits(fabsf(v[k]) < sg.thr ? 0.0f : v[k]);
+      if (R) R[q] = v[k];
+    }
+  }
+}
+
+__global__ __launch_bounds__(kWave * kMapWaves) __attribute__((amdgpu_num_vgpr(TN_RF_SHORT / 2))) void
+cppn_map_kernel(PopView pop, const int32_t* __restrict__ status,
+                const int32_t* __restrict__ prog_rows, const int32_t* __restrict__ n_valid,
+                const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ edge_src,
+                const int32_t* __restrict__ w_bits, const int32_t* __restrict__ fn,
+                const int32_t* __restrict__ bias_bits, const int32_t* __restrict__ resp_bits,
+                const int32_t* __restrict__ io_pos, SubGeom sg, int run, int wg_per_g,
+                uint16_t* __restrict__ w1t, uint16_t* __restrict__ w2t, float* __restrict__ raw1,
+                float* __restrict__ raw2) {
+  short_file_reserve();
+  extern __shared__ int2 map_edge[];
+  __shared__ __align__(16) float table_all[kMapWaves][kMapSlots][kMapRun];
+  const int lane = lane_id(), wave = wave_id();
+  const int g = blockIdx.x / wg_per_g;
+  const int item = (blockIdx.x - g * wg_per_g) * kMapWaves + wave;
+  const int64_t nb = uniform64(pop.node_base(g)), cb = uniform64(pop.conn_base(g)),
+                rb = uniform64(pop.rowptr_base(g));
+  const bool bad = status[g] != 0 || prog_rows[g] > kQueryRows;
+  const int n = n_valid[g];
+  CppnWave c{};
+  if (!bad) {
+    c = cppn_program<false>(n, row_ptr[rb + n], row_ptr + rb, edge_src + cb, w_bits + cb, fn + nb,
+                            bias_bits + nb, resp_bits + nb,
+                            io_pos + (int64_t)g * (pop.n_in + pop.n_out), kMapSlots, map_edge);
+  }
+  __syncthreads();
+  if (item >= cppn_items(sg, run)) return;
+  const CppnItem it = cppn_item(sg, run, item);
+  const int64_t Q1 = (int64_t)sg.S * sg.S, Q2 = (int64_t)sg.S * sg.n_out;
+  const int64_t at = (it.hidden ? g * Q1 : g * Q2) + (int64_t)it.t0 * sg.S + it.s0;
+  uint16_t* W = (it.hidden ? w1t : w2t) + at;
+  float* R = it.hidden ? raw1 : raw2;
+  if (R) R += at;
+  if (bad) {
+    for (int t = 0; t < it.t1 - it.t0; ++t) {
+      W[(int64_t)t * sg.S + lane] = bf16_bits(__builtin_nanf(""));
+      if (R) R[(int64_t)t * sg.S + lane] = __builtin_nanf("");
+    }
+  } else if (n <= kShortFileRows / 4) {
+    cppn_map<4>(c, sg, it, table_all[wave], W, R);
+  } else {
+    cppn_map<2>(c, sg, it, table_all[wave], W, R);
   }
 }
 
@@ -660,306 +1042,267 @@ __global__ __launch_bounds__(256) void transpose_x_kernel(const uint16_t* __rest
 
 // ----------------------------------------------------------- CPPN adjoint
 
-// Limits of the CPPN adjoint: node values, pre-activations and upstream
-// gradients live in registers indexed by topological position (no row reuse:
-// the reverse sweep needs every value).
+// Limits of the CPPN adjoint.
 constexpr int kCppnNodes = 32, kCppnEdges = 64;
-constexpr int kCppnPart = kCppnEdges + kCppnNodes;  // partial sums per wavefront
+constexpr int kCppnPart = kCppnEdges + kCppnNodes;  // partial sums per workgroup
+// rows of four sums: a computed node takes (in-edges + 4) / 4 of them
+constexpr int kCppnSums = (kCppnEdges + 4 * (kCppnNodes - 5)) / 4;
+// 64 targets per wavefront measured 1287 us, 32 (twice the wavefronts) 1438 us
+constexpr int kCppnWaves = 4, kCppnRun = 64, kCppnWavesWanted = 4096, kCppnSlots = 12;
 
-// Register file of the adjoint, per tile of 64 queries: values V at rows
-// 0..31, pre-activations Z at 32..63, upstream gradients G at 64..95; two
-// tiles per wavefront, tile 0 at v56, tile 1 at v152 (v56..v247 in all, the
-// compiler keeping v0..v55). Windows wait two cycles after s_set_gpr_idx_on
-// (see fwd_reg.hpp).
-__device__ __forceinline__ void adj_reserve() { asm volatile("" ::: "v247"); }
-
-// s{0,1} += w * V[j] of tiles 0 and 1.
-__device__ __forceinline__ void adj_fma_v(float& s0, float& s1, float w, int j) {
-  asm volatile(
-      "s_set_gpr_idx_on %3, gpr_idx(SRC1)\n\ts_nop 1\n\tv_fmac_f32 %0, %2, v56\n\t"
-      "v_fmac_f32 %1, %2, v152\n\ts_set_gpr_idx_off"
-      : "+v"(s0), "+v"(s1)
-      : "s"(w), "s"(j) : "m0");
-}
-// V[p] := v{0,1}
-__device__ __forceinline__ void adj_set_v(int p, float v0, float v1) {
-  asm volatile(
-      "s_set_gpr_idx_on %2, gpr_idx(DST)\n\ts_nop 1\n\tv_mov_b32 v56, %0\n\t"
-      "v_mov_b32 v152, %1\n\ts_set_gpr_idx_off" ::"v"(v0),
-      "v"(v1), "s"(p) : "m0");
-}
-// V[p] := v{0,1}, Z[p] := z{0,1}
-__device__ __forceinline__ void adj_set_vz(int p, float v0, float v1, float z0, float z1) {
-  asm volatile(
-      "s_set_gpr_idx_on %4, gpr_idx(DST)\n\ts_nop 1\n\tv_mov_b32 v56, %0\n\t"
-      "v_mov_b32 v152, %1\n\tv_mov_b32 v88, %2\n\tv_mov_b32 v184, %3\n\ts_set_gpr_idx_off" ::"v"(v0),
-      "v"(v1), "v"(z0), "v"(z1), "s"(p) : "m0");
-}
-// G[p] := g{0,1}
-__device__ __forceinline__ void adj_set_g(int p, float g0, float g1) {
-  asm volatile(
-      "s_set_gpr_idx_on %2, gpr_idx(DST)\n\ts_nop 1\n\tv_mov_b32 v120, %0\n\t"
-      "v_mov_b32 v216, %1\n\ts_set_gpr_idx_off" ::"v"(g0),
-      "v"(g1), "s"(p) : "m0");
-}
-// t{0,1} := V[j]
-__device__ __forceinline__ void adj_get_v(int j, float& t0, float& t1) {
-  asm volatile(
-      "s_set_gpr_idx_on %2, gpr_idx(SRC0)\n\ts_nop 1\n\tv_mov_b32 %0, v56\n\t"
-      "v_mov_b32 %1, v152\n\ts_set_gpr_idx_off"
-      : "=v"(t0), "=v"(t1)
-      : "s"(j) : "m0");
-}
-// G[p], V[p], Z[p] of both tiles
-__device__ __forceinline__ void adj_get_gvz(int p, float& g0, float& g1, float& v0, float& v1,
-                                            float& z0, float& z1) {
-  asm volatile(
-      "s_set_gpr_idx_on %6, gpr_idx(SRC0)\n\ts_nop 1\n\tv_mov_b32 %0, v120\n\t"
-      "v_mov_b32 %1, v216\n\tv_mov_b32 %2, v56\n\tv_mov_b32 %3, v152\n\t"
-      "v_mov_b32 %4, v88\n\tv_mov_b32 %5, v184\n\ts_set_gpr_idx_off"
-      : "=v"(g0), "=v"(g1), "=v"(v0), "=v"(v1), "=v"(z0), "=v"(z1)
-      : "s"(p) : "m0");
-}
-// G[j] += dt{0,1} * w, one indexed read-modify-write per tile
-__device__ __forceinline__ void adj_fma_g(int j, float dt0, float dt1, float w) {
-  asm volatile(
-      "s_set_gpr_idx_on %3, gpr_idx(SRC2,DST)\n\ts_nop 1\n\tv_fma_f32 v120, %0, %2, v120\n\t"
-      "v_fma_f32 v216, %1, %2, v216\n\ts_set_gpr_idx_off" ::"v"(dt0),
-      "v"(dt1), "s"(w), "s"(j) : "m0");
-}
-// G := 0 for both tiles (fixed registers, no window)
-__device__ __forceinline__ void adj_zero_g() {
-  asm volatile(
-#define TN_Z4(a, b, c, d) "v_mov_b32 v" #a ", 0\n\tv_mov_b32 v" #b ", 0\n\tv_mov_b32 v" #c \
-                          ", 0\n\tv_mov_b32 v" #d ", 0\n\t"
-      TN_Z4(120, 121, 122, 123) TN_Z4(124, 125, 126, 127) TN_Z4(128, 129, 130, 131)
-      TN_Z4(132, 133, 134, 135) TN_Z4(136, 137, 138, 139) TN_Z4(140, 141, 142, 143)
-      TN_Z4(144, 145, 146, 147) TN_Z4(148, 149, 150, 151) TN_Z4(216, 217, 218, 219)
-      TN_Z4(220, 221, 222, 223) TN_Z4(224, 225, 226, 227) TN_Z4(228, 229, 230, 231)
-      TN_Z4(232, 233, 234, 235) TN_Z4(236, 237, 238, 239) TN_Z4(240, 241, 242, 243)
-      TN_Z4(244, 245, 246, 247)
-#undef TN_Z4
-      "s_nop 0");
-}
-
-__device__ __forceinline__ float cppn_slope(int act, float v, float z) {
-  switch (act) {
-    case TN_ACT_IDENTITY: return 1.0f;
-    case TN_ACT_SIGMOID: return v * (1.0f - v);
-    case TN_ACT_TANH: return fmaf(-v, v, 1.0f);
-    case TN_ACT_RELU: return v > 0.0f ? 1.0f : 0.0f;
-    case TN_ACT_SIN: return cosf(z);
-    case TN_ACT_GAUSSIAN: return -2.0f * z * v;
-    default: return z > 0.0f ? 1.0f : (z < 0.0f ? -1.0f : 0.0f);  // abs
-  }
-}
+struct CppnLds {
+  int2 edge[kCppnEdges + kWave];
+  float acc[kCppnWaves][kCppnSums][kWave];
+  // values and slopes of the targets' coordinates and target nodes
+  __align__(16) float table[kCppnWaves][kCppnSlots][2][kCppnRun];
+  float part[kCppnPart];
+};
 
 // The gradient of sum_q u_q * w(q) over every query q of the substrate with
 // respect to the CPPN's connection weights and node biases, where the upstream
 // u_q is dw1t / dw2t at the query when its weight survived the threshold (the
-// CPPN value of this very evaluation, float32) and 0 otherwise. Each lane runs
-// the CPPN forward at one query of each of the wavefront's two tiles (values
-// and pre-activations kept by position), then the reverse sweep:
+// CPPN value of this very evaluation, float32) and 0 otherwise. A wavefront
+// (64 sources, 64 targets, K targets a step: four, or two for genomes whose
+// rows do not fit) runs the forward pass as the query does, each value beside
+// its gradient in the register file (and its slope, where that needs the
+// pre-activation), then the reverse sweep:
 //   delta_k = gbar_k act'(z_k);  db_k += delta_k;
 //   for in-edge e = (j -> k): dt = delta_k rho_k (/ n for mean);
 //   dw_e += dt v_j;  gbar_j += dt w_e
-// The per-lane sums (both tiles' terms added first) accumulate in LDS, one
-// slot per lane and sum (read, add, write: a wavefront's LDS operations
-// complete in order, so each sum runs in program order); at the end every
-// slot is reduced over the wavefront in a fixed order and written to this
-// wavefront's slot of `part`.
+// A fixed node's gradient is linear in its gbar, and its value is the same at
+// every step: its gbar adds up over the steps and its own sweep runs once, at
+// the end. Sums are folded four at a time into one LDS row (see rf_file.hpp),
+// then added over the workgroup in a fixed order, one partial per workgroup.
 // Sum and mean aggregation only (the CPPN's); other genomes get NaN.
-// The kernel is compiled for two slot counts and both forms are launched:
-// KE = 48 in-edge slots (80 per lane with the node slots: 20 KB per
-// wavefront, so eight wavefronts fit a compute unit's LDS, as many as its
-// registers allow) takes the genomes with at most 48 in-edges, KE = 64 the
-// others and writes the NaN partials of the genomes no form takes.
-constexpr int kCppnWaves = 2, kCppnUnitsPerWave = 32, kCppnUnit = 2 * kWave;
-constexpr int kCppnCompactEdges = 48;
+// Bound by instruction issue; registers hold two wavefronts per SIMD. 50 CPPNs
+// (11 computed nodes, 33 in-edges), 32 x 32 grid, 8 outputs: 1287 us; 2479 us
+// with every node at every pair, two tiles a step and a slot per sum and lane.
+template <int K>
+__device__ __forceinline__ void cppn_adjoint(const CppnWave& c, const SubGeom& sg,
+                                             const CppnItem& it, int l_sum,
+                                             const float* __restrict__ up, float (*acc)[kWave],
+                                             float (*table)[2][kCppnRun]) {
+  using F = Files<K>;
+  const int lane = lane_id();
+  auto row_of = [&](int p) { return __builtin_amdgcn_readlane(c.l_row, p); };
+  auto act_of = [&](int p) { return __builtin_amdgcn_readlane(c.l_fn, p) & 7; };
+  auto back = [&](int p, int2 ed) __attribute__((always_inline)) {
+    const int act = act_of(p), row = row_of(p);
+    const int le = __builtin_amdgcn_readlane(c.l_edge, p), ne = le >> 16;
+    const int f = __builtin_amdgcn_readlane(c.l_fn, p);
+    float* sum = acc[__builtin_amdgcn_readlane(l_sum, p)] + lane;
+    float old = *sum;
+    float g[K], v[K], slope[K], dt[K], db = 0.0f;
+    F::get_gv(row, g, v);
+    if (slope_needs_z(act))
+      F::get_v(row + 2, slope);
+    else
+      act_slopes_v<K>(act, v, slope);
+    const float rho = __int_as_float(__builtin_amdgcn_readlane(c.l_resp, p));
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const float d = g[k] * slope[k];
+      db += d;
+      dt[k] = d * rho;
+    }
+    if (((f >> 8) & 0xff) == TN_AGG_MEAN && ne > 0)
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        dt[k] = dt[k] / (float)ne;
+        asm volatile("" : "+v"(dt[k]));
+      }
+    auto term = [&](int e) {
+      const int j = __builtin_amdgcn_readlane(ed.x, e);
+      return j < c.n_rows
+                 ? F::dot_v_fma_g(j, dt, __int_as_float(__builtin_amdgcn_readlane(ed.y, e)))
+                 : F::dot_v(j, dt);  // an input
+    };
+    float t1 = 0.0f, t2 = 0.0f, t3 = 0.0f;
+    if (ne > 0) {
+      t1 = term(0);
+      if (ne > 1) {
+        t2 = term(1);
+        if (ne > 2) t3 = term(2);
+      }
+    }
+    *sum = old + fold4(db, t1, t2, t3);
+    for (int e = 3; e < ne; e += 4) {
+      sum += kWave;
+      old = *sum;
+      const float t0 = term(e);
+      t1 = t2 = t3 = 0.0f;
+      if (e + 1 < ne) {
+        t1 = term(e + 1);
+        if (e + 2 < ne) {
+          t2 = term(e + 2);
+          if (e + 3 < ne) t3 = term(e + 3);
+        }
+      }
+      *sum = old + fold4(t0, t1, t2, t3);
+    }
+  };
+  const int op_row = row_of(c.op);
+  const int runs = it.t1 - it.t0;
+  // Step -2 evaluates the fixed nodes, step -1 (lane = target) the target
+  // nodes, the others K targets each, and the last sweeps the fixed nodes back:
+  // one walk each way in the code for all.
+  const int last = (runs + K - 1) / K * K;
+  for (int t = -2 * K; t <= last; t += K) {
+    float v[K], slope[K], u[K];
+    uint64_t forth = c.both, back_over = c.both | c.target;
+    if (t < -K) {
+      float x0, y0, one = 1.0f;
+      asm volatile("" : "+v"(one));
+      source_xy(sg, it.s0 + lane, &x0, &y0);
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = x0;
+      F::set_v(c.in_row[0], v);
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = y0;
+      F::set_v(c.in_row[1], v);
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = one;
+      F::set_v(c.in_row[4], v);
+      forth = c.fixed;
+    } else if (t < 0) {
+      float x0, y0;
+      target_xy(sg, it.hidden, min(it.t0 + lane, it.t1 - 1), &x0, &y0);
+      table[0][0][lane] = x0;
+      table[1][0][lane] = y0;
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = x0;
+      F::set_v(c.in_row[2], v);
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] = y0;
+      F::set_v(c.in_row[3], v);
+      forth = c.target;
+    } else if (t < last) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) u[k] = up[(int64_t)min(t + k, runs - 1) * sg.S + lane];
+      uint64_t m = c.target;
+      for (int slot = 0; slot < c.n_kept; ++slot) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = table[slot][0][t + k];
+        if (slot < 2) {
+          F::set_v(slot == 0 ? c.in_row[2] : c.in_row[3], v);
+        } else {
+          const int p = __builtin_ctzll(m), row = row_of(p);
+          m &= m - 1;
+          F::set_vg(row, v);
+          if (slope_needs_z(act_of(p))) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) slope[k] = table[slot][1][t + k];
+            F::set_v(row + 2, slope);
+          }
+        }
+      }
+    } else {
+      forth = 0;
+      back_over = c.fixed;
+    }
+    int slot = 2;
+    cppn_forward(c, forth, [&](int p, int2 ed) __attribute__((always_inline)) {
+      float z[K];
+      cppn_pre<F, K, false>(c, p, ed, z);
+      const int act = act_of(p), row = row_of(p);
+      activate_all<K>(act, z, v);
+      F::set_vg(row, v);
+      slope[0] = 0.0f;
+      if (slope_needs_z(act)) {
+        act_slopes<K>(act, v, z, slope);
+        F::set_v(row + 2, slope);
+      }
+      if (t == -K) {
+        table[slot][0][lane] = v[0];
+        table[slot][1][lane] = slope[0];
+        ++slot;
+      }
+    });
+    if (t < 0) continue;
+    if (t < last) {
+      float y[K];
+      F::get_v(op_row, y);
+#pragma unroll
+      for (int k = 0; k < K; ++k)  // NaN y: no gradient
+        u[k] = t + k < runs && fabsf(y[k]) >= sg.thr ? u[k] : 0.0f;
+      F::fma_g(op_row, u, 1.0f);
+    }
+    cppn_reverse(c, back_over, back);
+  }
+}
 
-template <int KE>
-__global__ __launch_bounds__(kWave * kCppnWaves) __attribute__((amdgpu_num_vgpr(TN_RF_BASE))) void
+__global__ __launch_bounds__(kWave * kCppnWaves) __attribute__((amdgpu_num_vgpr(TN_RF_FILE / 2))) void
 cppn_backward_kernel(PopView pop, const int32_t* __restrict__ status,
                      const int32_t* __restrict__ n_valid, const int32_t* __restrict__ row_ptr,
                      const int32_t* __restrict__ edge_src, const int32_t* __restrict__ w_bits,
                      const int32_t* __restrict__ fn, const int32_t* __restrict__ bias_bits,
                      const int32_t* __restrict__ resp_bits, const int32_t* __restrict__ io_pos,
-                     SubGeom sg, int n_chunks, const float* __restrict__ dw1t,
+                     SubGeom sg, int run, int wg_per_g, const float* __restrict__ dw1t,
                      const float* __restrict__ dw2t, float* __restrict__ part) {
-  adj_reserve();
-  constexpr int kSlots = KE + kCppnNodes;  // LDS sums per lane: in-edges, then positions
-  __shared__ float acc_all[kCppnWaves * kSlots * kWave];
-  const int lane = lane_id();
-  const int wave = wave_id();
-  const int W = blockDim.x / kWave;
-  const int g = blockIdx.x / n_chunks;
-  const int chunk = blockIdx.x - g * n_chunks;
-  float* out = part + ((int64_t)g * n_chunks * W + (int64_t)chunk * W + wave) * kCppnPart;
-  float* acc = acc_all + wave * kSlots * kWave + lane;  // slot i at acc[i * kWave]
+  rf_file_reserve();
+  extern __shared__ __align__(16) char cppn_lds[];
+  CppnLds& L = *reinterpret_cast<CppnLds*>(cppn_lds);
+  const int lane = lane_id(), wave = wave_id(), tid = threadIdx.x;
+  const int g = blockIdx.x / wg_per_g;
+  const int item = (blockIdx.x - g * wg_per_g) * kCppnWaves + wave;
   const int n = n_valid[g];
   const int64_t nb = uniform64(pop.node_base(g)), cb = uniform64(pop.conn_base(g)),
                 rb = uniform64(pop.rowptr_base(g));
-  const int32_t* rp = row_ptr + rb;
-  const int n_edges = n > 0 ? rp[n] : 0;
-  const int nio = pop.n_in + pop.n_out;
-  const int op = status[g] ? 0 : io_pos[(int64_t)g * nio + pop.n_in];
+  const int n_edges = n > 0 ? row_ptr[rb + n] : 0;
+  float* out = part + (int64_t)blockIdx.x * kCppnPart;
   bool ok = status[g] == 0 && n <= kCppnNodes && n_edges <= kCppnEdges;
-  for (int p = 0; ok && p < n; ++p) {
-    const int f = fn[nb + p];
+  if (ok) {
+    const int f = lane < n ? fn[nb + lane] : -1;
     const int agg = (f >> 8) & 0xff;
-    if (f >= 0 && agg != TN_AGG_SUM && agg != TN_AGG_MEAN) ok = false;
+    ok = !__ballot(f >= 0 && agg != TN_AGG_SUM && agg != TN_AGG_MEAN);
   }
   if (!ok) {
-    if (KE == kCppnEdges)
-      for (int i = lane; i < kCppnPart; i += kWave) out[i] = __builtin_nanf("");
+    for (int i = tid; i < kCppnPart; i += blockDim.x) out[i] = __builtin_nanf("");
     return;
   }
-  if ((n_edges <= kCppnCompactEdges) != (KE == kCppnCompactEdges)) return;  // the other form's
-  for (int i = 0; i < kSlots; ++i) acc[i * kWave] = 0.0f;
-  // the genome's program across the wavefront, read once: lane p holds
-  // position p's function word, bias, response and first in-edge (lane n the
-  // end of the last), lane e edge e's source position and weight; the sweeps
-  // below take every field with v_readlane instead of a memory load
-  const int l_fn = lane < n ? fn[nb + lane] : 0;
-  const int l_bias = lane < n ? bias_bits[nb + lane] : 0;
-  const int l_resp = lane < n ? resp_bits[nb + lane] : 0;
-  const int l_rp = lane <= n ? rp[lane] : 0;
-  const int l_src = lane < n_edges ? edge_src[cb + lane] : 0;
-  const int l_w = lane < n_edges ? w_bits[cb + lane] : 0;
-  const int Q1 = sg.S * sg.S, Q2 = sg.S * sg.n_out, Q = Q1 + Q2;
-  const int n_units = (Q + kCppnUnit - 1) / kCppnUnit;
-  const int u0 = (chunk * W + wave) * kCppnUnitsPerWave;
-  const int u1 = min(u0 + kCppnUnitsPerWave, n_units);
-  const int step_r = kWave / sg.grid, step_c = kWave - step_r * sg.grid;  // 64 = step_r grid + step_c
-  for (int u = u0; u < u1; ++u) {
-    const bool first = u * kCppnUnit < Q1;  // S*S is a multiple of 4096
-    const int base = first ? u * kCppnUnit : u * kCppnUnit - Q1;
-    // coordinates divided once for the first tile, stepped by 64 queries for
-    // the second (as in the query kernel)
-    float in[2][5], up[2];
-    int tgt = (base + lane) / sg.S;
-    int src = base + lane - tgt * sg.S;
-    int rs = src / sg.grid, cs = src - rs * sg.grid;
-    int rt = tgt / sg.grid, ct = tgt - rt * sg.grid;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int qq = base + k * kWave + lane;
-      in[k][0] = fmaf((float)cs, sg.step, -1.0f);
-      in[k][1] = fmaf((float)rs, sg.step, -1.0f);
-      if (first) {
-        in[k][2] = fmaf((float)ct, sg.step, -1.0f);
-        in[k][3] = fmaf((float)rt, sg.step, -1.0f);
-        up[k] = dw1t[(int64_t)g * Q1 + qq];
-      } else {
-        in[k][2] = sg.n_out > 1 ? fmaf((float)tgt, sg.ostep, -1.0f) : 0.0f;
-        in[k][3] = 0.0f;
-        up[k] = qq < Q2 ? dw2t[(int64_t)g * Q2 + qq] : 0.0f;
+  const CppnWave c = cppn_program<true>(
+      n, n_edges, row_ptr + rb, edge_src + cb, w_bits + cb, fn + nb, bias_bits + nb,
+      resp_bits + nb, io_pos + (int64_t)g * (pop.n_in + pop.n_out), kCppnSlots, L.edge);
+  const int rows = c.l_fn >= 0 ? sum_rows(c.l_edge >> 16) : 0;
+  const int row_end = wave_inclusive_scan(rows), l_sum = row_end - rows;
+  const int n_sums = __builtin_amdgcn_readlane(row_end, kWave - 1);
+  for (int r = 0; r < n_sums; ++r) L.acc[wave][r][lane] = 0.0f;
+  for (int i = tid; i < kCppnPart; i += blockDim.x) L.part[i] = 0.0f;
+  __syncthreads();
+  if (item < cppn_items(sg, run)) {
+    const CppnItem it = cppn_item(sg, run, item);
+    const int64_t Q1 = (int64_t)sg.S * sg.S, Q2 = (int64_t)sg.S * sg.n_out;
+    const float* up = (it.hidden ? dw1t + g * Q1 : dw2t + g * Q2) + (int64_t)it.t0 * sg.S + it.s0;
+    if (c.n_rows + 5 <= kRfFileRows / 4)
+      cppn_adjoint<4>(c, sg, it, l_sum, up, L.acc[wave], L.table[wave]);
+    else
+      cppn_adjoint<2>(c, sg, it, l_sum, up, L.acc[wave], L.table[wave]);
+  }
+  __syncthreads();
+  // each sum's 16 lanes over the wavefronts, in a fixed order; partial sums:
+  // in-edge e at e, position p at kCppnEdges + p
+  for (int p = 0; p < n; ++p) {
+    if (__builtin_amdgcn_readlane(c.l_fn, p) < 0) continue;
+    const int le = __builtin_amdgcn_readlane(c.l_edge, p);
+    const int r0 = __builtin_amdgcn_readlane(l_sum, p);
+    for (int i = tid; i <= (le >> 16); i += blockDim.x) {  // 0: the bias
+      const int quarter = sum_of_quarter(i & 3);
+      float total = 0.0f;
+      for (int w = 0; w < kCppnWaves; ++w) {
+        const float* from = L.acc[w][r0 + (i >> 2)] + quarter * 16;
+        float t = 0.0f;
+#pragma unroll 8
+        for (int b = 0; b < 16; ++b) t += from[b];
+        total += t;
       }
-      in[k][4] = 1.0f;
-      src += kWave;
-      rs += step_r;
-      cs += step_c;
-      if (cs >= sg.grid) {
-        cs -= sg.grid;
-        ++rs;
-      }
-      if (src >= sg.S) {
-        src -= sg.S;
-        rs -= sg.grid;
-        ++tgt;
-        if (++ct == sg.grid) {
-          ct = 0;
-          ++rt;
-        }
-      }
-    }
-    // forward, values and pre-activations by position
-    for (int p = 0; p < n; ++p) {
-      const int f = __builtin_amdgcn_readlane(l_fn, p);
-      if (f < 0) {
-        const int i = (f >> 16) & 0x7fff;
-        float x[2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-          x[k] = i == 0 ? in[k][0] : i == 1 ? in[k][1] : i == 2 ? in[k][2] : i == 3 ? in[k][3]
-                                                                                 : in[k][4];
-        adj_set_v(p, x[0], x[1]);
-        continue;
-      }
-      const int e0 = __builtin_amdgcn_readlane(l_rp, p), e1 = __builtin_amdgcn_readlane(l_rp, p + 1);
-      float s0 = 0.0f, s1 = 0.0f;
-      for (int e = e0; e < e1; ++e) {
-        const int j = __builtin_amdgcn_readlane(l_src, e);
-        adj_fma_v(s0, s1, __int_as_float(__builtin_amdgcn_readlane(l_w, e)), j);
-      }
-      if (((f >> 8) & 0xff) == TN_AGG_MEAN && e1 > e0) {
-        s0 = s0 / (float)(e1 - e0);
-        s1 = s1 / (float)(e1 - e0);
-      }
-      const float rho = __int_as_float(__builtin_amdgcn_readlane(l_resp, p));
-      const float bias = __int_as_float(__builtin_amdgcn_readlane(l_bias, p));
-      const float z[2] = {fmaf(rho, s0, bias), fmaf(rho, s1, bias)};
-      float v[2];
-      activate_all<2>(f & 7, z, v);  // codes below 7 (flagged genomes return above)
-      adj_set_vz(p, v[0], v[1], z[0], z[1]);
-    }
-    float y0, y1;
-    adj_get_v(op, y0, y1);
-    // NaN y: no gradient
-    adj_zero_g();
-    adj_set_g(op, fabsf(y0) >= sg.thr ? up[0] : 0.0f, fabsf(y1) >= sg.thr ? up[1] : 0.0f);
-    // reverse sweep
-    for (int p = n - 1; p >= 0; --p) {
-      const int f = __builtin_amdgcn_readlane(l_fn, p);
-      if (f < 0) continue;
-      float g0, g1, v0, v1, z0, z1;
-      adj_get_gvz(p, g0, g1, v0, v1, z0, z1);
-      const int act = f & 7;
-      const float d0 = g0 * cppn_slope(act, v0, z0), d1 = g1 * cppn_slope(act, v1, z1);
-      acc[(KE + p) * kWave] += d0 + d1;
-      const int e0 = __builtin_amdgcn_readlane(l_rp, p), e1 = __builtin_amdgcn_readlane(l_rp, p + 1);
-      const float rho = __int_as_float(__builtin_amdgcn_readlane(l_resp, p));
-      float dt0 = d0 * rho, dt1 = d1 * rho;
-      if (((f >> 8) & 0xff) == TN_AGG_MEAN && e1 > e0) {
-        dt0 = dt0 / (float)(e1 - e0);
-        dt1 = dt1 / (float)(e1 - e0);
-      }
-      // two in-edges per step (their sources differ, so the two updates of
-      // G are independent); the fields of both are read before either window
-      int e = e0;
-      for (; e + 1 < e1; e += 2) {
-        const float oa = acc[e * kWave], ob = acc[(e + 1) * kWave];  // loads issued first
-        const int ja = __builtin_amdgcn_readlane(l_src, e);
-        const int jb = __builtin_amdgcn_readlane(l_src, e + 1);
-        const float wa = __int_as_float(__builtin_amdgcn_readlane(l_w, e));
-        const float wb = __int_as_float(__builtin_amdgcn_readlane(l_w, e + 1));
-        float ta0, ta1, tb0, tb1;
-        adj_get_v(ja, ta0, ta1);
-        adj_get_v(jb, tb0, tb1);
-        adj_fma_g(ja, dt0, dt1, wa);
-        adj_fma_g(jb, dt0, dt1, wb);
-        acc[e * kWave] = oa + fmaf(dt1, ta1, dt0 * ta0);
-        acc[(e + 1) * kWave] = ob + fmaf(dt1, tb1, dt0 * tb0);
-      }
-      if (e < e1) {
-        const float o = acc[e * kWave];
-        const int j = __builtin_amdgcn_readlane(l_src, e);
-        float t0, t1;
-        adj_get_v(j, t0, t1);
-        adj_fma_g(j, dt0, dt1, __int_as_float(__builtin_amdgcn_readlane(l_w, e)));
-        acc[e * kWave] = o + fmaf(dt1, t1, dt0 * t0);
-      }
+      L.part[i ? (le & 0xffff) + i - 1 : kCppnEdges + p] = total;
     }
   }
-  // one reduction over the wavefront per sum, fixed order; partial slot
-  // layout: in-edge e at e, position p at kCppnEdges + p
-  for (int i = 0; i < kSlots; ++i) {
-    const float t = wave_sum(acc[i * kWave]);
-    if (lane == 0) out[i < KE ? i : kCppnEdges + (i - KE)] = t;
-  }
+  __syncthreads();
+  for (int i = tid; i < kCppnPart; i += blockDim.x) out[i] = L.part[i];
 }
 
-// Sums the wavefront partials of each genome in slot order and scatters them:
+// Sums the workgroups' partials of each genome in slot order and scatters them:
 // dW[connection row of in-edge e], db[node row of position p]; every other row
 // of the genome (disabled, padding, inputs) is 0; NaN where the partials are.
 __global__ __launch_bounds__(256) void cppn_grad_reduce_kernel(
@@ -991,6 +1334,25 @@ __global__ __launch_bounds__(256) void cppn_grad_reduce_kernel(
   }
 }
 
+// Targets per wavefront: the most (each wavefront pays for reading its genome
+// and for the fixed and target nodes) that still gives `waves` wavefronts.
+int cppn_run(int P, const SubGeom& sg, int most, int waves) {
+  int run = most;
+  while (run > 8 && (int64_t)P * cppn_items(sg, run) < waves) run /= 2;
+  return run;
+}
+
+SubGeom geometry(const tn_substrate& sub) {
+  SubGeom sg;
+  sg.grid = sub.grid;
+  sg.S = sub.grid * sub.grid;
+  sg.n_out = sub.n_out;
+  sg.thr = sub.threshold;
+  sg.step = 2.0f / (float)(sub.grid - 1);
+  sg.ostep = sub.n_out > 1 ? 2.0f / (float)(sub.n_out - 1) : 0.0f;
+  return sg;
+}
+
 }  // namespace
 
 int check_substrate(const tn_substrate* sub) {
@@ -1005,13 +1367,30 @@ int check_substrate(const tn_substrate* sub) {
 int launch_cppn_query(const tn_population& p, const tn_transformed& t, const tn_substrate& sub,
                       uint16_t* w1t, uint16_t* w2t, float* raw1, float* raw2,
                       hipStream_t stream) {
-  SubGeom sg;
-  sg.grid = sub.grid;
-  sg.S = sub.grid * sub.grid;
-  sg.n_out = sub.n_out;
-  sg.thr = sub.threshold;
-  sg.step = 2.0f / (float)(sub.grid - 1);
-  sg.ostep = sub.n_out > 1 ? 2.0f / (float)(sub.n_out - 1) : 0.0f;
+  const SubGeom sg = geometry(sub);
+  // Genomes of up to 20 positions run four tiles in a file of 80 rows, larger
+  // ones two, so populations of more than kMapRows node rows take the packed
+  // program (which reuses rows: four tiles for all) and evaluate every node at
+  // every pair: 30 CPPNs of 21 to 38 positions (N_max 40) on a 16 x 16 grid took
+  // 76 us there and 85 us here; with N_max 32 and 10 to 21 positions 45 and 44
+  // us, 100 of them on a 32 x 32 grid 1112 and 713 us.
+  if (p.N_max <= kMapRows) {
+    const int run = cppn_run(p.P, sg, kMapRun, kMapWavesWanted);
+    const int per_g = (cppn_items(sg, run) + kMapWaves - 1) / kMapWaves;
+    const int64_t blocks = (int64_t)p.P * per_g;
+    if (blocks == 0) return TN_OK;
+    if (blocks > 0x7fffffff) return TN_EUNSUPPORTED;
+    const size_t lds = sizeof(int2) * ((size_t)p.C_max + kWave);
+    const int rc = allow_lds((const void*)cppn_map_kernel, lds);
+    if (rc != TN_OK) return rc;
+    hipLaunchKernelGGL(cppn_map_kernel, dim3((unsigned)blocks), dim3(kWave * kMapWaves), lds,
+                       stream, make_view(p), t.status, t.prog_rows, t.n_valid, t.row_ptr,
+                       t.edge_src, reinterpret_cast<const int32_t*>(t.edge_w), t.pos_fn,
+                       reinterpret_cast<const int32_t*>(t.pos_bias),
+                       reinterpret_cast<const int32_t*>(t.pos_resp), t.io_pos, sg, run, per_g, w1t,
+                       w2t, raw1, raw2);
+    return check_launch();
+  }
   const int64_t Q = (int64_t)sg.S * sg.S + (int64_t)sg.S * sg.n_out;  // < 2^31 by check_substrate
   const int64_t unit = (int64_t)rf_tiles(kQueryRows) * kWave;
   const int64_t n_units = (Q + unit - 1) / unit;
@@ -1119,49 +1498,38 @@ int launch_substrate_backward(const tn_substrate& sub, int P, const uint16_t* w2
 }
 
 namespace {
-int cppn_chunks(const tn_substrate& sub) {
-  const int64_t S = (int64_t)sub.grid * sub.grid;
-  const int64_t n_units = (S * S + S * sub.n_out + kCppnUnit - 1) / kCppnUnit;
-  const int64_t per_wg = (int64_t)kCppnWaves * kCppnUnitsPerWave;
-  return (int)((n_units + per_wg - 1) / per_wg);
+int adjoint_run(int P, const SubGeom& sg) { return cppn_run(P, sg, kCppnRun, kCppnWavesWanted); }
+int adjoint_workgroups(int P, const SubGeom& sg) {  // of a genome
+  return (cppn_items(sg, adjoint_run(P, sg)) + kCppnWaves - 1) / kCppnWaves;
 }
 }  // namespace
 
 size_t cppn_backward_workspace_bytes(const tn_population& p, const tn_substrate& sub) {
-  return sizeof(float) * (size_t)p.P * cppn_chunks(sub) * kCppnWaves * kCppnPart;
+  return sizeof(float) * (size_t)p.P * adjoint_workgroups(p.P, geometry(sub)) * kCppnPart;
 }
 
 int launch_cppn_backward(const tn_population& p, const tn_transformed& t, const tn_substrate& sub,
                          const float* dw1t, const float* dw2t, void* workspace, float* dW,
                          float* db, hipStream_t stream) {
-  SubGeom sg;
-  sg.grid = sub.grid;
-  sg.S = sub.grid * sub.grid;
-  sg.n_out = sub.n_out;
-  sg.thr = sub.threshold;
-  sg.step = 2.0f / (float)(sub.grid - 1);
-  sg.ostep = sub.n_out > 1 ? 2.0f / (float)(sub.n_out - 1) : 0.0f;
-  const int n_chunks = cppn_chunks(sub);
-  const int64_t grid = (int64_t)p.P * n_chunks;
+  const SubGeom sg = geometry(sub);
+  const int per_g = adjoint_workgroups(p.P, sg);
+  const int64_t grid = (int64_t)p.P * per_g;
   if (grid == 0) return TN_OK;
   if (grid > 0x7fffffff) return TN_EUNSUPPORTED;
   float* part = static_cast<float*>(workspace);
-  int rc = TN_OK;
-#define TN_CPPN_BWD(KE)                                                                        \
-  hipLaunchKernelGGL(cppn_backward_kernel<KE>, dim3((unsigned)grid), dim3(kWave * kCppnWaves), \
-                     0, stream, make_view(p), t.status, t.n_valid, t.row_ptr, t.edge_src,      \
-                     reinterpret_cast<const int32_t*>(t.edge_w), t.pos_fn,                    \
-                     reinterpret_cast<const int32_t*>(t.pos_bias),                            \
-                     reinterpret_cast<const int32_t*>(t.pos_resp), t.io_pos, sg, n_chunks,    \
-                     dw1t, dw2t, part);                                                       \
-  rc = check_launch();                                                                        \
+  int rc = allow_lds((const void*)cppn_backward_kernel, sizeof(CppnLds));
   if (rc != TN_OK) return rc;
-  TN_CPPN_BWD(kCppnCompactEdges)
-  TN_CPPN_BWD(kCppnEdges)
-#undef TN_CPPN_BWD
+  hipLaunchKernelGGL(cppn_backward_kernel, dim3((unsigned)grid), dim3(kWave * kCppnWaves),
+                     sizeof(CppnLds), stream, make_view(p), t.status, t.n_valid, t.row_ptr,
+                     t.edge_src, reinterpret_cast<const int32_t*>(t.edge_w), t.pos_fn,
+                     reinterpret_cast<const int32_t*>(t.pos_bias),
+                     reinterpret_cast<const int32_t*>(t.pos_resp), t.io_pos, sg, adjoint_run(p.P, sg), per_g,
+                     dw1t, dw2t, part);
+  rc = check_launch();
+  if (rc != TN_OK) return rc;
   hipLaunchKernelGGL(cppn_grad_reduce_kernel, dim3((unsigned)p.P), dim3(256), 0, stream,
                      make_view(p), t.n_valid, t.row_ptr, t.edge_row, t.order, t.pos_fn, part,
-                     n_chunks * kCppnWaves, dW, db);
+                     per_g, dW, db);
   return check_launch();
 }
 

@@ -31,6 +31,7 @@ import torch
 import oracle
 import synth
 from gpu_util import host, to_device
+from helpers import population_from_rows
 from oracle import hyperneat as hn
 
 pytestmark = pytest.mark.gpu
@@ -392,6 +393,99 @@ def test_cppn_backward_both_slot_forms_and_edge_limit():
         assert np.isnan(dW[g]).all() and np.isnan(db[g]).all()
     _check_cppn_grads(pop, grid, n_out, raws, u1, u2, dW, db,
                       [g for g in range(pop.P) if edges[g] <= 64])
+
+
+def _walk_genomes(rng, aggs):
+    """CPPNs around the limits of the walk over sources and targets. Nodes are
+    (sources, activation): 's' the source's coordinates, 't' the target's, 'o'
+    the constant input, a number an earlier node."""
+    tanh, sin = 2, 4
+    specs = [
+        [("st", tanh)],
+        [("s", sin)],                                         # one value per source
+        [("t", sin)], [("o", tanh)], [("", sin)],             # per target; constants
+        [("s", 5), ("t", 6), ([0, 1], tanh)],
+        [("t", sin)] + [([k], (sin, tanh, 5, 6)[k % 4]) for k in range(16)] + [(["s", 3, 16], tanh)],
+        [("s", sin), ([0], 5), ("o", 1), ("t", sin), ([1, 2, 3], sin), ("st", 0), ([4, 5], 3)],
+    ]
+    for n_tanh, n_sin in ((13, 2), (14, 2), (20, 1), (22, 0), (9, 18)):   # 20, 21 positions; 48, 49 rows; 32
+        specs.append([(("st", "s", "t", "o")[k % 4] if k < 6 else
+                       [k - 1, k - 4, k - 6][:2 if n_sin > 9 else 3], sin if k < n_sin else tanh) for k in range(n_tanh + n_sin)])
+    genomes = []
+    for g, spec in enumerate(specs):
+        keys = list(range(6, 5 + len(spec))) + [5]
+        nodes = [[k, 0.0, 1.0, 0, 0] for k in range(5)]
+        conns = []
+        for i, (srcs, act) in enumerate(spec):
+            nodes.append([keys[i], float(rng.normal() * 0.3), float(rng.choice([1.0, 0.75])), act,
+                          aggs[(g + i) % len(aggs)]])
+            for s in srcs:
+                for q in ({"s": (0, 1), "t": (2, 3), "o": (4,)}[s] if isinstance(s, str) else (keys[s],)):
+                    conns.append([q, keys[i], float(rng.normal()), 1])
+        nodes.sort()
+        genomes.append((nodes, conns + [[4, keys[0], 1.0, 0]] if spec[0][0] != "o" else conns))
+    return genomes
+
+
+@pytest.mark.parametrize("aggs", [(0,), (0, 1, 2, 3, 4, 5)])
+@pytest.mark.parametrize("grid,n_out", [(8, 130), (16, 1), (24, 7)])
+def test_query_walk_equals_the_packed_program(grid, n_out, aggs):
+    """Populations of 32 node rows (the walk over sources and targets), padded
+    and ragged, give the bits of the same genomes in 33 rows (the packed
+    program), with a flagged genome among them; where a mean may round a term
+    once instead of twice, values of size 1 agree to 1e-5."""
+    import paper_2504_08339_amd as tn
+    rng = np.random.default_rng(grid + n_out)
+    genomes = _walk_genomes(rng, aggs)
+    genomes.append((genomes[0][0] + [[6, 0.0, 1.0, 2, 0]],
+                    [[5, 6, 1.0, 1], [6, 5, 1.0, 1], [0, 6, 1.0, 1]]))    # a cycle
+    pop = population_from_rows(genomes, 5, 1)
+    assert pop.N_max == 32
+    rag = synth.to_ragged(pop)
+    out = []
+    for p in (synth.to_padded(rag, N_max=33, C_max=pop.C_max), pop, rag):
+        dp = to_device(p)
+        tr = tn.transform(dp)
+        assert list(np.flatnonzero(host(tr.status)[:p.P])) == [p.P - 1]
+        w1t, w2t, r1, r2 = tn.cppn_query(dp, tr, grid, n_out, THR, raw=True)
+        out.append((_bits16(w1t), _bits16(w2t), host(r1), host(r2)))
+    for w1, w2, r1, r2 in out[1:]:
+        assert np.isnan(r1[-1]).all() and np.isnan(r2[-1]).all() and (w1[-1] == 0x7FC0).all()
+        if aggs == (0,):
+            assert np.array_equal(w1, out[0][0]) and np.array_equal(w2, out[0][1])
+            assert np.array_equal(r1.view(np.uint32), out[0][2].view(np.uint32))
+            assert np.array_equal(r2.view(np.uint32), out[0][3].view(np.uint32))
+        else:
+            np.testing.assert_allclose(r1, out[0][2], rtol=1e-5, atol=1e-5)
+            np.testing.assert_allclose(r2, out[0][3], rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("grid,n_out", [(8, 70), (16, 3)])
+def test_cppn_backward_walk(grid, n_out):
+    """The adjoint of the same genomes (both register files, nodes of one value
+    per source or target, more target nodes than the table holds) against the
+    oracle."""
+    import paper_2504_08339_amd as tn
+    rng = np.random.default_rng(grid)
+    pop = population_from_rows(_walk_genomes(rng, (0,)), 5, 1)
+    dp = to_device(pop)
+    tr = tn.transform(dp)
+    S = grid * grid
+    u1 = rng.standard_normal((pop.P, S, S)).astype(np.float32)
+    u2 = rng.standard_normal((pop.P, n_out, S)).astype(np.float32)
+    src, outs = hn.grid_coords(grid), hn.row_coords(n_out)
+    raws = []
+    for g in range(pop.P):
+        gen = oracle.decode(pop, g)
+        otr = oracle.transform(gen)
+        r1, a1 = _oracle_raw(gen, otr, src, src)
+        r2, a2 = _oracle_raw(gen, otr, src, outs)
+        u1[g][a1.T] = 0.0
+        u2[g][a2.T] = 0.0
+        raws.append((r1, r2))
+    dW, db = tn.cppn_backward(dp, tr, torch.from_numpy(u1).cuda(), torch.from_numpy(u2).cuda(),
+                              grid, n_out, THR)
+    _check_cppn_grads(pop, grid, n_out, raws, u1, u2, host(dW), host(db), range(pop.P))
 
 
 def test_cppn_backward_through_the_substrate():
