@@ -54,7 +54,8 @@ inline size_t gene_list_bytes(int P, int cap) {
   return gene_align(sizeof(long long) * n) + 4 * gene_align(4 * n);
 }
 
-inline GeneList carve_list(unsigned char* p, size_t& o, int P, int cap) {
+// p: the workspace's address (0 to find its size, so no pointer arithmetic).
+inline GeneList carve_list(uintptr_t p, size_t& o, int P, int cap) {
   const size_t n = (size_t)P * cap;
   GeneList l;
   l.keyT = (long long*)(p + o);
@@ -75,7 +76,7 @@ inline size_t ws_nodes_bytes(int P, int N, int C) {
 }
 
 inline WsN carve_nodes(void* base, int P, int N, int C) {
-  unsigned char* p = (unsigned char*)base;
+  const uintptr_t p = (uintptr_t)base;
   size_t o = 0;
   WsN w;
   w.cnt_n = (int32_t*)(p + o);

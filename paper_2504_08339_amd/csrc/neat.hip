@@ -80,14 +80,14 @@ struct Table {
   tn_population_arrays reps;
 };
 
-// Carves the workspace at `base`; *bytes (may be null): its size.
+// Carves the workspace at `base` (null: its size alone); *bytes (may be null): its size.
 NeatWs carve(void* base, int P, int S, int N, int C, size_t* bytes) {
-  unsigned char* p = (unsigned char*)base;
+  const uintptr_t p = (uintptr_t)base;
   size_t o = 0;
   NeatWs w;
-  w.pop = carve_nodes(p + o, P, N, C);
+  w.pop = carve_nodes((void*)(p + o), P, N, C);
   o += ws_nodes_bytes(P, N, C);
-  w.reps = carve_nodes(p + o, S, N, C);
+  w.reps = carve_nodes((void*)(p + o), S, N, C);
   o += ws_nodes_bytes(S, N, C);
   auto ints = [&](size_t n) {
     int32_t* q = (int32_t*)(p + o);
@@ -110,7 +110,7 @@ NeatWs carve(void* base, int P, int S, int N, int C, size_t* bytes) {
   w.ssum = (float*)ints(S + 1);
   w.best = (float*)ints(S + 1);
   w.last = ints(S + 1);
-  w.repro = p + o;
+  w.repro = (void*)(p + o);
   if (bytes) *bytes = o + gene_align(reproduce_workspace_bytes(P));
   return w;
 }
