@@ -11,10 +11,9 @@ import os
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libtnhip.so")
 
-c_int32_p = ctypes.POINTER(ctypes.c_int32)
-c_int64_p = ctypes.POINTER(ctypes.c_int64)
-c_float_p = ctypes.POINTER(ctypes.c_float)
-c_uint8_p = ctypes.POINTER(ctypes.c_uint8)
+# Addresses of arrays of these types. All are void pointers to ctypes, so an
+# integer address passes as it is.
+c_int32_p = c_int64_p = c_float_p = c_uint8_p = ctypes.c_void_p
 
 TN_OK, TN_EINVAL, TN_ESHAPE, TN_EUNSUPPORTED, TN_EHIP, TN_ENOMEM = range(6)
 TN_MAX_NODES, TN_MAX_CONNS, TN_MAX_IO = 1024, 4096, 1024
