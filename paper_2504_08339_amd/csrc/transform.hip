@@ -6,7 +6,7 @@
 // genomes: every loop over node rows, connection rows, positions and edges is
 // split over the workgroup's threads); everything for the genome lives in LDS:
 //   1. node keys -> rows through an open-addressing hash (duplicate keys flagged)
-//   2. connection markings (in-key, out-key) through a 64-bit hash (duplicates
+//   2. connection markings (in-key, out-key) through a hash of rows (duplicates
 //      flagged), enabled rows resolved to (source row, destination row)
 //   3. level-synchronous Kahn sort: each round marks the node rows whose
 //      remaining in-degree is 0, places them in ascending row order (a prefix
@@ -32,8 +32,9 @@ namespace tn {
 
 namespace {
 
+static_assert(TN_MAX_CONNS <= 1 << 12, "a marking entry holds a row in 12 bits");
 constexpr int32_t kEmptyKey = -1;
-constexpr unsigned long long kEmptyMark = ~0ull;
+constexpr uint32_t kEmptyMark = ~0u;
 
 __device__ __forceinline__ uint32_t hash32(uint32_t k) {
   // lowbias32 (Chris Wellons' integer hash constants)
@@ -49,24 +50,27 @@ __device__ __forceinline__ uint32_t hash64(unsigned long long k) {
   return hash32((uint32_t)k ^ hash32((uint32_t)(k >> 32)));
 }
 
+// Slot of a hash in a table of any size: the tables are as large as their load
+// allows, since the LDS of the largest genomes decides how many fit a compute
+// unit (535 nodes, 1894 connections: three workgroups; one with tables of powers
+// of two and 64-bit markings. 10,000 uneven genomes, transformation and plan:
+// 1316 us, 1399 before).
+__device__ __forceinline__ int hash_slot(uint32_t h, int size) {
+  return (int)__umulhi(h, (uint32_t)size);
+}
+
 struct Layout {
   // genomes this launch takes: node rows <= n_cap and connection rows <= c_cap,
   // and not both within (n_prev, c_prev) (an earlier launch's); the launch
   // with the population's capacities also takes the oversize genomes
   int n_cap, c_cap, n_prev, c_prev;
   bool last;
-  int HN, HC;              // hash table sizes (powers of two)
+  int HN, HC;              // hash table sizes
   int off_hkey, off_hslot, off_nkey, off_deg, off_rem, off_outdeg, off_pos,
       off_order, off_level, off_ptr, off_cursor, off_outlist, off_esrc, off_edst,
       off_tmp, off_chash, off_csr_row, off_lstart;
   size_t bytes;
 };
-
-int next_pow2(int x) {
-  int p = 1;
-  while (p < x) p <<= 1;
-  return p;
-}
 
 Layout make_layout(int N, int C) {
   Layout L;
@@ -74,16 +78,16 @@ Layout make_layout(int N, int C) {
   L.c_cap = C;
   L.n_prev = L.c_prev = -1;
   L.last = true;
-  L.HN = next_pow2(2 * N);
-  L.HC = next_pow2(C + C / 4 + 1);  // marking hash at most 80 % full
+  L.HN = N + N / 2 + 1;  // at most two thirds full
+  L.HC = C + C / 4 + 1;  // marking hash at most 80 % full
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
     o += (bytes + 15) & ~size_t(15);
     return (int)at;
   };
-  // 8-byte aligned first; reused for the free-event list of step 9b
-  L.off_chash = take(std::max(sizeof(unsigned long long) * L.HC, sizeof(int16_t) * (2 * N + C)));
+  // reused for the free-event list of step 9b
+  L.off_chash = take(std::max(sizeof(uint32_t) * L.HC, sizeof(int16_t) * (2 * N + C)));
   L.off_hkey = take(sizeof(int32_t) * L.HN);
   L.off_hslot = take(sizeof(int16_t) * L.HN);
   L.off_nkey = take(sizeof(int32_t) * N);
@@ -107,12 +111,12 @@ Layout make_layout(int N, int C) {
 
 __device__ int lookup_node(const int32_t* hkey, const int16_t* hslot, int HN, int32_t k) {
   if (k < 0) return -1;
-  uint32_t h = hash32((uint32_t)k) & (uint32_t)(HN - 1);
+  int h = hash_slot(hash32((uint32_t)k), HN);
   while (true) {
     int32_t kk = hkey[h];
     if (kk == k) return hslot[h];
     if (kk == kEmptyKey) return -1;
-    h = (h + 1) & (uint32_t)(HN - 1);
+    h = h + 1 == HN ? 0 : h + 1;
   }
 }
 
@@ -267,7 +271,7 @@ __global__ __launch_bounds__(kWave * kW) void transform_kernel(PopView pop, TrVi
   }
   const int nrows = (int)nrows64, crows = (int)crows64;
 
-  unsigned long long* chash = (unsigned long long*)(smem + L.off_chash);
+  uint32_t* chash = (uint32_t*)(smem + L.off_chash);
   int32_t* hkey = (int32_t*)(smem + L.off_hkey);
   int16_t* hslot = (int16_t*)(smem + L.off_hslot);
   int32_t* nkey = (int32_t*)(smem + L.off_nkey);
@@ -307,7 +311,7 @@ __global__ __launch_bounds__(kWave * kW) void transform_kernel(PopView pop, TrVi
     ++my_valid;
     if (pop.node_act[nb + r] > TN_ACT_ABS || pop.node_agg[nb + r] > TN_AGG_MAXABS)
       atomicOr(&flags, TN_BAD_ATTR);
-    uint32_t h = hash32((uint32_t)k) & (uint32_t)(L.HN - 1);
+    int h = hash_slot(hash32((uint32_t)k), L.HN);
     while (true) {
       const int32_t old = atomicCAS(&hkey[h], kEmptyKey, k);
       if (old == kEmptyKey) {
@@ -318,7 +322,7 @@ __global__ __launch_bounds__(kWave * kW) void transform_kernel(PopView pop, TrVi
         atomicOr(&flags, TN_DUP_NODE);
         break;
       }
-      h = (h + 1) & (uint32_t)(L.HN - 1);
+      h = h + 1 == L.HN ? 0 : h + 1;
     }
   }
   int n_valid;
@@ -337,15 +341,22 @@ __global__ __launch_bounds__(kWave * kW) void transform_kernel(PopView pop, TrVi
     int16_t s = -1, d = -1;
     if (a >= 0 && b >= 0) {
       const unsigned long long mark = ((unsigned long long)(uint32_t)a << 32) | (uint32_t)b;
-      uint32_t h = hash64(mark) & (uint32_t)(L.HC - 1);
+      // an entry is 19 bits of the hash and the row: keys are compared only
+      // where those bits agree
+      const uint32_t hash = hash64(mark);
+      const uint32_t entry = ((hash & 0x7ffffu) << 12) | (uint32_t)r;
+      int h = hash_slot(hash, L.HC);
       while (true) {
-        const unsigned long long old = atomicCAS(&chash[h], kEmptyMark, mark);
+        const uint32_t old = atomicCAS(&chash[h], kEmptyMark, entry);
         if (old == kEmptyMark) break;
-        if (old == mark) {
-          atomicOr(&flags, TN_DUP_CONN);
-          break;
+        if (((old ^ entry) >> 12) == 0) {
+          const int q = (int)(old & 0xfffu);
+          if (pop.conn_in[cb + q] == a && pop.conn_out[cb + q] == b) {
+            atomicOr(&flags, TN_DUP_CONN);
+            break;
+          }
         }
-        h = (h + 1) & (uint32_t)(L.HC - 1);
+        h = h + 1 == L.HC ? 0 : h + 1;
       }
       if (pop.conn_en[cb + r]) {
         const int sa = lookup_node(hkey, hslot, L.HN, a);
