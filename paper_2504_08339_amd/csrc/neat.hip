@@ -421,52 +421,77 @@ __global__ __launch_bounds__(kBlock) void settle_kernel(NeatWs ws, Table t, Spec
 }
 
 // Members, largest and smallest fitness (the first of equal ones) and the sum
-// in ascending genome order of slot blockIdx.x: the sum is one serial chain,
-// taken 64 genomes at a time from the lanes (0 for the others: no bit of a sum
-// that starts at +0 changes).
-__global__ __launch_bounds__(kWave) void stats_kernel(NeatWs ws, const float* fit, int P) {
-  const int s = blockIdx.x, lane = threadIdx.x;
-  constexpr int kAhead = 4;  // chunks of 64 genomes in flight
-  int n = 0, imx = INT_MAX, imn = INT_MAX;
+// in ascending genome order of slot blockIdx.x. The sum is one serial chain: the
+// workgroup first packs a segment's members into LDS in genome order (counts of
+// all its chunks in one prefix sum), then a wavefront adds them 16 reads ahead.
+// 5000 genomes, 10 species: 23 us; 69 us by one wavefront that took the chain
+// over all genomes, members or not, from its lanes.
+constexpr int kStatsWaves = 4, kStatsChunks = kWave / kStatsWaves;
+constexpr int kStatsSegment = kStatsChunks * kStatsWaves * kWave;
+
+__global__ __launch_bounds__(kWave * kStatsWaves) void stats_kernel(NeatWs ws, const float* fit,
+                                                                    int P) {
+  constexpr int T = kWave * kStatsWaves;
+  __shared__ __align__(16) float member[kStatsSegment];
+  __shared__ int start[kWave];  // of a wavefront's part of a chunk: [chunk][wavefront]
+  __shared__ float wmx[kStatsWaves], wmn[kStatsWaves];
+  __shared__ int wimx[kStatsWaves], wimn[kStatsWaves];
+  const int s = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+  int total = 0, imx = INT_MAX, imn = INT_MAX;
   float mx = -INFINITY, mn = INFINITY, sum = 0.0f;
-  for (int base = 0; base < P; base += kAhead * kWave) {
-    bool in[kAhead];
-    float f[kAhead];
+  for (int base = 0; base < P; base += kStatsSegment) {
+    float f[kStatsChunks];
+    uint64_t in[kStatsChunks];
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const int g = base + u * kWave + lane;
-      in[u] = g < P && ws.sp[g] == s;
-      f[u] = g < P ? fit[g] : 0.0f;
+    for (int u = 0; u < kStatsChunks; ++u) {
+      const int g = base + u * T + tid, gg = min(g, P - 1);
+      const int sp = ws.sp[gg];
+      f[u] = fit[gg];
+      in[u] = __ballot(g < P && sp == s);
     }
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const uint64_t m = __ballot(in[u]);
-      if (m == 0) continue;
-      const int g = base + u * kWave + lane;
-      if (in[u] && f[u] > mx) {
-        mx = f[u];
-        imx = g;
+    for (int u = 0; u < kStatsChunks; ++u) {
+      if ((in[u] >> lane) & 1) {
+        const int g = base + u * T + tid;
+        if (f[u] > mx) {
+          mx = f[u];
+          imx = g;
+        }
+        if (f[u] < mn) {
+          mn = f[u];
+          imn = g;
+        }
       }
-      if (in[u] && f[u] < mn) {
-        mn = f[u];
-        imn = g;
-      }
-      n += __popcll(m);
-      const float v = in[u] ? f[u] : 0.0f;
-      if (__popcll(m) <= 20) {
-        for (uint64_t x = m; x; x &= x - 1)
-          sum = sum + __shfl(v, __ffsll((unsigned long long)x) - 1, kWave);
-      } else {
-#pragma unroll
-        for (int l = 0; l < kWave; ++l)
-          sum = sum + __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-      }
+      if (lane == 0) start[u * kStatsWaves + wave] = __popcll(in[u]);
     }
+    lds_barrier();
+    const int count = start[lane];
+    const int upto = wave_inclusive_scan(count);
+    const int n = __builtin_amdgcn_readlane(upto, kWave - 1);
+    const int mine = upto - count;
+#pragma unroll
+    for (int u = 0; u < kStatsChunks; ++u) {
+      const int at = __builtin_amdgcn_readlane(mine, u * kStatsWaves + wave);
+      if ((in[u] >> lane) & 1) member[at + mbcnt(in[u])] = f[u];
+    }
+    lds_barrier();
+    total += n;
+    if (wave == 0) {  // one chain of additions in genome order
+      int i = 0;
+      for (; i + 16 <= n; i += 16) {
+        float v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = member[i + k];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) sum = sum + v[k];
+      }
+      for (; i < n; ++i) sum = sum + member[i];
+    }
+    lds_barrier();  // the next segment overwrites the members
   }
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) {
-    const float omx = __shfl_xor(mx, off, kWave), omn = __shfl_xor(mn, off, kWave);
-    const int oimx = __shfl_xor(imx, off, kWave), oimn = __shfl_xor(imn, off, kWave);
+  // the larger maximum and the smaller minimum, of equal ones the earlier genome's
+  auto take = [](float& mx, int& imx, float& mn, int& imn, float omx, int oimx, float omn,
+                 int oimn) {
     if (omx > mx || (omx == mx && oimx < imx)) {
       mx = omx;
       imx = oimx;
@@ -475,9 +500,22 @@ __global__ __launch_bounds__(kWave) void stats_kernel(NeatWs ws, const float* fi
       mn = omn;
       imn = oimn;
     }
+  };
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    take(mx, imx, mn, imn, __shfl_xor(mx, off, kWave), __shfl_xor(imx, off, kWave),
+         __shfl_xor(mn, off, kWave), __shfl_xor(imn, off, kWave));
   }
   if (lane == 0) {
-    ws.nmem[s] = n;
+    wmx[wave] = mx;
+    wmn[wave] = mn;
+    wimx[wave] = imx;
+    wimn[wave] = imn;
+  }
+  lds_barrier();
+  if (tid == 0) {
+    for (int w = 1; w < kStatsWaves; ++w) take(mx, imx, mn, imn, wmx[w], wimx[w], wmn[w], wimn[w]);
+    ws.nmem[s] = total;
     ws.smax[s] = mx;
     ws.smin[s] = mn;
     ws.ssum[s] = sum;
@@ -775,7 +813,7 @@ int launch_neat_generation(const tn_population& p, const float* fit, int gen,
   hipLaunchKernelGGL(settle_kernel, dim3(blocks), dim3(kBlock), 0, stream, ws, t, a, species_of);
   rc = check_launch();
   if (rc != TN_OK) return rc;
-  hipLaunchKernelGGL(stats_kernel, dim3(S), dim3(kWave), 0, stream, ws, fit, P);
+  hipLaunchKernelGGL(stats_kernel, dim3(S), dim3(kWave * kStatsWaves), 0, stream, ws, fit, P);
   rc = check_launch();
   if (rc != TN_OK) return rc;
   hipLaunchKernelGGL(counts_kernel, dim3(1), dim3(kWave), 0, stream, ws, t, a);

@@ -127,6 +127,15 @@ def test_founding_rounds_at_the_edges(P):
     assert P < 16 or len(seen) == 5
 
 
+@pytest.mark.parametrize("P", [64, 257, 4096, 4097])
+def test_species_sums_at_the_segment_edges(P):
+    """Fitness sums of two large species, taken in segments of 4096 genomes:
+    the offspring counts and parents they lead to are the oracle's."""
+    prm = on.NeatParams(compatibility_threshold=0.9, max_species=2,
+                        mutation=orp.MutationParams(act_default=1, node_add=0.4, conn_add=0.6))
+    _chain(P, prm, 1, seed=P)
+
+
 def test_gpu_loop_on_xor_improves():
     """The loop with the fitness on the GPU (tn_forward_loss: 4 - SSE over the
     four XOR rows): every generation's parents are valid, the best fitness
