@@ -21,7 +21,6 @@ namespace tn {
 
 namespace {
 
-constexpr long long kPadKey = 0x7fffffffffffffffll;
 
 __device__ __forceinline__ uint32_t mix32(uint32_t k) {
   // lowbias32 (Chris Wellons' integer hash constants)
@@ -120,34 +119,8 @@ __global__ __launch_bounds__(kPrepGenomes * kWave) void prep_kernel(PopView pop,
       }
       n += __popcll(m);
     }
-    for (int i = n + lane; i < S; i += kWave) {
-      key[i] = kPadKey;
-      w[i] = 0.0f;
-    }
     wave_sync();
-    // bitonic sort of S entries (S is a power of two)
-    for (int k = 2; k <= S; k <<= 1) {
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        for (int i = lane; i < S; i += kWave) {
-          const int ixj = i ^ j;
-          if (ixj > i) {
-            const long long ki = key[i], kj = key[ixj];
-            const bool up = (i & k) == 0;
-            if ((ki > kj) == up) {
-              key[i] = kj;
-              key[ixj] = ki;
-              const float t = w[i];
-              w[i] = w[ixj];
-              w[ixj] = t;
-            }
-          }
-        }
-        wave_sync();
-      }
-    }
-    bool dup = !fits;
-    for (int i = lane + 1; i < n; i += kWave) dup |= key[i] == key[i - 1];
-    const bool bad = __ballot(dup) != 0;
+    const bool bad = wave_sort(key, reinterpret_cast<int32_t*>(w), n, S) || !fits;
     if (lane == 0) {
       ws.cnt[g] = bad ? -1 : n;
       ws.maxk[g] = n > 0 ? key[n - 1] : -1;

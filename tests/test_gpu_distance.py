@@ -87,6 +87,27 @@ def test_edge_cases():
     assert np.isnan(d[4]).all() and (E[4] == -1).all()
 
 
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 256, 257])
+def test_list_lengths_at_the_sort_edges(n):
+    """Lists of n connections in random row order (the counting sort up to 256,
+    the bitonic one above), some disabled, with holes, and one list that
+    repeats a marking."""
+    rng = np.random.default_rng(n)
+    genomes = []
+    for g in range(6):
+        marks = rng.choice(40 * 40, size=n, replace=False)
+        rows = [[int(m) // 40, int(m) % 40, float(rng.normal()), int(rng.random() < 0.8)]
+                for m in marks]
+        rows.insert(int(rng.integers(0, n + 1)), None)
+        if g == 5 and n > 1:
+            rows[rows.index(None)] = [rows[-1][0], rows[-1][1], 1.0, 1] if rows[-1] else rows[0]
+        genomes.append(([[0, 0, 1, 0, 0]], rows))
+    pop = population_from_rows(genomes, 0, 1)
+    d, E, D = gpu_distance(pop)
+    check_pairs(pop, d, E, D, [(i, j) for i in range(pop.P) for j in range(pop.P)])
+    assert np.isnan(d[5]).all() == (n > 1)
+
+
 def test_ragged_uneven():
     pop = synth.batching_population(P=70)
     d, E, D = gpu_distance(pop)
