@@ -588,6 +588,33 @@ __device__ __forceinline__ void store_global(float* q, float v) {
   *(__attribute__((address_space(1))) float*)q = v;
 }
 
+// Stores a wavefront's 64 x 64 quarter of C. The fragment of D = C^T holds rows
+// 4 (lane / 16) + e, column lane % 16: C row row0 (+ 16 i), columns col0 (+ 16 j)
+// + e.
+template <bool kTanh>
+__device__ __forceinline__ void store_tile(const GemmArgs& p, const f32x4 (&acc)[4][4], float* C,
+                                           int row0, int col0) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int row = row0 + 16 * i, col = col0 + 16 * j;
+      if (row >= p.M) continue;
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = kTanh ? act_tanh(acc[i][j][e]) : acc[i][j][e];
+      float* q = C + (int64_t)row * p.ldc + col;
+      if (col + 3 < p.N && (p.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0) {
+        f32x4 w = {v[0], v[1], v[2], v[3]};
+        *(__attribute__((address_space(1))) f32x4*)q = w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (col + e < p.N) store_global(q + e, v[e]);
+      }
+    }
+}
+
 template <bool kTanh>
 __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs p) {
   extern __shared__ __align__(16) uint16_t gemm_lds[];
@@ -674,29 +701,101 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs p) {
     if (more) stash(buf ^ 1, rg);
     __syncthreads();
   }
-  float* C = p.c + (int64_t)g * p.c_batch;
+  store_tile<kTanh>(p, acc, p.c + (int64_t)g * p.c_batch, m0 + wm + li, n0 + wn + (lane >> 4) * 4);
+}
+
+// The same product with operands that are 16-byte aligned in every row: stages
+// of 32 k (16 KB) arrive by LDS-direct loads, kRing buffers deep, so four
+// stages per workgroup are in flight without a register (gemm_nt_kernel: one,
+// in registers). A row's 64 bytes of a stage are four lanes' loads, and a
+// fragment read of a wavefront then is 1 KB of consecutive LDS: no bank
+// conflicts, no padding. One barrier per stage: it tells that every
+// wavefront's part of stage st has landed and that stage st - 1 is no longer
+// read, so stage st + 4 takes its buffer. Rows past M and N read the last row
+// and are not stored. Bound by memory: 200 genomes, 128 x 1024 x 1024 (577 MB)
+// 165 us, 177 us by gemm_nt_kernel. Runs of columns instead of tiles (1600 tiles
+// make 3.1 rounds of 512 workgroups) measured 184 us, stages in an order of
+// their own per workgroup 167. The order of the sums is gemm_nt_kernel's.
+constexpr int kRing = 5, kRingKs = 32;
+constexpr int kRingBytes = kGemmTile * kRingKs * 2;  // one operand of a stage
+constexpr size_t kRingLds = (size_t)kRing * 2 * kRingBytes;
+
+template <bool kTanh>
+__global__ __launch_bounds__(256, 2) void gemm_ring_kernel(GemmArgs p) {
+  extern __shared__ __align__(16) uint16_t gemm_lds[];
+  const int lane = lane_id(), wave = wave_id();
+  const int64_t item = gemm_item(blockIdx.x, gridDim.x);
+  const int per_g = p.m_tiles * p.n_tiles;
+  const int g = (int)(item / per_g);
+  const int r = (int)(item - (int64_t)g * per_g);
+  const int nt = r / p.m_tiles, mt = r - nt * p.m_tiles;
+  const int m0 = mt * kGemmTile, n0 = nt * kGemmTile;
+  const uint16_t* A = p.a + (int64_t)g * p.a_batch + (int64_t)m0 * p.lda;
+  const uint16_t* Bm = p.b + (int64_t)g * p.b_batch + (int64_t)n0 * p.ldb;
+  const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(gemm_lds);
+
+  // this wavefront's loads of a stage: rows 32 wave .. + 31 of either operand,
+  // 16 rows (1 KB) each
+  constexpr int kLoads = 4;
+  uint32_t off[kLoads];
+#pragma unroll
+  for (int u = 0; u < kLoads; ++u) {
+    const int row = 32 * wave + 16 * (u & 1) + (lane >> 2);
+    const int last = (u < 2 ? p.M - m0 : p.N - n0) - 1;
+    off[u] = (uint32_t)(min(row, last) * (int)(u < 2 ? p.lda : p.ldb) * 2 + (lane & 3) * 16);
+  }
+  auto fetch = [&](int st) {
+    const uint32_t at = lds0 + (uint32_t)(st % kRing) * (2 * kRingBytes) + (uint32_t)wave * 2048;
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const uint32_t to = __builtin_amdgcn_readfirstlane(at + (u >> 1) * kRingBytes + (u & 1) * 1024);
+      const uint16_t* from = (u < 2 ? A : Bm) + st * kRingKs;
+      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off[u]),
+                   "s"(from), "s"(to)
+                   : "memory", "m0");
+    }
+  };
+
+  const int wm = (wave & 1) * 64, wn = (wave >> 1) * 64;  // this wavefront's quarter
+  const int li = lane & 15, kq = (lane >> 4) * 8;
+  f32x4 acc[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      // the fragment of D = C^T holds rows 4 (lane / 16) + e, column lane % 16:
-      // C row lane % 16, columns 4 (lane / 16) + e of the block
-      const int row = m0 + wm + 16 * i + li;
-      const int col = n0 + wn + 16 * j + (lane >> 4) * 4;
-      if (row >= p.M) continue;
-      float v[4];
+    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0f;
+  auto multiply = [&](int st) {
+    const uint16_t* sa = gemm_lds + (st % kRing) * kRingBytes;  // 2 operands of kRingBytes / 2
+    const uint16_t* pa = sa + (wm + li) * kRingKs + kq;
+    const uint16_t* pb = sa + kRingBytes / 2 + (wn + li) * kRingKs + kq;
+    bf16x8 fa[4], fb[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = kTanh ? act_tanh(acc[i][j][e]) : acc[i][j][e];
-      float* q = C + (int64_t)row * p.ldc + col;
-      if (col + 3 < p.N && (p.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0) {
-        f32x4 w = {v[0], v[1], v[2], v[3]};
-        *(__attribute__((address_space(1))) f32x4*)q = w;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (col + e < p.N) store_global(q + e, v[e]);
-      }
+    for (int i = 0; i < 4; ++i) {
+      fa[i] = *reinterpret_cast<const bf16x8*>(pa + 16 * i * kRingKs);
+      fb[i] = *reinterpret_cast<const bf16x8*>(pb + 16 * i * kRingKs);
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+  };
+  const int n_stages = p.K / kRingKs;
+  const int ahead = min(kRing - 1, n_stages);
+  for (int st = 0; st < ahead; ++st) fetch(st);
+  // the wavefront's loads complete in order: at most those of the later
+  // stages that were requested may still be on their way
+  for (int st = 0; st < n_stages; ++st) {
+    switch (min(kRing - 2, n_stages - 1 - st)) {
+      case 3: asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); break;
+      case 2: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
+      case 1: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
+      default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+    }
+    lds_barrier();
+    if (st + kRing - 1 < n_stages) fetch(st + kRing - 1);
+    multiply(st);
+  }
+  store_tile<kTanh>(p, acc, p.c + (int64_t)g * p.c_batch, m0 + wm + li, n0 + wn + (lane >> 4) * 4);
 }
 
 template <bool kTanh>
@@ -704,11 +803,15 @@ int launch_gemm(GemmArgs p, int batch, hipStream_t stream) {
   p.m_tiles = (p.M + kGemmTile - 1) / kGemmTile;
   p.n_tiles = (p.N + kGemmTile - 1) / kGemmTile;
   p.n_items = (int64_t)batch * p.m_tiles * p.n_tiles;
-  const int rc = allow_lds((const void*)gemm_nt_kernel<kTanh>, kGemmLds);
+  // LDS-direct loads take 16-byte pieces of every row: both operands aligned
+  const bool ring = ((reinterpret_cast<uintptr_t>(p.a) | reinterpret_cast<uintptr_t>(p.b)) & 15) == 0 &&
+                    ((p.lda | p.ldb | p.a_batch | p.b_batch) & 7) == 0;
+  const auto kern = ring ? gemm_ring_kernel<kTanh> : gemm_nt_kernel<kTanh>;
+  const size_t lds = ring ? kRingLds : kGemmLds;
+  const int rc = allow_lds((const void*)kern, lds);
   if (rc != TN_OK || p.n_items == 0) return rc;
   if (p.n_items > 0x7fffffff) return TN_EUNSUPPORTED;
-  hipLaunchKernelGGL((gemm_nt_kernel<kTanh>), dim3((unsigned)p.n_items), dim3(256), kGemmLds,
-                     stream, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)p.n_items), dim3(256), lds, stream, p);
   return check_launch();
 }
 

@@ -171,6 +171,34 @@ def test_substrate_forward_matches_oracle(shared):
         assert np.all(np.abs(y[g] - Hb @ W2[g].T) <= (2.0 ** -8 + 2.0 ** -14) * mag + 1e-30), g
 
 
+@pytest.mark.parametrize("grid,B", [(8, 1), (8, 129), (16, 127), (24, 128), (32, 257)])
+def test_substrate_product_forms_agree(grid, B):
+    """The product by LDS-direct loads (aligned operands) and by registers
+    (inputs shifted by one element) take the same sums: equal bits, at sizes
+    that fill a tile of 128 rows and columns, miss it and pass it; hidden
+    values and, above 128 rows, the weight gradient."""
+    import paper_2504_08339_amd as tn
+    rng = np.random.default_rng(B)
+    S, P = grid * grid, 3
+    bf = lambda *shape: torch.from_numpy(rng.standard_normal(shape).astype(np.float32)).cuda() \
+        .to(torch.bfloat16)
+    w1t, w2t, x = bf(P, S, S) * 0.1, bf(P, 5, S) * 0.1, bf(P, B, S)
+    shifted = torch.empty(P * B * S + 1, dtype=torch.bfloat16, device="cuda")[1:].view(P, B, S)
+    shifted.copy_(x)
+    h, _ = tn.substrate_forward(w1t, w2t, x, grid, 5, THR)
+    h2, _ = tn.substrate_forward(w1t, w2t, shifted, grid, 5, THR)
+    assert torch.equal(h.view(torch.int32), h2.view(torch.int32))
+    ref = torch.tanh(torch.stack([x[g].float() @ w1t[g].float().T for g in range(P)]).double())
+    assert (h - ref).abs().max() < 1e-4
+    if B > 128:
+        dy = torch.from_numpy(rng.standard_normal((P, B, 5)).astype(np.float32)).cuda()
+        dw1t, _ = tn.substrate_backward(w2t, x, h, dy, grid, 5, THR)
+        dz = (torch.stack([dy[g] @ w2t[g].float() for g in range(P)]) * (1 - h * h)).to(torch.bfloat16)
+        want = torch.stack([dz[g].double().T @ x[g].double() for g in range(P)])
+        size = torch.stack([dz[g].double().abs().T @ x[g].double().abs() for g in range(P)])
+        assert ((dw1t - want).abs() <= 2.0 ** -7 * size).all()
+
+
 @pytest.mark.parametrize("shared", [True, False])
 def test_substrate_backward_matches_oracle(shared):
     """Gradients of sum(dY * Y) against the oracle's substrate adjoint on the
