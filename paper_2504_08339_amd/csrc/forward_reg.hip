@@ -37,6 +37,7 @@ struct RegArgs {
   int in_phase;            // tiles of inputs staged per LDS-direct round
   int stage_stride;        // floats of LDS staging per wavefront
   int n_list;              // persistent form: list length
+  int wide_phase;          // in_phase of the wide units (see reg_genome)
 };
 
 // Persistent form, XCD-aware: workgroup b runs on XCD b % 8 (the round-robin
@@ -251,6 +252,18 @@ __device__ __forceinline__ float reg_genome(TN_REG_PARAMS, int g, int t_begin, i
     }
     const float* xg = obs + (int64_t)g * a.obs_stride;
     const float* tg = kLoss ? target + (int64_t)g * a.target_stride : nullptr;
+    // A genome of more rows than four tiles leave it, in a launch that takes
+    // up to 100: two units of two tiles in the same registers. (Left to a
+    // launch of its own, the one genome in a hundred that needs it cost 4.5 us
+    // beside the 51 of 1000 control genomes on 1000 observations.)
+    if constexpr (NB == 50 && !kLoss) {
+      if (rows > NB) {
+        for (int b = b0; b < b0 + nobs; b += 2 * kWave)
+          run_unit<100, false>(rec, pe, nn, a.wide_phase, pn, out_pos, orow_first, I, O, b, a.B,
+                               xg, yg, tg, stg, lane);
+        continue;
+      }
+    }
     sse += run_unit<NB, kLoss>(rec, pe, nn, a.in_phase, pn, out_pos, orow_first, I, O, b0, a.B, xg,
                                yg, tg, stg, lane);
   }
@@ -395,16 +408,17 @@ int launch_forward_reg(const tn_population& p, const tn_transformed& t, const fl
                        int64_t obs_stride, int B, float* out, const RegTile& tile,
                        const FwdWork& work, hipStream_t stream) {
   const int waves = tile.waves <= 0 ? 4 : tile.waves;
-  const int rows = tile.rf;
+  const int rows = tile.rows ? tile.rows : tile.rf;
   const int variant = tile.rf;
   if (waves > 8 || !valid_variant(variant)) return TN_EINVAL;
+  if (tile.rows && (tile.rf != 50 || tile.rows != 100 || work.queue)) return TN_EINVAL;
   const int n_list = work.genomes ? work.n_genomes : p.P;
   // units of stage_tiles(variant) tiles of 64 observations per genome
   const int kt = stage_tiles(variant);
   const int n_tiles = ((B + kWave - 1) / kWave + kt - 1) / kt;
   RegArgs a{obs_stride, B,  0, 0.0f, 0.0f, n_tiles, 1, n_tiles, rows, tile.rows_lo,
             tile.skip_above ? 1 : 0, work.genomes, work.queue, 0, dma_phase(variant, p.n_in),
-            stage_floats(variant, p.n_in), n_list};
+            stage_floats(variant, p.n_in), n_list, dma_phase(100, p.n_in)};
   if (work.queue) {
     if (!work.genomes) return TN_EINVAL;  // the persistent form takes a list
     a.n_items = n_list * n_tiles;
@@ -447,7 +461,7 @@ int loss_rf(const tn_population& p, const tn_transformed& t, const float* obs,
   const int n_units = ((B + kWave - 1) / kWave + kt - 1) / kt;
   RegArgs a{obs_stride, B, target_stride, scale, offset, n_units, 1, n_units, V, rows_lo,
             skip_above ? 1 : 0, nullptr, nullptr, 0, dma_phase(V, p.n_in),
-            stage_floats(V, p.n_in), p.P};
+            stage_floats(V, p.n_in), p.P, 0};
   return launch_grid<V, true>(p, t, obs, out, target, loss, a, p.P, waves, stream);
 }
 

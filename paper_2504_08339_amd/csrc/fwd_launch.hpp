@@ -21,8 +21,10 @@ struct RegTile {
   int rf = 64;              // rows per tile of the register file (32, 64, 96, 128, 160,
                             // 200: one tile of 64 observations per wavefront; 100: two;
                             // 50: four)
+  int rows = 0;             // rows a genome may need (0: rf; 100 with rf = 50 in the grid form:
+                            // genomes of more than 50 run two tiles at a time)
   int rows_lo = -1;         // genomes with prog_rows <= rows_lo are skipped
-  bool skip_above = false;  // genomes with prog_rows > rf are skipped (else NaN)
+  bool skip_above = false;  // genomes that need more rows are skipped (else NaN)
 };
 
 // Level-parallel LDS engine (forward.hip).

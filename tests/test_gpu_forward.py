@@ -401,3 +401,21 @@ def test_small_batches_equal_the_lds_engine(B):
                                      store_outputs=False)
         assert none is None and np.array_equal(host(only).view(np.uint32), host(loss).view(np.uint32))
         assert np.isnan(host(loss)[flagged]).all()
+
+
+@pytest.mark.parametrize("B", [193, 256, 257, 384, 385, 460])
+def test_two_tile_genomes_in_the_four_tile_launch(B):
+    """The automatic choice from 193 observations on runs genomes of 51 to 100
+    program rows two tiles at a time in the launch of those of up to 50: the
+    LDS engine's bits, over units that end in each of their four tiles."""
+    import paper_2504_08339_amd as tn
+    pop = synth.grow_population(24, 17, 6, 128, 512, np.linspace(60, 230, 24).astype(int),
+                                np.random.default_rng(B), hidden_acts=("tanh", "sin"),
+                                output_acts=("tanh",))
+    dp = to_device(pop)
+    tr = tn.transform(dp)
+    rows = host(tr.prog_rows)[:pop.P]
+    assert (rows <= 50).any() and ((rows > 50) & (rows <= 100)).any()
+    obs = tensor(np.random.default_rng(1).normal(size=(pop.P, B, 17)).astype(np.float32))
+    ref = host(tn.forward(dp, tr, obs, engine=tn.TN_ENGINE_LDS))
+    assert np.array_equal(host(tn.forward(dp, tr, obs)).view(np.uint32), ref.view(np.uint32))
