@@ -50,27 +50,24 @@ __device__ __forceinline__ uint32_t hash64(unsigned long long k) {
   return hash32((uint32_t)k ^ hash32((uint32_t)(k >> 32)));
 }
 
-// Slot of a hash in a table of any size: the tables are as large as their load
-// allows, since the LDS of the largest genomes decides how many fit a compute
-// unit (535 nodes, 1894 connections: three workgroups; one with tables of powers
-// of two and 64-bit markings. 10,000 uneven genomes, transformation and plan:
-// 1316 us, 1399 before).
-__device__ __forceinline__ int hash_slot(uint32_t h, int size) {
-  return (int)__umulhi(h, (uint32_t)size);
-}
-
 struct Layout {
   // genomes this launch takes: node rows <= n_cap and connection rows <= c_cap,
   // and not both within (n_prev, c_prev) (an earlier launch's); the launch
   // with the population's capacities also takes the oversize genomes
   int n_cap, c_cap, n_prev, c_prev;
   bool last;
-  int HN, HC;              // hash table sizes
+  int HN, HC;              // hash table sizes (powers of two)
   int off_hkey, off_hslot, off_nkey, off_deg, off_rem, off_outdeg, off_pos,
       off_order, off_level, off_ptr, off_cursor, off_outlist, off_esrc, off_edst,
       off_tmp, off_chash, off_csr_row, off_lstart;
   size_t bytes;
 };
+
+int next_pow2(int x) {
+  int p = 1;
+  while (p < x) p <<= 1;
+  return p;
+}
 
 Layout make_layout(int N, int C) {
   Layout L;
@@ -78,8 +75,14 @@ Layout make_layout(int N, int C) {
   L.c_cap = C;
   L.n_prev = L.c_prev = -1;
   L.last = true;
-  L.HN = N + N / 2 + 1;  // at most two thirds full
-  L.HC = C + C / 4 + 1;  // marking hash at most 80 % full
+  // Tables half empty and 4-byte marking entries: the largest genomes of 535
+  // nodes and 1983 connections then take 68 KB, two workgroups per compute unit
+  // (84 KB and one with the 8-byte marking itself as the entry): 10,000 uneven
+  // genomes 785 -> 655 us. Smaller tables, at two thirds and 80 % of their size,
+  // let three workgroups in and lost more to longer probes: 695 us, and 710
+  // against 635 us where C_max is 1894.
+  L.HN = next_pow2(2 * N);
+  L.HC = next_pow2(C + C / 4 + 1);  // marking hash at most 80 % full
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
@@ -111,12 +114,12 @@ Layout make_layout(int N, int C) {
 
 __device__ int lookup_node(const int32_t* hkey, const int16_t* hslot, int HN, int32_t k) {
   if (k < 0) return -1;
-  int h = hash_slot(hash32((uint32_t)k), HN);
+  uint32_t h = hash32((uint32_t)k) & (uint32_t)(HN - 1);
   while (true) {
     int32_t kk = hkey[h];
     if (kk == k) return hslot[h];
     if (kk == kEmptyKey) return -1;
-    h = h + 1 == HN ? 0 : h + 1;
+    h = (h + 1) & (uint32_t)(HN - 1);
   }
 }
 
@@ -311,7 +314,7 @@ __global__ __launch_bounds__(kWave * kW) void transform_kernel(PopView pop, TrVi
     ++my_valid;
     if (pop.node_act[nb + r] > TN_ACT_ABS || pop.node_agg[nb + r] > TN_AGG_MAXABS)
       atomicOr(&flags, TN_BAD_ATTR);
-    int h = hash_slot(hash32((uint32_t)k), L.HN);
+    uint32_t h = hash32((uint32_t)k) & (uint32_t)(L.HN - 1);
     while (true) {
       const int32_t old = atomicCAS(&hkey[h], kEmptyKey, k);
       if (old == kEmptyKey) {
@@ -322,7 +325,7 @@ __global__ __launch_bounds__(kWave * kW) void transform_kernel(PopView pop, TrVi
         atomicOr(&flags, TN_DUP_NODE);
         break;
       }
-      h = h + 1 == L.HN ? 0 : h + 1;
+      h = (h + 1) & (uint32_t)(L.HN - 1);
     }
   }
   int n_valid;
@@ -341,11 +344,11 @@ __global__ __launch_bounds__(kWave * kW) void transform_kernel(PopView pop, TrVi
     int16_t s = -1, d = -1;
     if (a >= 0 && b >= 0) {
       const unsigned long long mark = ((unsigned long long)(uint32_t)a << 32) | (uint32_t)b;
-      // an entry is 19 bits of the hash and the row: keys are compared only
-      // where those bits agree
+      // an entry is the upper 19 bits of the hash and the row: keys are compared
+      // only where those bits agree (the top bit stays clear: no entry is empty)
       const uint32_t hash = hash64(mark);
-      const uint32_t entry = ((hash & 0x7ffffu) << 12) | (uint32_t)r;
-      int h = hash_slot(hash, L.HC);
+      const uint32_t entry = ((hash >> 13) << 12) | (uint32_t)r;
+      uint32_t h = hash & (uint32_t)(L.HC - 1);
       while (true) {
         const uint32_t old = atomicCAS(&chash[h], kEmptyMark, entry);
         if (old == kEmptyMark) break;
@@ -356,7 +359,7 @@ __global__ __launch_bounds__(kWave * kW) void transform_kernel(PopView pop, TrVi
             break;
           }
         }
-        h = h + 1 == L.HC ? 0 : h + 1;
+        h = (h + 1) & (uint32_t)(L.HC - 1);
       }
       if (pop.conn_en[cb + r]) {
         const int sa = lookup_node(hkey, hslot, L.HN, a);
