@@ -115,11 +115,10 @@ __device__ float agg_partial(int agg, int e, int e0, int e1, const EdgeRec* edge
 
 // Genomes the register-file adjoint (backward_rf_kernel, below) takes: at most
 // kRfPos positions, kRfEdges in-edges and kRfSums rows of four sums, sum or
-// mean aggregation. Where N_max rows exceed the device's LDS and the LDS
-// adjoint cannot run, the limits are the documented ones (kRfPosAlone,
-// kRfEdgesAlone): a larger genome's gradients are NaN there.
+// mean aggregation; in some launches (see launch_backward) kRfPosLow and
+// kRfEdgesLow.
 constexpr int kRfPos = 64, kRfEdges = 192, kRfSums = 64;
-constexpr int kRfPosAlone = 48, kRfEdgesAlone = 64;
+constexpr int kRfPosLow = 48, kRfEdgesLow = 64;
 constexpr int kRfWaves = 4;  // wavefronts per genome, at most
 
 // Whether genome g is backward_rf_kernel's; by one wavefront, lane = position.
@@ -628,8 +627,15 @@ int launch_backward(const tn_population& p, const tn_transformed& t, const float
     rc = TN_OK;
   }
   if (rc != TN_OK || p.P == 0) return rc;
+  // The low limits hold where the LDS adjoint cannot run (the documented ones: a
+  // larger genome's gradients are NaN there), and where genomes may exceed the
+  // register file while the LDS adjoint holds the whole population at once: its
+  // time is then one genome's, and the register kernel's is added to it (200
+  // genomes of 55 to 75 positions, 40 observations: 62 us, 109 with the high
+  // limits; 1200 of them, 300 observations: 682 us, 458 with the high limits).
+  const bool full = lds_ok && (p.N_max <= kRfPos || p.P > 256 * (int64_t)(160 * 1024 / lds));
   BwdArgs a{obs_stride, B, dY, dY_stride, target, target_stride, scale, loss, dW, db,
-            lds_ok ? kRfPos : kRfPosAlone, lds_ok ? kRfEdges : kRfEdgesAlone};
+            full ? kRfPos : kRfPosLow, full ? kRfEdges : kRfEdgesLow};
   // Wavefronts per genome: as many as have steps of two tiles, up to 8192 in
   // all. The chip holds 2048 of them, and genomes differ in size: 4096 genomes
   // of 1024 samples took 345 us in two rounds of one wavefront each, 298 us

@@ -119,25 +119,33 @@ def _sized_genome(rng, nc, degrees):
     return nodes, conns
 
 
-@pytest.mark.parametrize("B", [1, 64, 65, 128, 129, 300, 530, 1025])
-def test_register_adjoint_file_sizes(B):
+@pytest.mark.parametrize("B,copies", [(1, 1), (64, 1), (65, 1), (128, 1), (129, 1), (300, 1),
+                                      (530, 1), (1025, 1), (129, 80)])
+def test_register_adjoint_file_sizes(B, copies):
     """Genomes on both sides of each limit of the register-file adjoint (files
     of 48 and 96 rows, 64 positions, 192 in-edges, 64 rows of sums), at batches
-    that end in every part of a step and take one to four wavefronts."""
+    that end in every part of a step and take one to four wavefronts; with many
+    copies also genomes of 65 positions beside them (a population that the LDS
+    adjoint does not hold at once)."""
     import paper_2504_08339_amd as tn
     rng = np.random.default_rng(B)
-    sizes = [(nc, [3] * nc) for nc in (2, 22, 23, 46, 47, 60, 61)]
+    sizes = [(nc, [3] * nc) for nc in (2, 22, 23, 46, 47, 60) + ((61,) if copies > 1 else ())]
     sizes += [(32, [4] * 32), (33, [4] * 33), (2, [0, 0]), (24, [8] * 24), (30, [0, 24] * 15)]
     sizes += [(30, [3] * 3 + [7] * 26 + [1 + extra]) for extra in (0, 1)]  # 192, 193 in-edges
-    pop = population_from_rows([_sized_genome(rng, *s) for s in sizes], 4, 2)
-    X = rng.uniform(-1, 1, size=(pop.P, B, 4)).astype(np.float32)
-    dY = rng.uniform(0.5, 1.5, size=(pop.P, B, 2)).astype(np.float32)
+    genomes = [_sized_genome(rng, *s) for s in sizes]
+    n = len(genomes)
+    pop = population_from_rows(genomes * copies, 4, 2)
+    X = np.tile(rng.uniform(-1, 1, size=(n, B, 4)).astype(np.float32), (copies, 1, 1))
+    dY = np.tile(rng.uniform(0.5, 1.5, size=(n, B, 2)).astype(np.float32), (copies, 1, 1))
     dp = to_device(pop)
     tr = tn.transform(dp)
     assert not host(tr.status)[:pop.P].any()
     dW, db = tn.backward(dp, tr, tensor(X), tensor(dY))
-    rW, rb = oracle.backward_population(pop, X, dY)
-    check_grads(pop, host(dW), host(db), rW, rb, list(range(pop.P)))
+    dW, db = host(dW).reshape(copies, n, -1), host(db).reshape(copies, n, -1)
+    assert (dW == dW[0]).all() and (db == db[0]).all()
+    one = population_from_rows(genomes, 4, 2)
+    rW, rb = oracle.backward_population(one, X[:n], dY[:n])
+    check_grads(one, dW[0], db[0], rW, rb, list(range(n)))
 
 
 def test_lds_adjoint_beyond_device_lds():
