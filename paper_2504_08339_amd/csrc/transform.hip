@@ -869,7 +869,7 @@ namespace {
 // genomes). Side streams (default priority, non-blocking) and events are made
 // once per device; the mutex keeps the fork / launch / join sequence of one
 // call from interleaving with another's on the same events.
-constexpr int kTfMaxClasses = 5;
+constexpr int kTfMaxClasses = 4;
 constexpr int kMaxDevices = 64;
 struct ClassStreams {
   hipStream_t side[kTfMaxClasses - 1] = {};
@@ -949,11 +949,14 @@ int launch_transform(const tn_population& p, const tn_transformed& t, hipStream_
   // Size classes of a large ragged population: one launch per class, each with
   // the LDS of its largest genome, so the many small genomes are not held to
   // the few large ones' LDS (two workgroups per CU at 535 nodes / 1894
-  // connections). A padded population, or a small one, is one launch.
+  // connections). A padded population, or a small one, is one launch. Four
+  // classes, as many as a process has hardware queues: 10,000 uneven genomes 603
+  // us, 10,000 others 571 and 2500 of them 193 us, against 637, 623 and 253 us
+  // with five (96, 192, 320 and 400 rows) and 626, 612 and 203 us with three.
   std::vector<Layout> cls;
   if (p.node_off && p.P >= kTfClassMinGenomes) {
     int n_prev = -1, c_prev = -1;
-    for (int n : {96, 192, 320, 400}) {
+    for (int n : {128, 256, 400}) {
       const int c = std::min(p.C_max, 4 * n);
       if (n >= p.N_max) break;
       Layout L = make_layout(n, c);
