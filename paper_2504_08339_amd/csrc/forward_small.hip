@@ -54,6 +54,18 @@ __host__ __device__ inline SmallLds small_lds(int N, int C, int nio, int shift) 
   return l;
 }
 
+// log2 of B observations rounded up to a power of two.
+inline int batch_shift(int B) {
+  int shift = 0;
+  while ((1 << shift) < B) ++shift;
+  return shift;
+}
+
+// LDS bytes of one wavefront.
+inline size_t small_bytes(const tn_population& p, int B) {
+  return (size_t)small_lds(p.N_max, p.C_max, p.n_in + p.n_out, batch_shift(B)).bytes;
+}
+
 // One node's aggregate over in-edges e0 .. e1-1 at this lane's observation:
 // v[edge.x] is the source's value. In-edges come four at a time, their records
 // and then their values requested together.
@@ -185,10 +197,8 @@ template <bool kLoss>
 int launch_small(const tn_population& p, const tn_transformed& t, const float* obs,
                  int64_t obs_stride, int B, const float* target, int64_t target_stride,
                  float scale, float offset, float* out, float* loss, hipStream_t stream) {
-  int shift = 0;
-  while ((1 << shift) < B) ++shift;
-  SmallArgs a{obs_stride, B, shift, target_stride, scale, offset, lds_rows_cap(p),
-              small_lds(p.N_max, p.C_max, p.n_in + p.n_out, shift).bytes};
+  SmallArgs a{obs_stride, B, batch_shift(B), target_stride, scale, offset, lds_rows_cap(p),
+              (int)small_bytes(p, B)};
   // as many genomes per workgroup as leave two workgroups to a compute unit
   int waves = kSmallWaves;
   while (waves > 1 && (size_t)waves * a.wave_bytes > 80 * 1024) waves /= 2;
@@ -204,6 +214,11 @@ int launch_small(const tn_population& p, const tn_transformed& t, const float* o
 }
 
 }  // namespace
+
+bool small_batch(const tn_population& p, int B) {
+  return p.N_max > 32 && B > 0 && (B <= 16 || (B <= 32 && p.P <= 2048)) &&
+         small_bytes(p, B) <= max_dynamic_lds();
+}
 
 int launch_forward_small(const tn_population& p, const tn_transformed& t, const float* obs,
                          int64_t obs_stride, int B, const float* target, int64_t target_stride,

@@ -87,9 +87,10 @@ int launch_forward_loss(const tn_population& p, const tn_transformed& t, const f
 // Not where one launch of the smallest register file takes every genome
 // (N_max <= 32): 150 genomes of 16 rows 6.7 against 4.6 us, 10,000 12.2 against
 // 10.7.
-constexpr bool small_batch(const tn_population& p, int B) {
-  return p.N_max > 32 && B > 0 && (B <= 16 || (B <= 32 && p.P <= 2048));
-}
+// Nor where the chip's LDS does not hold one genome of these capacities (from
+// about N_max 880 at C_max 4096 and 17 to 32 observations on): the other engines
+// need no more LDS for a larger batch.
+bool small_batch(const tn_population& p, int B);
 int launch_forward_small(const tn_population& p, const tn_transformed& t, const float* obs,
                          int64_t obs_stride, int B, const float* target, int64_t target_stride,
                          float scale, float offset, float* out, float* loss, hipStream_t stream);

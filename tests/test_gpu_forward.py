@@ -419,3 +419,31 @@ def test_two_tile_genomes_in_the_four_tile_launch(B):
     obs = tensor(np.random.default_rng(1).normal(size=(pop.P, B, 17)).astype(np.float32))
     ref = host(tn.forward(dp, tr, obs, engine=tn.TN_ENGINE_LDS))
     assert np.array_equal(host(tn.forward(dp, tr, obs)).view(np.uint32), ref.view(np.uint32))
+
+
+@pytest.mark.parametrize("B", [1, 16, 17, 32, 33])
+@pytest.mark.parametrize("N,C", [(1024, 4096), (900, 4096), (1024, 2000), (500, 2000)])
+def test_small_batches_of_large_capacities(N, C, B):
+    """Every capacity within the library's limits is accepted at every small
+    batch, by the outputs and by the fused loss: the bits of the register
+    engine (most genomes) and of the LDS engine (the larger ones)."""
+    import paper_2504_08339_amd as tn
+    rng = np.random.default_rng(N + C + B)
+    pop = synth.grow_population(9, 17, 6, N, C, np.array([0, 5, 30, 60, 90, 120, 200, 900, 1300]), rng,
+                                hidden_acts=("tanh", "sin"), output_acts=("tanh",))
+    dp = to_device(pop)
+    tr = tn.transform(dp)
+    obs = tensor(rng.normal(size=(pop.P, B, pop.n_in)).astype(np.float32))
+    need = host(tr.prog_rows)[:pop.P]
+    assert (need <= 200).sum() >= 6 and (need > 200).any()
+    ref = host(tn.forward(dp, tr, obs, engine=tn.TN_ENGINE_REG, rows=200))
+    lds = host(tn.forward(dp, tr, obs, engine=tn.TN_ENGINE_LDS, rows=min(N, 400)))
+    ref[need > 200] = lds[need > 200]
+    assert not np.isnan(ref).any()
+    Y = host(tn.forward(dp, tr, obs))
+    assert np.array_equal(Y.view(np.uint32), ref.view(np.uint32))
+    target = rng.normal(size=(B, pop.n_out)).astype(np.float32)
+    loss, out = tn.forward_loss(dp, tr, obs, tensor(target))
+    assert np.array_equal(host(out).view(np.uint32), ref.view(np.uint32))
+    sse = ((ref.astype(np.float64) - target) ** 2).sum((1, 2))
+    np.testing.assert_allclose(host(loss), sse, rtol=1e-5)
