@@ -342,10 +342,10 @@ int tn_forward(const tn_population* pop, const tn_transformed* tr,
  *                  genomes whose prog_rows exceeds `rows` get NaN outputs.
  *   TN_ENGINE_AUTO the library's choice for every genome (the other fields
  *                  are ignored): for N_max > 32 and B <= 16 (<= 32 for at most
- *                  2048 genomes), where the LDS holds a genome of N_max and
- *                  C_max rows with its values, one wavefront per genome with
- *                  its lanes over the nodes of a level and the observations;
- *                  else TN_ENGINE_REG for prog_rows <= 200 (rows
+ *                  2048 genomes), where the LDS holds enough genomes of N_max
+ *                  and C_max rows with their values, one wavefront per genome
+ *                  with its lanes over the nodes of a level and the
+ *                  observations; else TN_ENGINE_REG for prog_rows <= 200 (rows
  *                  50, 100, 128, 160, 200 when B spans at least 4 tiles of
  *                  64; 100, 128, 160, 200 for 2 or 3 tiles; 32, 64, 96, 128,
  *                  160, 200 for one; each launch takes the genomes the

@@ -80,16 +80,17 @@ int launch_forward_loss(const tn_population& p, const tn_transformed& t, const f
 // Small batches (forward_small.hip): one wavefront per genome, lanes over
 // (node, observation) pairs; loss null: outputs only, else out may be null.
 // Taken up to 16 observations: at 10,000 genomes of 40 nodes 17 us against the
-// register engine's 51 at B = 1 and 28 against 54 at B = 16; at 2000 genomes of
-// up to 535 nodes 32 against 356 us and 137 against 359. Up to 32 where the
+// register engine's 51 at B = 1 and 28 against 54 at B = 16. Up to 32 where the
 // genomes alone do not fill the register engine's 2048 wavefronts: 15 against
 // 24 us at 1000 genomes (but 61 against 55 at 10,000, and 22 against 25 at B = 48).
 // Not where one launch of the smallest register file takes every genome
 // (N_max <= 32): 150 genomes of 16 rows 6.7 against 4.6 us, 10,000 12.2 against
-// 10.7.
-// Nor where the chip's LDS does not hold one genome of these capacities (from
-// about N_max 880 at C_max 4096 and 17 to 32 observations on): the other engines
-// need no more LDS for a larger batch.
+// 10.7. The kernel's LDS follows the row capacities, and with it the wavefronts
+// on the chip: where these would take the genomes in too many rounds, genomes
+// are taken by size class, or, where that does not pay either or the LDS does not
+// hold one genome (from about N_max 880 at C_max 4096 and B = 17 on), the other
+// engines take the call. 2000 genomes of 40 nodes in 512 / 2048 rows, 32 observations:
+// 47 us there, 142 us here.
 bool small_batch(const tn_population& p, int B);
 int launch_forward_small(const tn_population& p, const tn_transformed& t, const float* obs,
                          int64_t obs_stride, int B, const float* target, int64_t target_stride,

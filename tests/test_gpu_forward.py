@@ -447,3 +447,42 @@ def test_small_batches_of_large_capacities(N, C, B):
     assert np.array_equal(host(out).view(np.uint32), ref.view(np.uint32))
     sse = ((ref.astype(np.float64) - target) ** 2).sum((1, 2))
     np.testing.assert_allclose(host(loss), sse, rtol=1e-5)
+
+
+@pytest.mark.parametrize("B", [1, 3, 8, 16])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_small_batches_by_size_class(B, ragged):
+    """Populations too large for one launch at their row capacities (the genomes
+    by size class, or all by the other engines at 16 observations): the
+    engines' bits for genomes on either side of the classes' lines, a flagged
+    genome among them, with the fused loss."""
+    import paper_2504_08339_amd as tn
+    rng = np.random.default_rng(40 + B)
+    few = synth.grow_population(12, 17, 6, 1024, 4096,
+                                np.array([0, 40, 120, 300, 330, 360, 700, 1000, 1300, 20, 60, 250]), rng,
+                                hidden_acts=("tanh", "sin"), output_acts=("tanh",))
+    few.node_key[9, 3] = few.node_key[9, 4]  # a repeated key
+    pop = synth.subset(few, [i % 12 for i in range(1603)])
+    if ragged:
+        pop = synth.to_ragged(pop)
+    dp = to_device(pop)
+    tr = tn.transform(dp)
+    status, need = host(tr.status)[:12], host(tr.prog_rows)[:12]
+    assert (status != 0).tolist() == [i == 9 for i in range(12)]
+    obs = rng.normal(size=(pop.P, B, pop.n_in)).astype(np.float32)
+    large = (need > 200)[np.arange(pop.P) % 12]
+    ok = np.arange(pop.P) % 12 != 9
+    assert large.any() and not large[9]
+    x = tensor(obs)
+    ref = host(tn.forward(dp, tr, x, engine=tn.TN_ENGINE_REG, rows=200))
+    lds = host(tn.forward(dp, tr, x, engine=tn.TN_ENGINE_LDS, rows=400))
+    ref[large] = lds[large]
+    assert not np.isnan(ref[ok]).any()
+    Y = host(tn.forward(dp, tr, x))
+    assert np.array_equal(Y[ok].view(np.uint32), ref[ok].view(np.uint32)) and np.isnan(Y[~ok]).all()
+    target = rng.normal(size=(B, pop.n_out)).astype(np.float32)
+    loss, out = tn.forward_loss(dp, tr, x, tensor(target))
+    assert np.array_equal(host(out)[ok].view(np.uint32), ref[ok].view(np.uint32))
+    sse = ((ref[ok].astype(np.float64) - target) ** 2).sum((1, 2))
+    np.testing.assert_allclose(host(loss)[ok], sse, rtol=1e-5)
+    assert np.isnan(host(loss)[~ok]).all()
