@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(256, 2) void substrate_wgrad_kernel(
 
   // dz of the workgroup's hidden units and dw2t: thread = hidden unit, two
   // threads per unit with every other group of eight rows
-  const int tl = tid & (kGemmTile - 1), half = tid >> 7, t = t0 + tl;
+  const int tl = tid & (kGemmTile - 1), half = wave >> 1, t = t0 + tl;
   const bool unit = t < S;
   const float* H = h + (int64_t)g * B * S + (unit ? t : 0);
   float* sdy = reinterpret_cast<float*>(sx);
@@ -1033,15 +1033,18 @@ __global__ __launch_bounds__(256, 2) void substrate_wgrad_kernel(
     float dz[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const float* d = sdy + min(b0 + u, B - 1) * m;
-      float up = 0.0f;  // rows from B on: H is 0 here, and dz is cleared below
+      dz[u] = 0.0f;
+      if (b0 + u < B) {  // rows from B on add nothing, whatever dY holds
+        const float* d = sdy + (b0 + u) * m;
+        float up = 0.0f;
 #pragma unroll
-      for (int j = 0; j < MO; ++j)
-        if (j < m) {
-          up = fmaf(d[j], w2[j], up);
-          acc2[j] = fmaf(hb[u], d[j], acc2[j]);
-        }
-      dz[u] = b0 + u < B ? up * fmaf(-hb[u], hb[u], 1.0f) : 0.0f;
+        for (int j = 0; j < MO; ++j)
+          if (j < m) {
+            up = fmaf(d[j], w2[j], up);
+            acc2[j] = fmaf(hb[u], d[j], acc2[j]);
+          }
+        dz[u] = up * fmaf(-hb[u], hb[u], 1.0f);
+      }
     }
     u32x4 v;
 #pragma unroll

@@ -598,3 +598,33 @@ def test_substrate_tiles_and_remainders(grid, B, m, shared, shift):
     dzt = dz.transpose(1, 2).contiguous()
     bar = 2.0 ** -8 * (dz_terms.transpose(1, 2).contiguous() @ xd.abs()) + 2.0 ** -126
     assert ((g1 - dzt @ xd).abs() <= bar).all()
+
+
+@pytest.mark.parametrize("B", [1, 31, 32, 97, 127, 130])
+@pytest.mark.parametrize("m", [3, 9])
+def test_substrate_backward_of_infinite_upstreams(B, m):
+    """An infinite upstream value in the batch's last row gives the infinities
+    (and, where it meets a 0, the NaNs) of dY^T H and dZ^T x, on every side of
+    the batch sizes that the gradient kernels round up to."""
+    import paper_2504_08339_amd as tn
+    grid, P = 8, 3
+    S = grid * grid
+    gen = torch.Generator().manual_seed(100 * B + m)
+    normal = lambda *shape: torch.randn(shape, generator=gen)
+    x, w2 = normal(P, B, S).bfloat16(), torch.tanh(normal(P, m, S)).bfloat16()
+    h, dy = torch.tanh(normal(P, B, S)), normal(P, B, m)
+    h[0, B - 1, 5] = 0.0
+    x[0, B - 1, 7] = 0.0
+    dy[0, B - 1, 1] = float("inf")
+    dy[1, B - 1, m - 1] = float("-inf")
+    g1, g2 = tn.substrate_backward(w2.cuda(), x.cuda(), h.cuda(), dy.cuda(), grid, m)
+    hd, dd, xd, wd = h.double(), dy.double(), x.double(), w2.double()
+    want2 = torch.stack([(dd[g, :, :, None] * hd[g, :, None, :]).sum(0) for g in range(P)])
+    dz = torch.stack([(dd[g, :, :, None] * wd[g][None]).sum(1) for g in range(P)]) * (1 - hd * hd)
+    want1 = torch.stack([(dz[g, :, :, None] * xd[g, :, None, :]).sum(0) for g in range(P)])
+    assert torch.isinf(want2).any() and torch.isnan(want2).any() and torch.isinf(want1).any()
+    for got, want in ((g1.cpu().double(), want1), (g2.cpu().double(), want2)):
+        fine = torch.isfinite(want)
+        assert torch.equal(torch.isnan(got), torch.isnan(want))
+        assert torch.equal(got[~fine & ~torch.isnan(want)], want[~fine & ~torch.isnan(want)])
+        assert torch.isfinite(got[fine]).all()
