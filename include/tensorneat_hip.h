@@ -524,8 +524,8 @@ int tn_substrate_forward(const tn_substrate* sub, int32_t P, const uint16_t* w1t
  *   dw1t [P][S][S]      dw1t[g][t][s] = sum_b dZ[b][t] x[b][s],
  *                       dZ = (dY W2^T) (1 - H^2) rounded to bfloat16
  * dy [P][B][n_out] float32; h the forward's output; w2t, x as given to the
- * forward. float32 accumulation in a fixed order (dw1t on the matrix cores).
- * workspace: tn_substrate_workspace_size bytes of device memory
+ * forward. float32 accumulation (dw2t in ascending b; dw1t on the matrix
+ * cores). workspace: tn_substrate_workspace_size bytes of device memory
  * (caller-owned, contents irrelevant). n_out <= 32 and B * n_out <= 16384 here
  * (TN_EUNSUPPORTED otherwise). */
 int tn_substrate_workspace_size(const tn_substrate* sub, int32_t P, int32_t B,

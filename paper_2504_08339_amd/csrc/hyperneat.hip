@@ -945,7 +945,7 @@ __global__ __launch_bounds__(256) void substrate_grad_out_kernel(
 // of x come through registers into LDS transposed (the next tile is requested
 // before this one's MFMAs). So H is read once, and neither dz nor x^T passes
 // through memory. Bound by the stores of dw1t and the reads of H and x: 200 genomes (32 x 32 grids, 128 rows; 840 MB written, 160 MB read)
-// 320 us, against 445 us in three kernels that wrote dz and x^T out.
+// 284 us, against 445 us in three kernels that wrote dz and x^T out.
 constexpr int kFusedBatch = 128;
 constexpr int kFusedRow = kFusedBatch + 8;  // bf16 per LDS row
 constexpr size_t kFusedLds = sizeof(uint16_t) * 2 * kGemmTile * kFusedRow;
@@ -958,7 +958,7 @@ __global__ __launch_bounds__(256, 2) void substrate_wgrad_kernel(
     int tiles_per_part, float* __restrict__ dw1t, float* __restrict__ dw2t) {
   extern __shared__ __align__(16) uint16_t wg_lds[];
   uint16_t* sz = wg_lds;                         // dz^T [128 t][kFusedRow]
-  uint16_t* sx = wg_lds + kGemmTile * kFusedRow; // x^T [128 s][kFusedRow]; first dY, then dw2t's halves
+  uint16_t* sx = wg_lds + kGemmTile * kFusedRow; // x^T [128 s][kFusedRow]; first dY
   const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   const int64_t item = gemm_item(blockIdx.x, gridDim.x);
   const int per_g = t_tiles * parts;
@@ -1005,19 +1005,31 @@ __global__ __launch_bounds__(256, 2) void substrate_wgrad_kernel(
   fetch(s_begin + turn * kGemmTile);
 
   // dz of the workgroup's hidden units and dw2t: thread = hidden unit, two
-  // threads per unit with every other group of eight rows
+  // threads per unit. Each reads every other group of eight rows of H and
+  // takes dz of these; the pair's 16 rows meet in LDS, and each thread adds them
+  // to half of the outputs' sums: one chain per output in ascending b, the sum of
+  // the kernel for larger batches. (With both threads reading all rows of H the
+  // kernel takes 429 us, with branches around the rows past the last 398.)
   const int tl = tid & (kGemmTile - 1), half = wave >> 1, t = t0 + tl;
   const bool unit = t < S;
   const float* H = h + (int64_t)g * B * S + (unit ? t : 0);
-  float* sdy = reinterpret_cast<float*>(sx);
-  for (int i = tid; i < B * m; i += 256) sdy[i] = dy[(int64_t)g * B * m + i];
-  float w2[MO], acc2[MO];
-#pragma unroll
-  for (int j = 0; j < MO; ++j) {
-    w2[j] = j < m && unit ? bf16_float(w2t[((int64_t)g * m + j) * S + t]) : 0.0f;
-    acc2[j] = 0.0f;
+  constexpr int kPair = 16;  // rows that two threads share at once
+  float* sdy = reinterpret_cast<float*>(sx);                  // [B][MO]
+  float (*sh)[kPair][kGemmTile] =                             // [2][kPair][128]
+      reinterpret_cast<float (*)[kPair][kGemmTile]>(sdy + kFusedBatch * MO);
+  static_assert(sizeof(float) * (kFusedBatch * MO + 2 * kPair * kGemmTile) <=
+                sizeof(uint16_t) * kGemmTile * kFusedRow, "dY and H rows fit the tile of x");
+  // rows from B on and outputs from m on are zeros, which add nothing below
+  for (int i = tid; i < (B + 31) / 32 * 32 * MO; i += 256) {
+    const int b = i / MO, j = i % MO;
+    sdy[i] = b < B && j < m ? dy[((int64_t)g * B + b) * m + j] : 0.0f;
   }
-  lds_barrier();
+  float w2[MO], acc2[MO / 2];
+#pragma unroll
+  for (int j = 0; j < MO; ++j)
+    w2[j] = j < m && unit ? bf16_float(w2t[((int64_t)g * m + j) * S + t]) : 0.0f;
+#pragma unroll
+  for (int j = 0; j < MO / 2; ++j) acc2[j] = 0.0f;
   // one group of eight rows ahead; not unrolled further, the code has to stay
   // well inside the instruction cache
   float hb[8], hn[8];
@@ -1028,23 +1040,21 @@ __global__ __launch_bounds__(256, 2) void substrate_wgrad_kernel(
   };
   rows_of(half * 8, hb);
 #pragma unroll 1
-  for (int b0 = half * 8; b0 < (B + 31) / 32 * 32; b0 += 16) {
-    rows_of(b0 + 16, hn);
+  for (int p0 = 0; p0 < (B + 31) / 32 * 32; p0 += kPair) {
+    const int b0 = p0 + half * 8;
+    rows_of(b0 + kPair, hn);
+    float (*rows)[kGemmTile] = sh[(p0 / kPair) & 1];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) rows[half * 8 + u][tl] = hb[u];
+    lds_barrier();  // the rows, and before the first pair dY
     float dz[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      dz[u] = 0.0f;
-      if (b0 + u < B) {  // rows from B on add nothing, whatever dY holds
-        const float* d = sdy + (b0 + u) * m;
-        float up = 0.0f;
+      const float* d = sdy + (b0 + u) * MO;
+      float up = 0.0f;
 #pragma unroll
-        for (int j = 0; j < MO; ++j)
-          if (j < m) {
-            up = fmaf(d[j], w2[j], up);
-            acc2[j] = fmaf(hb[u], d[j], acc2[j]);
-          }
-        dz[u] = up * fmaf(-hb[u], hb[u], 1.0f);
-      }
+      for (int j = 0; j < MO; ++j) up = fmaf(d[j], w2[j], up);
+      dz[u] = b0 + u < B ? up * fmaf(-hb[u], hb[u], 1.0f) : 0.0f;
     }
     u32x4 v;
 #pragma unroll
@@ -1052,20 +1062,20 @@ __global__ __launch_bounds__(256, 2) void substrate_wgrad_kernel(
       v[e] = bf16_bits(dz[2 * e]) | ((uint32_t)bf16_bits(dz[2 * e + 1]) << 16);
     *reinterpret_cast<u32x4*>(sz + tl * kFusedRow + b0) = v;
 #pragma unroll
+    for (int u = 0; u < kPair; ++u) {
+      const float* d = sdy + (p0 + u) * MO + half * (MO / 2);
+      const float x = rows[u][tl];
+#pragma unroll
+      for (int j = 0; j < MO / 2; ++j) acc2[j] = fmaf(x, d[j], acc2[j]);
+    }
+#pragma unroll
     for (int u = 0; u < 8; ++u) hb[u] = hn[u];
   }
-  lds_barrier();  // dY is no longer read
-  if (part == 0) {
-    float* sum = reinterpret_cast<float*>(sx);  // [MO][128]
-    if (half == 1)
+  if (part == 0 && unit)
 #pragma unroll
-      for (int j = 0; j < MO; ++j) sum[j * kGemmTile + tl] = acc2[j];
-    lds_barrier();
-    if (half == 0 && unit)
-#pragma unroll
-      for (int j = 0; j < MO; ++j)
-        if (j < m) dw2t[((int64_t)g * m + j) * S + t] = acc2[j] + sum[j * kGemmTile + tl];
-  }
+    for (int j = 0; j < MO / 2; ++j)
+      if (half * (MO / 2) + j < m)
+        dw2t[((int64_t)g * m + half * (MO / 2) + j) * S + t] = acc2[j];
 
   // this wavefront's quarter: 64 hidden units x 64 columns of a tile
   const int wm = (wave & 1) * 64, wn = (wave >> 1) * 64;
@@ -1078,7 +1088,7 @@ __global__ __launch_bounds__(256, 2) void substrate_wgrad_kernel(
   for (int i_tile = 0; i_tile < n_tiles; ++i_tile) {
     const int s0 = s_begin + turn * kGemmTile;
     turn = turn + 1 == n_tiles ? 0 : turn + 1;
-    lds_barrier();  // the previous tile (or dw2t's halves) is no longer read
+    lds_barrier();  // the previous tile (or dY) is no longer read
     stash();
     lds_barrier();
     if (i_tile + 1 < n_tiles) fetch(s_begin + turn * kGemmTile);
@@ -1563,7 +1573,9 @@ int launch_substrate_backward(const tn_substrate& sub, int P, const uint16_t* w2
     const int per = (tiles + want - 1) / want, parts = (tiles + per - 1) / per;
     const int64_t grid = (int64_t)P * tiles * parts;
     if (grid > 0x7fffffff) return TN_EUNSUPPORTED;
-    const auto kern = m <= 8 ? substrate_wgrad_kernel<8> : substrate_wgrad_kernel<kMaxOutBwd>;
+    const auto kern = m <= 8    ? substrate_wgrad_kernel<8>
+                      : m <= 16 ? substrate_wgrad_kernel<16>
+                                : substrate_wgrad_kernel<kMaxOutBwd>;
     const int rc = allow_lds((const void*)kern, kFusedLds);
     if (rc != TN_OK) return rc;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), kFusedLds, stream, h, w2t, dy, x,

@@ -628,3 +628,22 @@ def test_substrate_backward_of_infinite_upstreams(B, m):
         assert torch.equal(torch.isnan(got), torch.isnan(want))
         assert torch.equal(got[~fine & ~torch.isnan(want)], want[~fine & ~torch.isnan(want)])
         assert torch.isfinite(got[fine]).all()
+
+
+@pytest.mark.parametrize("grid", [8, 24])
+@pytest.mark.parametrize("B,m", [(1, 1), (9, 2), (31, 8), (64, 9), (127, 5), (128, 32)])
+def test_substrate_backward_bits_do_not_depend_on_alignment(grid, B, m):
+    """Inputs that are only 2-byte aligned take the kernels of larger batches:
+    the same bits, dw2t summed in ascending batch index."""
+    import paper_2504_08339_amd as tn
+    S, P = grid * grid, 3
+    gen = torch.Generator().manual_seed(grid + 10 * B + m)
+    normal = lambda *shape: torch.randn(shape, generator=gen)
+    x, w2 = normal(P, B, S).bfloat16().cuda(), torch.tanh(normal(P, m, S)).bfloat16().cuda()
+    h, dy = torch.tanh(normal(P, B, S)).cuda(), normal(P, B, m).cuda()
+    shifted = torch.empty(P * B * S + 1, dtype=torch.bfloat16, device="cuda")[1:].view(P, B, S)
+    shifted.copy_(x)
+    a1, a2 = tn.substrate_backward(w2, x, h, dy, grid, m)
+    b1, b2 = tn.substrate_backward(w2, shifted, h, dy, grid, m)
+    assert torch.equal(a1.view(torch.int32), b1.view(torch.int32))
+    assert torch.equal(a2.view(torch.int32), b2.view(torch.int32))
