@@ -512,8 +512,7 @@ int tn_cppn_query(const tn_population* pop, const tn_transformed* tr, const tn_s
 
 /* Substrate forward of P genomes: x [B][S] bfloat16 bits per genome at
  * x + g*x_genome_stride (0: shared); h [P][B][S] float32 (tanh of the fp32
- * accumulation); y [P][B][n_out] float32 (float32 accumulation in a fixed
- * order). */
+ * accumulation); y [P][B][n_out] float32, summed in ascending hidden index. */
 int tn_substrate_forward(const tn_substrate* sub, int32_t P, const uint16_t* w1t,
                          const uint16_t* w2t, const uint16_t* x, int64_t x_genome_stride,
                          int32_t B, float* h, float* y, hipStream_t stream);

@@ -12,7 +12,7 @@
 //   hidden   H = tanh(X W1): v_mfma_f32_16x16x32_bf16, a workgroup of four
 //            wavefronts per 128 x 128 tile of H with K staged through LDS,
 //            fp32 accumulation, tanh in the epilogue.
-//   output   Y = bf16(H) W2 with fp32 accumulation in a fixed order.
+//   output   Y = bf16(H) W2 with fp32 accumulation in ascending t.
 // Geometry: an n x n grid layer has node n*r + c at (-1 + 2c/(n-1),
 // -1 + 2r/(n-1)); output j of m sits at (-1 + 2j/(m-1), 0).
 #include <algorithm>
@@ -817,65 +817,100 @@ int launch_gemm(GemmArgs p, int batch, hipStream_t stream) {
 
 // ----------------------------------------------------------------- output
 
-// Y[b][j] = sum_t bf16(H[b][t]) w2t[j][t], fp32 accumulation. A workgroup takes
-// 16 rows b and 16 outputs j of one genome; its four wavefronts take every
-// fourth block of 32 hidden units with MFMA 16x16x32, operands straight from
-// memory (a row's 128 bytes of H are four lanes' loads), and add their parts in
-// wavefront order. Bound by reading H once: 200 genomes (128 rows, 1024 hidden
-// units, 8 outputs; 105 MB) 24 us, against 135 us with one thread per
-// output and its 1024 dependent multiply-adds.
+// Y[b][j] = sum_t bf16(H[b][t]) w2t[j][t], fp32 accumulation in ascending t, one
+// product after the other: the order is part of the result, so the sums are 4 x 4
+// outer products on the matrix cores (16 of them for 64 rows and four outputs;
+// bfloat16 MFMA adds 32 products at once). A workgroup takes 64 rows b and 16
+// outputs j of one genome, a wavefront four of them; t comes in blocks of 64
+// through two LDS buffers, kAhead blocks requested ahead. Rows are padded so that
+// 16-byte reads down a column of rows touch every bank once. Bound by reading H
+// and, for few genomes, by the chain of products: 200 genomes (128 rows, 1024
+// hidden units, 8 outputs; 105 MB) 24 us, 135 us with one thread per output
+// straight from memory; vector multiply-adds took 27 us, and 19 us for 60 genomes
+// with 10 outputs (13 us so), bound by their reads of weights from LDS.
+constexpr int kOutRows = kWave, kOutCols = 16, kOutKs = 64, kOutRow = kOutKs + 4;
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
 __global__ __launch_bounds__(256) void substrate_output_kernel(
     const float* __restrict__ h, const uint16_t* __restrict__ w2t, int S, int B, int m,
     int b_tiles, int j_tiles, float* __restrict__ y) {
-  __shared__ f32x4 part[4][kWave];
-  const int lane = lane_id(), wave = wave_id();
+  __shared__ __align__(16) float sh[2][kOutRows * kOutRow];
+  __shared__ __align__(16) float sw[2][kOutCols * kOutRow];
+  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   const int per_g = b_tiles * j_tiles;
   const int g = blockIdx.x / per_g, r = blockIdx.x - g * per_g;
   const int bt = r / j_tiles, jt = r - bt * j_tiles;
-  const int li = lane & 15, kq = (lane >> 4) * 8;
-  const int b = bt * 16 + li, j = jt * 16 + li;
-  const bool row = b < B, col = j < m;
-  const float* H = h + ((int64_t)g * B + (row ? b : 0)) * S + kq;
-  const uint16_t* W = w2t + ((int64_t)g * m + (col ? j : 0)) * S + kq;
-  const bool whole = (reinterpret_cast<uintptr_t>(w2t) & 15) == 0;
-  auto weights = [&](int c) {
-    if (whole) return *reinterpret_cast<const bf16x8*>(W + 32 * c);
-    bf16x8 w;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) w[i] = __builtin_bit_cast(__bf16, W[32 * c + i]);
-    return w;
+  const int b0 = bt * kOutRows, j0 = jt * kOutCols;
+  const float* H = h + ((int64_t)g * B + b0) * S;
+  const uint16_t* W = w2t + ((int64_t)g * m + j0) * S;
+
+  // this thread's part of a block: four hidden units of four rows and of one
+  // output's weights. Loads without a branch, so that older blocks can be waited
+  // for alone: past the last block, row and output they read the last, which is
+  // not used.
+  constexpr int kAhead = 4, kLoads = kOutRows * kOutKs / 4 / 256;
+  struct Block {
+    f32x4 h[kLoads];
+    uint16_t w[4];
   };
-  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-  constexpr int kAhead = 4;  // blocks of 32 in flight
-  for (int c0 = wave; c0 < S / 32; c0 += 4 * kAhead) {
-    f32x8 a[kAhead];
-    bf16x8 w[kAhead];
+  Block in[kAhead];
+  const int n_blocks = S / kOutKs;
+  const int tr = tid >> 4, tk = (tid & 15) * 4;
+  const uint16_t* Wt = W + (int64_t)min(tr, m - j0 - 1) * S + tk;
+  auto fetch = [&](int i, Block& q) {
+    const int t0 = min(i, n_blocks - 1) * kOutKs;
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const int c = c0 + 4 * u;
-      const bool in = c < S / 32;
-      const f32x4 lo = in && row ? *reinterpret_cast<const f32x4*>(H + 32 * c) : f32x4(0.0f);
-      const f32x4 hi = in && row ? *reinterpret_cast<const f32x4*>(H + 32 * c + 4) : f32x4(0.0f);
-      a[u] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      w[u] = in && col ? weights(c) : bf16x8((__bf16)0.0f);
+    for (int u = 0; u < kLoads; ++u)
+      q.h[u] = *reinterpret_cast<const f32x4_any*>(
+          H + (int64_t)min(tr + 16 * u, B - b0 - 1) * S + t0 + tk);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) q.w[e] = Wt[t0 + e];
+  };
+  auto stash = [&](int i, const Block& q) {
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u)
+      *reinterpret_cast<f32x4*>(sh[i & 1] + (tr + 16 * u) * kOutRow + tk) =
+          __builtin_convertvector(__builtin_convertvector(q.h[u], bf16x4), f32x4);
+    f32x4 w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = bf16_float(q.w[e]);
+    *reinterpret_cast<f32x4*>(sw[i & 1] + tr * kOutRow + tk) = w;
+  };
+  const int jw = j0 + 4 * wave;  // this wavefront's outputs
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};  // of row `lane`
+#pragma unroll
+  for (int a = 0; a < kAhead; ++a) fetch(a, in[a]);
+  stash(0, in[0]);
+  fetch(kAhead, in[0]);
+  for (int i0 = 0; i0 < n_blocks; i0 += kAhead) {
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a) {
+      const int i = i0 + a;
+      if (i >= n_blocks) break;
+      lds_barrier();
+      if (jw < m) {
+        const float* ph = sh[i & 1] + lane * kOutRow;
+        const float* pw = sw[i & 1] + (4 * wave + (lane & 3)) * kOutRow;
+#pragma unroll
+        for (int k = 0; k < kOutKs; k += 4) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(ph + k);
+          const f32x4 w = *reinterpret_cast<const f32x4*>(pw + k);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            acc = __builtin_amdgcn_mfma_f32_4x4x1f32(w[e], x[e], acc, 0, 0, 0);
+        }
+      }
+      // the other buffer was last read before the barrier above
+      stash(i + 1, in[(a + 1) % kAhead]);
+      fetch(i + 1 + kAhead, in[(a + 1) % kAhead]);
     }
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u)
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u], __builtin_convertvector(a[u], bf16x8),
-                                                    acc, 0, 0, 0);
   }
-  part[wave][lane] = acc;
-  __syncthreads();
-  if (wave != 0) return;
-#pragma unroll
-  for (int v = 1; v < 4; ++v) acc += part[v][lane];
-  // this lane: row lane % 16, outputs 4 (lane / 16) .. + 3
-  if (!row) return;
-  const int jo = jt * 16 + (lane >> 4) * 4;
-  float* q = y + ((int64_t)g * B + b) * m + jo;
+  if (b0 + lane >= B) return;
+  float* q = y + ((int64_t)g * B + b0 + lane) * m + jw;
 #pragma unroll
   for (int e = 0; e < 4; ++e)
-    if (jo + e < m) q[e] = acc[e];
+    if (jw + e < m) q[e] = acc[e];
 }
 
 // ---------------------------------------------------------------- backward
@@ -1542,7 +1577,7 @@ int launch_substrate_forward(const tn_substrate& sub, int P, const uint16_t* w1t
   ga.K = S;
   int rc = launch_gemm<true>(ga, P, stream);
   if (rc != TN_OK) return rc;
-  const int b_tiles = (B + 15) / 16, j_tiles = (sub.n_out + 15) / 16;
+  const int b_tiles = (B + kOutRows - 1) / kOutRows, j_tiles = (sub.n_out + kOutCols - 1) / kOutCols;
   const int64_t grid = (int64_t)P * b_tiles * j_tiles;
   if (grid > 0x7fffffff) return TN_EUNSUPPORTED;
   hipLaunchKernelGGL(substrate_output_kernel, dim3((unsigned)grid), dim3(256), 0, stream, h, w2t,

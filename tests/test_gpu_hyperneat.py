@@ -647,3 +647,24 @@ def test_substrate_backward_bits_do_not_depend_on_alignment(grid, B, m):
     b1, b2 = tn.substrate_backward(w2, shifted, h, dy, grid, m)
     assert torch.equal(a1.view(torch.int32), b1.view(torch.int32))
     assert torch.equal(a2.view(torch.int32), b2.view(torch.int32))
+
+
+@pytest.mark.parametrize("grid,B,m,scale", [(8, 1, 1, 1.0), (8, 70, 130, 1.0), (16, 64, 8, 1.0),
+                                            (16, 65, 17, 1e-3), (24, 129, 10, 1.0),
+                                            (32, 40, 16, 1.0), (8, 33, 5, 1e-38)])
+def test_substrate_outputs_add_in_ascending_order(grid, B, m, scale):
+    """y is one chain of fused multiply-adds in ascending hidden index: every bit
+    of it, at the edges of the tiles of 64 rows and 16 outputs and for weights
+    down to the smallest magnitudes. The chain here adds the exact product in
+    float64 and rounds to float32 once."""
+    import paper_2504_08339_amd as tn
+    S, P = grid * grid, 2
+    gen = torch.Generator().manual_seed(B + m)
+    normal = lambda *shape: torch.randn(shape, generator=gen)
+    w1, w2, x = (normal(P, S, S) * 0.1).bfloat16(), (normal(P, m, S) * scale).bfloat16(), normal(P, B, S)
+    h, y = tn.substrate_forward(w1.cuda(), w2.cuda(), x.bfloat16().cuda(), grid, m)
+    hb, wd = host(h.bfloat16().double()), w2.double().numpy()
+    acc = np.zeros((P, B, m), np.float32)
+    for t in range(S):
+        acc = (acc.astype(np.float64) + hb[:, :, t, None] * wd[:, None, :, t]).astype(np.float32)
+    assert np.array_equal(host(y).view(np.uint32), acc.view(np.uint32))
