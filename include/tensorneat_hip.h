@@ -576,6 +576,10 @@ int tn_cppn_backward(const tn_population* pop, const tn_transformed* tr, const t
  * The forward pass is recomputed inside the call (nothing is saved by
  * tn_forward). Batch sums run in a fixed order, so results are deterministic.
  * A flagged genome gets NaN in all its rows.
+ * The order is a genome's own, with one exception: above N_max 64, genomes with
+ * 49 to 64 positions or 65 to 192 enabled connections take the LDS adjoint
+ * below in populations that it holds at once (a few hundred genomes), and the
+ * two adjoints round differently.
  * Limits: genomes with at most 64 positions, 192 enabled connections and sum
  * or mean aggregations take a register-file adjoint; the others take an LDS
  * adjoint holding N_max rows of 65 values and of 65 gradients. When that

@@ -120,6 +120,11 @@ __device__ float agg_partial(int agg, int e, int e0, int e1, const EdgeRec* edge
 constexpr int kRfPos = 64, kRfEdges = 192, kRfSums = 64;
 constexpr int kRfPosLow = 48, kRfEdgesLow = 64;
 constexpr int kRfWaves = 4;  // wavefronts per genome, at most
+// Groups of steps, and LDS rows of a wavefront: its sums, and the folded ones of
+// a group (20,240 bytes with the genome's tables: eight wavefronts fit a compute
+// unit, as many as the registers allow).
+constexpr int kRfGroups = 4, kRfRows = kRfSums + 4 * kRfSums / kWave;
+constexpr int kRfWide = 256;  // four tiles a step from this many observations on
 
 // Whether genome g is backward_rf_kernel's; by one wavefront, lane = position.
 __device__ __forceinline__ bool rf_bwd_eligible(int st, int n, const int32_t* rp,
@@ -317,8 +322,8 @@ __global__ __launch_bounds__(kWave) void backward_kernel(
 // 16 lanes, added to one LDS row. That is a quarter of the LDS traffic and of
 // the LDS itself of one slot per sum and lane, so the registers (two wavefronts
 // per SIMD) and not the LDS limit occupancy, and genomes of up to 192 in-edges
-// fit. At the end each sum's 16 lanes are added over the wavefronts in a fixed
-// order. Bound by instruction issue. 4096 genomes (4 -> 2, 22 positions, 45
+// fit. At the end of a group of steps each sum's 16 lanes are added, then the groups
+// in order: the same bits however the launch splits a genome. Bound by instruction issue. 4096 genomes (4 -> 2, 22 positions, 45
 // in-edges), 1024 samples: 264 us; 569 us with a slot per sum and lane, two
 // tiles a step. 1000 genomes (17 -> 6, 39 positions, 126 in-edges), 256
 // observations: 47 us; 148 us in backward_kernel.
@@ -486,6 +491,8 @@ __device__ __forceinline__ float rf_step(const RfGenome& q, int b0, const float*
   return sse;
 }
 
+// kFold: a genome may have more groups of steps than wavefronts.
+template <bool kFold>
 __global__ __launch_bounds__(kWave * kRfWaves) __attribute__((amdgpu_num_vgpr(TN_RF_FILE / 2))) void
 backward_rf_kernel(PopView pop, const int32_t* __restrict__ status,
                    const int32_t* __restrict__ n_valid, const int32_t* __restrict__ order,
@@ -495,12 +502,11 @@ backward_rf_kernel(PopView pop, const int32_t* __restrict__ status,
                    const int32_t* __restrict__ resp_bits, const int32_t* __restrict__ io_pos,
                    const float* __restrict__ obs, BwdArgs a) {
   rf_file_reserve();
-  extern __shared__ __align__(16) float acc_all[];  // [waves][kRfSums][64]
+  extern __shared__ __align__(16) float acc_all[];  // [waves][kRows][64]
   __shared__ int2 edge[kRfEdges + kWave];
   __shared__ int32_t sums_of[kRfSums];  // a row of sums' computed node | its row of the node << 8
   __shared__ int2 node[kRfPos];            // its position, l_edge
-  __shared__ uint32_t held[TN_MAX_CONNS / 32 + TN_MAX_NODES / 32];  // rows with a sum
-  __shared__ float part[kRfWaves];
+  __shared__ float part[kRfGroups];
   const int g = blockIdx.x, tid = threadIdx.x, T = blockDim.x;
   const int lane = lane_id(), wave = wave_id(), W = T / kWave;
   const int64_t nb = uniform64(pop.node_base(g)), cb = uniform64(pop.conn_base(g)),
@@ -510,7 +516,8 @@ backward_rf_kernel(PopView pop, const int32_t* __restrict__ status,
   if (!rf_bwd_eligible(status[g], n, row_ptr + rb, fn + nb, a)) return;  // the LDS kernel's genome
   const int n_edges = row_ptr[rb + n];
   const int nio = pop.n_in + pop.n_out;
-  float* acc = acc_all + wave * kRfSums * kWave;
+  constexpr int kRows = kFold ? kRfRows : kRfSums;
+  float* acc = acc_all + wave * kRows * kWave;
   RfGenome q;
   q.edge = edge;
   q.I = pop.n_in;
@@ -527,7 +534,6 @@ backward_rf_kernel(PopView pop, const int32_t* __restrict__ status,
   };
   for (int e = tid; e < n_edges; e += T)
     edge[e] = make_int2(row_at(src[cb + e]), w_bits[cb + e]);
-  for (int i = tid; i < TN_MAX_CONNS / 32 + TN_MAX_NODES / 32; i += T) held[i] = 0u;
   const int mine = p_fn >= 0 ? mbcnt(nodes) : -1;
   if (wave == 0 && mine >= 0)
     node[mine] = make_int2(lane, (p_start * (int)sizeof(int2)) | ((p_end - p_start) << 16));
@@ -546,66 +552,81 @@ backward_rf_kernel(PopView pop, const int32_t* __restrict__ status,
   if (wave == 0)
     for (int c = 0; c < rows; ++c) sums_of[row0 + c] = lane | (c << 8);
   for (int r = 0; r < n_sums; ++r) acc[r * kWave + lane] = 0.0f;
-  float sse = 0.0f;
+  // rows without a sum stay 0; the others are stored after the last barrier
+  for (int r = tid; r < crows; r += T) a.dW[cb + r] = 0.0f;
+  for (int r = tid; r < nrows; r += T) a.db[nb + r] = 0.0f;
   const float* xg = obs + (int64_t)g * a.obs_stride;
   const float* ug = a.dY ? a.dY + (int64_t)g * a.dY_stride
                          : a.target + (int64_t)g * a.target_stride;
-  // As many tiles a step as the genome's rows leave room for, while every
-  // wavefront still has a step.
+  // As many tiles a step as the genome's rows leave room for and the batch fills.
+  // The steps belong to kRfGroups groups, whose sums are folded and then added
+  // in order: which wavefront takes a group leaves the bits alone.
+  float* kept = acc + kRfSums * kWave;  // kFold: folded sums of groups before the wavefront's last
+  // sum i / 4, quarter i % 4: its 16 lanes, starting at a lane of its own so that
+  // neighbours read different banks
+  auto folded = [](const float* rows, int i) {
+    const float* from = rows + (i >> 2) * kWave + (i & 3) * 16;
+    float t = 0.0f;
+#pragma unroll 8
+    for (int b = 0; b < 16; ++b) t += from[(b + i) & 15];
+    return t;
+  };
   auto steps = [&](auto tiles) {
-    constexpr int K = decltype(tiles)::value;
-    for (int b0 = wave * K * kWave; b0 < a.B; b0 += W * K * kWave)
-      sse += rf_step<K>(q, b0, xg, ug, a, acc);
+    constexpr int K = decltype(tiles)::value, kStep = K * kWave;
+    if constexpr (!kFold) {  // wavefront v takes group v
+      float sse = 0.0f;
+      for (int b0 = wave * kStep; b0 < a.B; b0 += W * kStep)
+        sse += rf_step<K>(q, b0, xg, ug, a, acc);
+      if (a.loss) {
+        const float total = wave_sum(sse);
+        if (lane == 0) part[wave] = total;
+      }
+      return;
+    }
+    for (int v = wave; v < kRfGroups && v * kStep < a.B; v += W) {
+      float sse = 0.0f;
+      for (int b0 = v * kStep; b0 < a.B; b0 += kRfGroups * kStep)
+        sse += rf_step<K>(q, b0, xg, ug, a, acc);
+      if (a.loss) {
+        const float total = wave_sum(sse);
+        if (lane == 0) part[v] = total;
+      }
+      if (v + W >= kRfGroups || (v + W) * kStep >= a.B) break;
+      wave_sync();
+      for (int i = lane; i < 4 * n_sums; i += kWave)
+        kept[i] = v >= W ? kept[i] + folded(acc, i) : folded(acc, i);
+      wave_sync();
+      for (int r = 0; r < n_sums; ++r) acc[r * kWave + lane] = 0.0f;
+    }
   };
   const int file = n + q.nc;
-  if (file <= 48 && a.B > W * 2 * kWave)
+  const int K = file <= 48 && a.B > kRfWide ? 4 : file <= 96 && a.B > kWave ? 2 : 1;
+  if (K == 4)
     steps(std::integral_constant<int, 4>{});
-  else if (file <= 96 && a.B > W * kWave)
+  else if (K == 2)
     steps(std::integral_constant<int, 2>{});
   else
     steps(std::integral_constant<int, 1>{});
-  if (a.loss) {
-    const float total = wave_sum(sse);
-    if (lane == 0) part[wave] = total;
-  }
-  // rows of the genome's blocks that hold a sum; the others get 0
-  for (int e = tid; e < n_edges; e += T) {
-    const int r = edge_row[cb + e];
-    atomicOr(&held[r >> 5], 1u << (r & 31));
-  }
-  for (int i = tid; i < q.nc; i += T) {
-    const int r = order[nb + node[i].x];
-    atomicOr(&held[TN_MAX_CONNS / 32 + (r >> 5)], 1u << (r & 31));
-  }
+  const int groups = min(kRfGroups, (a.B + K * kWave - 1) / (K * kWave));
   __syncthreads();
-  // sum i / 4, quarter i % 4: its 16 lanes over the wavefronts, starting at a
-  // lane of its own so that neighbours read different banks
   for (int i = tid; i < 4 * n_sums; i += T) {
-    const int r = i >> 2, quarter = i & 3;
     float total = 0.0f;
-    for (int w = 0; w < W; ++w) {
-      const float* from = acc_all + (w * kRfSums + r) * kWave + quarter * 16;
-      float t = 0.0f;
-#pragma unroll 8
-      for (int b = 0; b < 16; ++b) t += from[(b + i) & 15];
-      total += t;
+    for (int v = kFold && W == 1 ? max(groups - 2, 0) : 0; v < groups; ++v) {
+      const float* rows = acc_all + (kFold ? v % W : v) * kRows * kWave;
+      total += kFold && v + W < groups ? rows[kRfSums * kWave + i] : folded(rows, i);
     }
-    const int of = sums_of[r];
+    const int of = sums_of[i >> 2];
     const int2 at = node[of & 0xff];
-    const int term = (of >> 8) * 4 + sum_of_quarter(quarter) - 1;  // -1: the bias
+    const int term = (of >> 8) * 4 + sum_of_quarter(i & 3) - 1;  // -1: the bias
     const int e0 = (at.y & 0xffff) / (int)sizeof(int2), ne = at.y >> 16;
     if (term < 0)
       a.db[nb + order[nb + at.x]] = total;
     else if (term < ne)
       a.dW[cb + edge_row[cb + e0 + term]] = total;
   }
-  for (int r = tid; r < crows; r += T)
-    if (!((held[r >> 5] >> (r & 31)) & 1)) a.dW[cb + r] = 0.0f;
-  for (int r = tid; r < nrows; r += T)
-    if (!((held[TN_MAX_CONNS / 32 + (r >> 5)] >> (r & 31)) & 1)) a.db[nb + r] = 0.0f;
   if (a.loss && tid == 0) {
     float total = 0.0f;
-    for (int w = 0; w < W; ++w) total += part[w];
+    for (int v = 0; v < groups; ++v) total += part[v];
     a.loss[g] = a.scale * total;
   }
 }
@@ -633,20 +654,27 @@ int launch_backward(const tn_population& p, const tn_transformed& t, const float
   // time is then one genome's, and the register kernel's is added to it (200
   // genomes of 55 to 75 positions, 40 observations: 62 us, 109 with the high
   // limits; 1200 of them, 300 observations: 682 us, 458 with the high limits).
-  const bool full = lds_ok && (p.N_max <= kRfPos || p.P > 256 * (int64_t)(160 * 1024 / lds));
+  const bool full = lds_ok && (p.N_max <= kRfPos ||
+                               p.P > kComputeUnits * (int64_t)(max_dynamic_lds() / lds));
   BwdArgs a{obs_stride, B, dY, dY_stride, target, target_stride, scale, loss, dW, db,
             full ? kRfPos : kRfPosLow, full ? kRfEdges : kRfEdgesLow};
-  // Wavefronts per genome: as many as have steps of two tiles, up to 8192 in
-  // all. The chip holds 2048 of them, and genomes differ in size: 4096 genomes
-  // of 1024 samples took 345 us in two rounds of one wavefront each, 298 us
-  // with two, 296 us with four.
-  const int64_t steps = ((int64_t)B + 2 * kWave - 1) / (2 * kWave);
-  const int waves = (int)std::max<int64_t>(
-      1, std::min<int64_t>({(int64_t)kRfWaves, steps, (8192 + p.P - 1) / p.P}));
-  const size_t rf_lds = sizeof(float) * (size_t)waves * kRfSums * kWave;
-  rc = allow_lds((const void*)backward_rf_kernel, rf_lds);
+  // Wavefronts per genome; none of a result's bits follow them. With few genomes
+  // one for every tile, up to a group each. Else as many as the usual genomes
+  // have steps (of two tiles, of four beyond kRfWide observations), the groups of
+  // the others folded in turn: three wavefronts that share four groups took 227 us
+  // for 1000 genomes of 600 observations, four 159.
+  const int tiles = std::max(1, (B + kWave - 1) / kWave);
+  int waves = std::min(kRfWaves, tiles);
+  if (p.P > 8192)
+    waves = 1;
+  else if (p.P > 512 && tiles <= (p.P > 4000 ? 12 : 8))
+    waves = tiles <= 2 ? 1 : 2;
+  const bool fold = waves < std::min(kRfGroups, tiles);
+  const auto kern = fold ? backward_rf_kernel<true> : backward_rf_kernel<false>;
+  const size_t rf_lds = sizeof(float) * (size_t)waves * (fold ? kRfRows : kRfSums) * kWave;
+  rc = allow_lds((const void*)kern, rf_lds);
   if (rc != TN_OK) return rc;
-  hipLaunchKernelGGL(backward_rf_kernel, dim3(p.P), dim3(kWave * waves), rf_lds, stream, make_view(p),
+  hipLaunchKernelGGL(kern, dim3(p.P), dim3(kWave * waves), rf_lds, stream, make_view(p),
                      t.status, t.n_valid, t.order, t.row_ptr, t.edge_src,
                      reinterpret_cast<const int32_t*>(t.edge_w), t.edge_row, t.pos_fn,
                      reinterpret_cast<const int32_t*>(t.pos_bias),

@@ -244,7 +244,7 @@ SmallFit small_fit(int n_cap, int c_cap, int nio, int shift) {
   f.waves = kSmallWaves;
   while (f.waves > 1 && f.waves * f.bytes > 80 * 1024) f.waves /= 2;
   const int64_t groups = (int64_t)max_dynamic_lds() / (f.waves * f.bytes);
-  f.resident = 256 * std::min<int64_t>(32, groups * f.waves);
+  f.resident = kComputeUnits * std::min<int64_t>(32, groups * f.waves);
   return f;
 }
 

@@ -14,6 +14,7 @@ namespace tn {
 __host__ __device__ constexpr int rf_tiles_of(int R) { return R == 50 ? 4 : R == 100 ? 2 : 1; }
 
 constexpr int kWave = 64;
+constexpr int kComputeUnits = 256;  // of an MI355X
 
 // Population descriptor passed to kernels by value.
 struct PopView {

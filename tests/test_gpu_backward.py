@@ -324,3 +324,27 @@ def test_autograd_function():
     _, dW, db = tn.forward_backward_mse(dp, tr, Xt, Tt)
     np.testing.assert_allclose(host(w.grad), host(dW), rtol=1e-5, atol=1e-7)
     np.testing.assert_allclose(host(b.grad), host(db), rtol=1e-5, atol=1e-7)
+
+
+@pytest.mark.parametrize("B", [40, 100, 128, 200, 300, 512, 600, 1100])
+def test_gradients_do_not_follow_the_population(B):
+    """A genome's gradients and loss have the same bits in populations of 9, 600,
+    5000 and 9000 genomes, which split its batch over different numbers of
+    wavefronts: genomes of four, two and one tile a step."""
+    import paper_2504_08339_amd as tn
+    few = synth.grow_population(9, 4, 2, 64, 192, np.array([6, 12, 18, 24, 50, 90, 120, 150, 170]),
+                                np.random.default_rng(B), hidden_acts=("tanh", "sin"),
+                                output_acts=("identity",))
+    nodes = (few.node_key >= 0).sum(1)
+    file = 2 * nodes - 4  # rows of values and gradients
+    assert (file <= 48).any() and ((file > 48) & (file <= 96)).any() and (file > 96).any()
+    X = tensor(np.random.default_rng(1).normal(size=(B, 4)).astype(np.float32))
+    T = tensor(np.random.default_rng(2).normal(size=(B, 2)).astype(np.float32))
+    first = None
+    for P in (9, 600, 5000, 9000):
+        dp = to_device(synth.subset(few, [i % 9 for i in range(P)]))
+        got = [host(t)[:9].view(np.uint32) for t in tn.forward_backward_mse(dp, tn.transform(dp), X, T)]
+        first = got if first is None else first
+        for a, b in zip(first, got):
+            assert np.array_equal(a, b), P
+    assert np.isfinite(first[1].view(np.float32)).all()
