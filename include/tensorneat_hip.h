@@ -546,7 +546,9 @@ int tn_substrate_backward(const tn_substrate* sub, int32_t P, const uint16_t* w2
  * 0; genomes that are flagged, have more than 32 nodes or 64 enabled
  * connections, or use an aggregation other than sum or mean get NaN.
  * Per-query terms are accumulated in float32 per lane and reduced in a fixed
- * order (deterministic). workspace: tn_cppn_backward_workspace_size bytes. */
+ * order (deterministic; it follows the substrate's size and, where few genomes
+ * are split finer, their number). workspace: tn_cppn_backward_workspace_size
+ * bytes, which is enough for fewer genomes too. */
 int tn_cppn_backward_workspace_size(const tn_population* pop, const tn_substrate* sub,
                                     size_t* bytes);
 int tn_cppn_backward(const tn_population* pop, const tn_transformed* tr, const tn_substrate* sub,

@@ -1487,9 +1487,10 @@ __global__ __launch_bounds__(256) void cppn_grad_reduce_kernel(
 
 // Targets per wavefront: the most (each wavefront pays for reading its genome
 // and for the fixed and target nodes) that still gives `waves` wavefronts.
+constexpr int kCppnRunLeast = 8;
 int cppn_run(int P, const SubGeom& sg, int most, int waves) {
   int run = most;
-  while (run > 8 && (int64_t)P * cppn_items(sg, run) < waves) run /= 2;
+  while (run > kCppnRunLeast && (int64_t)P * cppn_items(sg, run) < waves) run /= 2;
   return run;
 }
 
@@ -1657,8 +1658,19 @@ int adjoint_workgroups(int P, const SubGeom& sg) {  // of a genome
 }
 }  // namespace
 
+// Enough for every population of up to P genomes: fewer genomes take shorter runs,
+// so 15 of them (32 x 32 grid, 8 outputs) make more partial sums than 16.
 size_t cppn_backward_workspace_bytes(const tn_population& p, const tn_substrate& sub) {
-  return sizeof(float) * (size_t)p.P * adjoint_workgroups(p.P, geometry(sub)) * kCppnPart;
+  const SubGeom sg = geometry(sub);
+  int64_t groups = 0;
+  for (int run = kCppnRun; run >= kCppnRunLeast; run /= 2) {
+    // genomes that take this run, at most
+    const int64_t genomes =
+        run == kCppnRun ? p.P
+                        : std::min<int64_t>(p.P, (kCppnWavesWanted - 1) / cppn_items(sg, 2 * run));
+    groups = std::max(groups, genomes * ((cppn_items(sg, run) + kCppnWaves - 1) / kCppnWaves));
+  }
+  return sizeof(float) * (size_t)groups * kCppnPart;
 }
 
 int launch_cppn_backward(const tn_population& p, const tn_transformed& t, const tn_substrate& sub,

@@ -204,3 +204,25 @@ def test_reproduce_and_node_distance_reject_bad_arguments_without_a_gpu(lib):
                                  None) == _abi.TN_EINVAL
     assert lib.tn_distance_nodes(ctypes.byref(p), 1.0, 0.5, None, dummy_f, None, None,
                                  None) == _abi.TN_EINVAL
+
+
+def test_workspaces_of_more_genomes_are_enough_for_fewer(lib):
+    """Every workspace size grows with the number of genomes, so a buffer made for
+    the largest population serves the smaller ones."""
+    n = ctypes.c_size_t()
+
+    def size(name, *args):
+        assert getattr(lib, name)(*args, ctypes.byref(n)) == _abi.TN_OK
+        return n.value
+
+    for grid, n_out in ((8, 1), (16, 3), (24, 10), (32, 8)):
+        sub = _abi.TnSubstrate(grid, n_out, 0.2)
+        last = [0] * 6
+        for P in range(1, 400):
+            p = ctypes.byref(_fake_pop(P=P, n_in=5, n_out=1))
+            now = [size("tn_cppn_backward_workspace_size", p, ctypes.byref(sub)),
+                   size("tn_substrate_workspace_size", ctypes.byref(sub), P, 40, 40 * grid * grid),
+                   size("tn_distance_workspace_size", p), size("tn_distance_nodes_workspace_size", p),
+                   size("tn_neat_workspace_size", p, 10), size("tn_reproduce_workspace_size", P)]
+            assert all(a <= b for a, b in zip(last, now)), (grid, P, last, now)
+            last = now
