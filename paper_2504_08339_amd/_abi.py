@@ -6,14 +6,35 @@ missing library is an ImportError (there is no fallback path).
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libtnhip.so")
 
-# Addresses of arrays of these types. All are void pointers to ctypes, so an
-# integer address passes as it is.
-c_int32_p = c_int64_p = c_float_p = c_uint8_p = ctypes.c_void_p
+c_int32_p = ctypes.POINTER(ctypes.c_int32)
+c_int64_p = ctypes.POINTER(ctypes.c_int64)
+c_float_p = ctypes.POINTER(ctypes.c_float)
+c_uint8_p = ctypes.POINTER(ctypes.c_uint8)
+_ARRAYS = (c_int32_p, c_int64_p, c_float_p, c_uint8_p)
+
+
+def _address(ctype):
+    """``ctype`` with a plain address (an int or None) in the place of a pointer to
+    an array: making a typed pointer object costs host time at every call."""
+    return ctypes.c_void_p if ctype in _ARRAYS else ctype
+
+
+@functools.lru_cache(maxsize=None)
+def _address_form(struct):
+    return type("_" + struct.__name__, (ctypes.Structure,),
+                {"_fields_": [(name, _address(ctype)) for name, ctype in struct._fields_]})
+
+
+def filled(struct, *values):
+    """A ``struct`` of these values, array pointers given as plain addresses."""
+    return struct.from_buffer(_address_form(struct)(*values))
+
 
 TN_OK, TN_EINVAL, TN_ESHAPE, TN_EUNSUPPORTED, TN_EHIP, TN_ENOMEM = range(6)
 TN_MAX_NODES, TN_MAX_CONNS, TN_MAX_IO = 1024, 4096, 1024
@@ -196,7 +217,9 @@ SIGNATURES = {
 }
 
 
-def load(path: str = LIB_PATH):
+def load(path: str = LIB_PATH, addresses: bool = False):
+    """The library with typed entry points. ``addresses``: with plain addresses in the
+    place of pointers to arrays, for callers that check types and sizes themselves."""
     if not os.path.exists(path):
         raise ImportError(
             f"libtnhip.so not found at {path}; build it with "
@@ -206,7 +229,7 @@ def load(path: str = LIB_PATH):
     for name, (res, args) in SIGNATURES.items():
         fn = getattr(lib, name)
         fn.restype = res
-        fn.argtypes = args
+        fn.argtypes = [_address(a) for a in args] if addresses else args
     return lib
 
 

@@ -17,7 +17,8 @@ import torch
 from . import _abi
 from ._abi import TNError, TnPopulation, TnTransformed, TnTransformedElems
 
-_lib = _abi.load()
+_typed = _abi.load()
+_lib = _abi.load(addresses=True)  # every argument below is checked here
 
 _NODE = {"node_key": torch.int32, "node_bias": torch.float32, "node_resp": torch.float32,
          "node_act": torch.uint8, "node_agg": torch.uint8}
@@ -26,7 +27,7 @@ _CONN = {"conn_in": torch.int32, "conn_out": torch.int32, "conn_w": torch.float3
 
 
 def lib():
-    return _lib
+    return _typed
 
 
 def _p(t, ctype):
@@ -103,8 +104,8 @@ class Population:
             self.t[name] = _need(tensors[name], name, dt, node_shape, self.device)
         for name, dt in _CONN.items():
             self.t[name] = _need(tensors[name], name, dt, conn_shape, self.device)
-        self.c = TnPopulation(
-            self.P, self.n_in, self.n_out, self.N_max, self.C_max, total_nodes, total_conns,
+        self.c = _abi.filled(
+            TnPopulation, self.P, self.n_in, self.n_out, self.N_max, self.C_max, total_nodes, total_conns,
             _p(node_off, _abi.c_int64_p), _p(conn_off, _abi.c_int64_p),
             _p(self.t["node_key"], _abi.c_int32_p), _p(self.t["node_bias"], _abi.c_float_p),
             _p(self.t["node_resp"], _abi.c_float_p), _p(self.t["node_act"], _abi.c_uint8_p),
@@ -147,7 +148,7 @@ def pack_paper_layout(PN: torch.Tensor, PC: torch.Tensor, n_in: int, n_out: int,
     _need(PC, "PC", torch.float32, (P, C_max, 4), d)
     ts = {k: torch.empty((P, N_max), dtype=dt, device=d) for k, dt in _NODE.items()}
     ts.update({k: torch.empty((P, C_max), dtype=dt, device=d) for k, dt in _CONN.items()})
-    arrays = _abi.TnPopulationArrays(*[_p(ts[k], ty) for k, ty in (
+    arrays = _abi.filled(_abi.TnPopulationArrays, *[_p(ts[k], ty) for k, ty in (
         ("node_key", _abi.c_int32_p), ("node_bias", _abi.c_float_p),
         ("node_resp", _abi.c_float_p), ("node_act", _abi.c_uint8_p),
         ("node_agg", _abi.c_uint8_p), ("conn_in", _abi.c_int32_p), ("conn_out", _abi.c_int32_p),
@@ -195,7 +196,7 @@ class Transformed:
                                                  sz.genome_elems, sz.io_elems)
         self._buf = torch.empty(total, dtype=torch.int32, device=pop.device)
         base = self._buf.data_ptr()
-        self.c = TnTransformed(*[base + 4 * at for at, _, _ in self._parts.values()])
+        self.c = _abi.filled(TnTransformed, *[base + 4 * at for at, _, _ in self._parts.values()])
         at, n, _ = self._parts["prog_edge"]
         self._buf[at + n - 16:at + n].zero_()  # the library never writes the padding: keep it defined
 
@@ -447,7 +448,7 @@ def _padded_arrays(n: int, N_max: int, C_max: int, device):
     """Fresh [n][N_max] / [n][C_max] tensors and their tn_population_arrays."""
     ts = {k: torch.empty((n, N_max), dtype=dt, device=device) for k, dt in _NODE.items()}
     ts.update({k: torch.empty((n, C_max), dtype=dt, device=device) for k, dt in _CONN.items()})
-    arrays = _abi.TnPopulationArrays(*[_p(ts[k], ty) for k, ty in (
+    arrays = _abi.filled(_abi.TnPopulationArrays, *[_p(ts[k], ty) for k, ty in (
         ("node_key", _abi.c_int32_p), ("node_bias", _abi.c_float_p),
         ("node_resp", _abi.c_float_p), ("node_act", _abi.c_uint8_p),
         ("node_agg", _abi.c_uint8_p), ("conn_in", _abi.c_int32_p), ("conn_out", _abi.c_int32_p),
@@ -530,7 +531,7 @@ class SpeciesTable:
                                device=device)
         self.last_improved = torch.zeros(self.max_species, **i32)
         self.size = torch.zeros(self.max_species, **i32)
-        self.c = _abi.TnSpeciesTable(self.max_species, arrays, _p(self.alive, _abi.c_int32_p),
+        self.c = _abi.filled(_abi.TnSpeciesTable, self.max_species, arrays, _p(self.alive, _abi.c_int32_p),
                                      _p(self.best, _abi.c_float_p),
                                      _p(self.last_improved, _abi.c_int32_p),
                                      _p(self.size, _abi.c_int32_p))

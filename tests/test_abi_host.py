@@ -226,3 +226,22 @@ def test_workspaces_of_more_genomes_are_enough_for_fewer(lib):
                    size("tn_neat_workspace_size", p, 10), size("tn_reproduce_workspace_size", P)]
             assert all(a <= b for a, b in zip(last, now)), (grid, P, last, now)
             last = now
+
+
+def test_the_mirror_takes_typed_pointers_and_refuses_others(lib):
+    """Struct fields and arguments take ctypes arrays, typed pointers and NULL; an
+    array of another type is refused. filled() takes plain addresses."""
+    keys, floats = (ctypes.c_int32 * 4)(), (ctypes.c_float * 4)()
+    p = _fake_pop()
+    for value in (keys, ctypes.cast(keys, ctypes.POINTER(ctypes.c_int32)), 
+                  ctypes.pointer(ctypes.c_int32(3)), None):
+        p.node_key = value
+        assert bool(p.node_key) == (value is not None)
+    with pytest.raises(TypeError):
+        p.node_key = floats
+    with pytest.raises(ctypes.ArgumentError):
+        lib.tn_distance(ctypes.byref(p), 1.0, 1.0, 0.4, None, keys, None, None, None)
+    a = _abi.filled(_abi.TnPopulationArrays, *[0x1000 * (i + 1) for i in range(8)], None)
+    assert ctypes.cast(a.node_bias, ctypes.c_void_p).value == 0x2000 and not a.conn_en
+    t = _abi.filled(_abi.TnSpeciesTable, 3, a, 0x10, 0x20, 0x30, None)
+    assert ctypes.cast(t.reps.conn_w, ctypes.c_void_p).value == 0x8000 and t.max_species == 3
