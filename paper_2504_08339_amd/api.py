@@ -165,11 +165,12 @@ def pack_paper_layout(PN: torch.Tensor, PC: torch.Tensor, n_in: int, n_out: int,
 
 @functools.lru_cache(maxsize=64)
 def _transformed_layout(node: int, rowptr: int, conn: int, genome: int, io: int):
-    """(elements in all, {name: (offset, elements, dtype)}) of the arrays of a
-    transformation in the C struct's order, each on a boundary of 256 bytes."""
+    """(elements of each of two buffers, {name: (buffer, offset, elements, dtype)}) of
+    the arrays of a transformation in the C struct's order, each on a boundary of
+    256 bytes; the arrays of one word per genome in buffer 0, the others in 1."""
     node, rowptr, conn, genome, io = (max(n, 1) for n in (node, rowptr, conn, genome, io))
     i32, f32 = torch.int32, torch.float32
-    parts, at = {}, 0
+    parts, at = {}, [0, 0]
     for name, n, dtype in (
             ("status", genome, i32), ("n_valid", genome, i32), ("order", node, i32),
             ("level", node, i32), ("row_ptr", rowptr, i32), ("edge_src", conn, i32),
@@ -178,34 +179,38 @@ def _transformed_layout(node: int, rowptr: int, conn: int, genome: int, io: int)
             ("pos_row", node, i32), ("n_rows", genome, i32), ("prog_node", 4 * node, i32),
             ("prog_edge", 2 * (conn + 8), i32),  # + 8 entries of padding
             ("prog_rows", genome, i32), ("prog_rec", 16 * node, i32)):
-        parts[name] = (at, n, dtype)
-        at += (n + 63) // 64 * 64
+        buf = 0 if name in ("status", "n_valid", "n_rows", "prog_rows") else 1
+        parts[name] = (buf, at[buf], n, dtype)
+        at[buf] += (n + 63) // 64 * 64
     return at, parts
 
 
 class Transformed:
-    """Device tensors written by tn_transform (layout in the C header): views of
-    one allocation, made when they are first asked for. (With 18 tensors
-    allocated one by one and typed pointers, the host took longer than the
-    kernels: an autograd step of 1000 control policies 210 us, now 142.)"""
+    """Device tensors written by tn_transform (layout in the C header): views of two
+    allocations, made when they are first asked for. (With 18 tensors allocated
+    one by one and typed pointers, making one took 42 us of host time, now 11, 38
+    with every view; an autograd step of 1000 control policies 210 us, now 142.)
+    A kept ``status`` (or n_valid, n_rows, prog_rows) holds on to a few words per
+    genome, any other view to the whole program."""
 
     def __init__(self, pop: Population):
         sz = TnTransformedElems()
         _check("tn_transformed_size", _lib.tn_transformed_size(ctypes.byref(pop.c), ctypes.byref(sz)))
-        total, self._parts = _transformed_layout(sz.node_elems, sz.rowptr_elems, sz.conn_elems,
-                                                 sz.genome_elems, sz.io_elems)
-        self._buf = torch.empty(total, dtype=torch.int32, device=pop.device)
-        base = self._buf.data_ptr()
-        self.c = _abi.filled(TnTransformed, *[base + 4 * at for at, _, _ in self._parts.values()])
-        at, n, _ = self._parts["prog_edge"]
-        self._buf[at + n - 16:at + n].zero_()  # the library never writes the padding: keep it defined
+        totals, self._parts = _transformed_layout(sz.node_elems, sz.rowptr_elems, sz.conn_elems,
+                                                  sz.genome_elems, sz.io_elems)
+        self._bufs = [torch.empty(n, dtype=torch.int32, device=pop.device) for n in totals]
+        base = [b.data_ptr() for b in self._bufs]
+        self.c = _abi.filled(TnTransformed,
+                             *[base[buf] + 4 * at for buf, at, _, _ in self._parts.values()])
+        buf, at, n, _ = self._parts["prog_edge"]
+        self._bufs[buf][at + n - 16:at + n].zero_()  # the library never writes the padding: keep it defined
 
     def __getattr__(self, name):
         part = self.__dict__.get("_parts", {}).get(name)
         if part is None:
             raise AttributeError(name)
-        at, n, dtype = part
-        t = self._buf[at:at + n]
+        buf, at, n, dtype = part
+        t = self._bufs[buf][at:at + n]
         if dtype != t.dtype:
             t = t.view(dtype)
         self.__dict__[name] = t

@@ -546,3 +546,20 @@ def test_packed_program_malformed_and_holed():
         for g in range(pop.P):
             if got["status"][g] == 0:
                 _check_prog(pop, got, g)
+
+
+def test_kept_arrays_of_a_word_per_genome_hold_no_program():
+    """The per-genome arrays share no storage with the program, so keeping them
+    does not keep it; every array has its documented length."""
+    import paper_2504_08339_amd as tn
+    pop = synth.xor_population(P=40)
+    dp = to_device(pop)
+    tr = tn.transform(dp)
+    small = [tr.status, tr.n_valid, tr.n_rows, tr.prog_rows]
+    large = {getattr(tr, k).untyped_storage().data_ptr()
+             for k in FIELDS if k not in ("status", "n_valid", "n_rows", "prog_rows")}
+    for t in small:
+        assert t.shape == (40,) and t.untyped_storage().nbytes() <= 16 * 256
+        assert t.untyped_storage().data_ptr() not in large
+    assert tr.prog_rec.numel() == 16 * 40 * pop.N_max and tr.edge_w.dtype.is_floating_point
+    assert all(getattr(tr, k).data_ptr() % 256 == 0 for k in FIELDS)
