@@ -297,7 +297,8 @@ __global__ __launch_bounds__(kWave) void transform_small_kernel(PopView pop, TrV
   const int freed = n_unused + mbcnt(dead) + frees_before(end);  // up to this position
   const int taken = mbcnt(nodes) + 1;                            // allocations up to this node
   const int made = max(0, wave_inclusive_max(node ? taken - freed : INT_MIN));  // rows created
-  const int made_before = lane == 0 ? 0 : __shfl_up(made, 1, kWave);
+  const int made_up = __shfl_up(made, 1, kWave);  // every lane active: lane 0 is read
+  const int made_before = lane == 0 ? 0 : made_up;
   const int n_new = __builtin_amdgcn_readlane(made, kWave - 1);
   wave_sync();
   int prog = k;

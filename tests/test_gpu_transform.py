@@ -563,3 +563,29 @@ def test_kept_arrays_of_a_word_per_genome_hold_no_program():
         assert t.untyped_storage().data_ptr() not in large
     assert tr.prog_rec.numel() == 16 * 40 * pop.N_max and tr.edge_w.dtype.is_floating_point
     assert all(getattr(tr, k).data_ptr() % 256 == 0 for k in FIELDS)
+
+
+@pytest.mark.parametrize("dead", [1, 2, 3, 5])
+def test_small_genomes_with_dead_leading_nodes(dead):
+    """Computed nodes without any connection in the first rows, so that the first
+    positions already take and free value rows: the general kernel's fields."""
+    genomes = []
+    for g in range(6):
+        nodes = [[50 + i, 0.5 * i, 1.0, 2, 0] for i in range(dead)]
+        nodes += [[2, 0.0, 1.0, 0, 0], [0, 0.0, 1.0, 0, 0], [40, 0.1, 1.0, 1, 0], [1, 0.0, 1.0, 0, 0]]
+        if g % 2:
+            nodes.reverse()
+        conns = [[0, 40, 0.5, 1], [40, 2, 1.5, 1]] + ([[50, 2, 1.0, 1]] if g % 3 == 1 else [])
+        genomes.append((nodes, conns))
+    pop = population_from_rows(genomes, 2, 1, N_max=12, C_max=4)
+    big = population_from_rows(genomes, 2, 1, N_max=80, C_max=300)
+    got, ref = run_transform(pop), run_transform(big)
+    assert compare(pop, got) == 6
+    for g in range(pop.P):
+        _check_rows(pop, got, g)
+        _check_prog(pop, got, g)
+        (ns, _, _), (nt, _, _) = blocks(pop, g), blocks(big, g)
+        assert got["prog_rows"][g] == ref["prog_rows"][g]
+        for k, w in (("pos_row", 1), ("prog_node", 4), ("prog_rec", 16)):
+            assert np.array_equal(got[k][w * ns.start:w * ns.stop],
+                                  ref[k][w * nt.start:w * (nt.start + 12)]), (k, g)
