@@ -42,16 +42,18 @@ def sources():
 # these files: plain scalar branches instead of structurized flow variables,
 # 8-14 % fewer cycles on the evaluation kernels. Not applied to the NEAT
 # generation and reproduction kernels (the generation's speciation gave wrong
-# species with it). The program-interpreting kernels (forward engines,
-# HyperNEAT, adjoints, recurrent) also start every block that is only reached
-# by a branch on a 32-byte boundary: their per-node code is a chain of taken
+# species with it), nor to the small-batch forward kernel, whose branches on a
+# node's codes differ between lanes (10,000 control policies, one observation:
+# 18.5 us without the flags, 18.3 with them). The program-interpreting kernels
+# (forward engines, HyperNEAT, adjoints, recurrent) also start every block that
+# is only reached by a branch on a 32-byte boundary: their per-node code is a chain of taken
 # branches, and aligned targets made them 1-3 % faster (distance: 1 % slower,
 # transform: no change, so not there).
 _UNIFORM = ["-mllvm", "-structurizecfg-skip-uniform-regions=true"]
 _ALIGN = ["-mllvm", "-align-all-nofallthru-blocks=5"]
 FILE_FLAGS = {f: _UNIFORM for f in ("transform.hip", "distance.hip")}
-FILE_FLAGS.update({f: _UNIFORM + _ALIGN for f in ("forward.hip", "forward_reg.hip", "forward_small.hip",
-                                                  "hyperneat.hip", "backward.hip", "recurrent.hip")})
+FILE_FLAGS.update({f: _UNIFORM + _ALIGN for f in ("forward.hip", "forward_reg.hip", "hyperneat.hip",
+                                                  "backward.hip", "recurrent.hip")})
 
 
 def _compile(src: str, extra) -> str:
