@@ -218,7 +218,8 @@ __device__ __forceinline__ float run_unit(const int32_t* __restrict__ rec,
 // Tiles t_begin, t_begin + t_step, ... < t_end of genome g by this wavefront;
 // returns its part of the squared error (kLoss). *st_out: the genome's
 // status as the launch sees it (0: evaluated; -2: left to another launch).
-template <int NB, bool kLoss>
+// kWide: the launch may take genomes of up to 100 rows on files of 50.
+template <int NB, bool kLoss, bool kWide>
 __device__ __forceinline__ float reg_genome(TN_REG_PARAMS, int g, int t_begin, int t_end,
                                             int t_step, float* stg, int* st_out) {
   const int lane = lane_id();
@@ -256,7 +257,7 @@ __device__ __forceinline__ float reg_genome(TN_REG_PARAMS, int g, int t_begin, i
     // up to 100: two units of two tiles in the same registers. (Left to a
     // launch of its own, the one genome in a hundred that needs it cost 4.5 us
     // beside the 51 of 1000 control genomes on 1000 observations.)
-    if constexpr (NB == 50 && !kLoss) {
+    if constexpr (kWide) {
       if (rows > NB) {
         for (int b = b0; b < b0 + nobs; b += 2 * kWave)
           run_unit<100, false>(rec, pe, nn, a.wide_phase, pn, out_pos, orow_first, I, O, b, a.B,
@@ -303,7 +304,7 @@ forward_rf_kernel(TN_REG_PARAMS, float* __restrict__ loss) {
   }
   const int g = a.genomes ? a.genomes[entry] : entry;
   int st;
-  const float sse = reg_genome<R, kLoss>(TN_REG_ARGS, g, t_begin, t_end, t_step, stg, &st);
+  const float sse = reg_genome<R, kLoss, R == 50 && !kLoss>(TN_REG_ARGS, g, t_begin, t_end, t_step, stg, &st);
   if (kLoss && st != -2) {
     const float total = wave_sum(sse);
     if (lane == 0) part[wave] = total;
@@ -342,7 +343,7 @@ forward_rf_queue_kernel(TN_REG_PARAMS) {
       if (item >= n_share) break;
       const int le = item / a.n_tiles, t = item - le * a.n_tiles;
       int st;
-      reg_genome<R, false>(TN_REG_ARGS, a.genomes[le * kXcds + x], t, t + 1, 1, stg, &st);
+      reg_genome<R, false, false>(TN_REG_ARGS, a.genomes[le * kXcds + x], t, t + 1, 1, stg, &st);
     }
   }
 }

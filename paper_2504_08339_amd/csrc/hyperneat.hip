@@ -211,14 +211,13 @@ __device__ __forceinline__ CppnWave cppn_program(int n, int n_edges, const int32
   } else {
     c.l_row = lane;
   }
-  int first_src = 0;
   for (int e0 = 0; e0 < n_edges; e0 += T) {  // whole wavefronts: the shuffle
     const int e = e0 + tid;
     const int q = e < n_edges ? edge_src[e] : 0;
     const int row = __shfl(c.l_row, q, kWave);
     if (e < n_edges) edge[e] = make_int2(row, w_bits[e]);
   }
-  first_src = lane < n_edges ? edge_src[lane] : 0;  // the first 64 edges' sources
+  const int first_src = lane < n_edges ? edge_src[lane] : 0;  // the first 64 edges' sources
   uint64_t on_src = 0, on_tgt = 0;
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
@@ -496,8 +495,8 @@ __device__ __forceinline__ void cppn_map(const CppnWave& c, const SubGeom& sg, c
 
 __global__ __launch_bounds__(kWave * kMapWaves) __attribute__((amdgpu_num_vgpr(TN_RF_SHORT / 2))) void
 cppn_map_kernel(PopView pop, const int32_t* __restrict__ status,
-                const int32_t* __restrict__ prog_rows, const int32_t* __restrict__ n_valid,
-                const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ edge_src,
+                const int32_t* __restrict__ n_valid, const int32_t* __restrict__ row_ptr,
+                const int32_t* __restrict__ edge_src,
                 const int32_t* __restrict__ w_bits, const int32_t* __restrict__ fn,
                 const int32_t* __restrict__ bias_bits, const int32_t* __restrict__ resp_bits,
                 const int32_t* __restrict__ io_pos, SubGeom sg, int run, int wg_per_g,
@@ -511,7 +510,7 @@ cppn_map_kernel(PopView pop, const int32_t* __restrict__ status,
   const int item = (blockIdx.x - g * wg_per_g) * kMapWaves + wave;
   const int64_t nb = uniform64(pop.node_base(g)), cb = uniform64(pop.conn_base(g)),
                 rb = uniform64(pop.rowptr_base(g));
-  const bool bad = status[g] != 0 || prog_rows[g] > kQueryRows;
+  const bool bad = status[g] != 0;
   const int n = n_valid[g];
   CppnWave c{};
   if (!bad) {
@@ -1536,8 +1535,8 @@ int launch_cppn_query(const tn_population& p, const tn_transformed& t, const tn_
     const int rc = allow_lds((const void*)cppn_map_kernel, lds);
     if (rc != TN_OK) return rc;
     hipLaunchKernelGGL(cppn_map_kernel, dim3((unsigned)blocks), dim3(kWave * kMapWaves), lds,
-                       stream, make_view(p), t.status, t.prog_rows, t.n_valid, t.row_ptr,
-                       t.edge_src, reinterpret_cast<const int32_t*>(t.edge_w), t.pos_fn,
+                       stream, make_view(p), t.status, t.n_valid, t.row_ptr, t.edge_src,
+                       reinterpret_cast<const int32_t*>(t.edge_w), t.pos_fn,
                        reinterpret_cast<const int32_t*>(t.pos_bias),
                        reinterpret_cast<const int32_t*>(t.pos_resp), t.io_pos, sg, run, per_g, w1t,
                        w2t, raw1, raw2);

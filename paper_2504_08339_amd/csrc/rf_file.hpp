@@ -427,39 +427,6 @@ __device__ __forceinline__ void short_file_reserve() { asm volatile("" ::: "v127
 template <int K>
 struct ShortFiles;
 template <>
-struct ShortFiles<1> {
-  static __device__ __forceinline__ void set_v(int r, const float (&v)[1]) {
-    asm volatile(
-        "s_set_gpr_idx_on %1, gpr_idx(DST)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 v48, %0\n\t"
-        "s_set_gpr_idx_off"
-        : 
-        : "v"(v[0]), "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ void get_v(int r, float (&t)[1]) {
-    asm volatile(
-        "s_set_gpr_idx_on %1, gpr_idx(SRC0)\n\t"
-        "s_nop 1\n\t"
-        "v_mov_b32 %0, v48\n\t"
-        "s_set_gpr_idx_off"
-        : "=v"(t[0])
-        : "s"(r)
-        : "m0");
-  }
-  static __device__ __forceinline__ void fma_v(float (&s)[1], float w, int r) {
-    asm volatile(
-        "s_set_gpr_idx_on %2, gpr_idx(SRC1)\n\t"
-        "s_nop 1\n\t"
-        "v_fmac_f32 %0, %1, v48\n\t"
-        "s_set_gpr_idx_off"
-        : "+v"(s[0])
-        : "s"(w), "s"(r)
-        : "m0");
-  }
-};
-template <>
 struct ShortFiles<2> {
   static __device__ __forceinline__ void set_v(int r, const float (&v)[2]) {
     asm volatile(
