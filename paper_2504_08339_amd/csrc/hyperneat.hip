@@ -306,6 +306,7 @@ __device__ __forceinline__ void cppn_pre(const CppnWave& c, int p, int2 ed, floa
         const float w = weight(e);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
+#pragma clang fp contract(off)
           const float t = w * x[k];
           if (b + e == 0) {
             s[k] = t;

@@ -668,3 +668,17 @@ def test_substrate_outputs_add_in_ascending_order(grid, B, m, scale):
     for t in range(S):
         acc = (acc.astype(np.float64) + hb[:, :, t, None] * wd[:, None, :, t]).astype(np.float32)
     assert np.array_equal(host(y).view(np.uint32), acc.view(np.uint32))
+
+
+@pytest.mark.parametrize("aggs", [(1,), (2,), (3,), (4,), (5,), (0, 1, 2, 3, 4, 5)])
+def test_query_walk_bits_of_every_aggregation(aggs):
+    """The walk over sources and targets and the packed program round every
+    aggregation's terms alike (a term of a mean is rounded before it is added)."""
+    import paper_2504_08339_amd as tn
+    pop = population_from_rows(_walk_genomes(np.random.default_rng(7), aggs), 5, 1)
+    out = []
+    for p in (synth.to_padded(synth.to_ragged(pop), N_max=33, C_max=pop.C_max), pop):
+        dp = to_device(p)
+        out.append([host(t) for t in tn.cppn_query(dp, tn.transform(dp), 8, 70, THR, raw=True)[2:]])
+    for a, b in zip(*out):
+        assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
