@@ -790,6 +790,35 @@ int recurrent_lds_check(const tn_population& p, size_t* bytes) {
   return l.total > max_dynamic_lds() ? TN_EUNSUPPORTED : TN_OK;
 }
 
+namespace {
+// Whether the register form is the faster one. A genome's tables and partial
+// sums cost it more, and its wavefronts do not share a tile's nodes: short runs
+// stay on the LDS form. 200 genomes (17 -> 6): 10 sweeps of 64 / 128 observations
+// 40 / 73 us on the LDS form, 61 / 62 us on registers (256: 137 and 63), one sweep
+// 13 / 18 against 32 / 33; 1000 genomes (two rounds of register workgroups): 10
+// sweeps of 64 / 128 / 256 45 / 81 / 155 against 90 / 123 / 125, four sweeps of 256
+// / 500 72 / 137 against 88 / 124. The first lines lie where genomes of five inputs
+// (fewer terms to keep) break even too.
+// Genomes of many inputs or of more than 64 rows mostly fill the file with a tile
+// or two. Four wavefronts then take `units` tiles each, some of their places
+// empty, and a batch of a tile too many is better off on the LDS form: 300 genomes
+// (17 -> 6, 22 computed nodes), register / LDS form, 320 observations, two sweeps
+// 64 / 53 us, four 72 / 86; 1000 genomes, 512 observations, three sweeps 146 / 116,
+// six 156 / 202. The second lines are fitted to 2880 calls (8 to 2500 genomes of 20
+// to 60 nodes, 1 to 24 tiles, 1 to 10 sweeps).
+bool register_form_pays(const tn_population& p, int B, int T) {
+  const int64_t tiles = ((int64_t)B + kWave - 1) / kWave;
+  if (p.P <= 512 ? tiles * ((int64_t)T + 3) < 28 : tiles * ((int64_t)T - 1) < 32) return false;
+  if (p.n_in <= 10 && p.N_max <= 64) return true;
+  const float units = (float)((tiles + kWaves - 1) / kWaves);
+  const float places = units * kWaves / (float)tiles;
+  const float least = p.N_max > 64 ? 4.7f * places + 3.0f / units - 4.0f
+                      : p.P <= 512 ? 4.0f * places + 3.0f / units - 4.0f
+                                   : 3.5f * places + 14.0f / (float)tiles - 0.5f;
+  return (float)T >= least;
+}
+}  // namespace
+
 int launch_forward_recurrent(const tn_population& p, const float* obs, int64_t obs_stride, int B,
                              int T, float* out, int32_t* status, hipStream_t stream) {
   const Layout l = layout(p.N_max, p.C_max, p.n_in + p.n_out);
@@ -808,17 +837,8 @@ int launch_forward_recurrent(const tn_population& p, const float* obs, int64_t o
   const size_t rf_lds = tables + kWaves * sizeof(float) * (size_t)stage;
   // The register form takes every genome it can hold (connection capacities
   // whose tables exceed the LDS leave it out); the LDS form is launched where
-  // a genome of these capacities could be too large for it. A genome's tables
-  // and partial sums cost the register form more, and its wavefronts do not
-  // share a tile's nodes: short runs stay on the LDS form. 200 genomes (17 ->
-  // 6): 10 sweeps of 64 / 128 observations 40 / 73 us on the LDS form, 61 / 62 us
-  // on registers (256: 137 and 63), one sweep 13 / 18 against 32 / 33; 1000
-  // genomes (two rounds of register workgroups): 10 sweeps of 64 / 128 / 256
-  // 45 / 81 / 155 against 90 / 123 / 125, four sweeps of 256 / 500 72 / 137
-  // against 88 / 124. The lines lie where genomes of five inputs (fewer terms to
-  // keep) break even too.
-  const int64_t per = (B + kWave - 1) / kWave;
-  const bool pays = p.P <= 512 ? per * (T + 3) >= 28 : per * (T - 1) >= 32;
+  // a genome of these capacities could be too large for it.
+  const bool pays = register_form_pays(p, B, T);
   rc = pays ? allow_lds((const void*)recurrent_rf_kernel, rf_lds) : TN_EUNSUPPORTED;
   const bool rf = rc == TN_OK;
   if (rf) {
