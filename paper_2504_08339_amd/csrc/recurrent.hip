@@ -799,22 +799,22 @@ namespace {
 // sweeps of 64 / 128 / 256 45 / 81 / 155 against 90 / 123 / 125, four sweeps of 256
 // / 500 72 / 137 against 88 / 124. The first lines lie where genomes of five inputs
 // (fewer terms to keep) break even too.
-// Genomes of many inputs or of more than 64 rows mostly fill the file with a tile
-// or two. Four wavefronts then take `units` tiles each, some of their places
+// Genomes of many inputs mostly fill the file with a tile or two. Four wavefronts
+// then take `units` tiles each, some of their places
 // empty, and a batch of a tile too many is better off on the LDS form: 300 genomes
 // (17 -> 6, 22 computed nodes), register / LDS form, 320 observations, two sweeps
 // 64 / 53 us, four 72 / 86; 1000 genomes, 512 observations, three sweeps 146 / 116,
-// six 156 / 202. The second lines are fitted to 2880 calls (8 to 2500 genomes of 20
-// to 60 nodes, 1 to 24 tiles, 1 to 10 sweeps).
+// six 156 / 202. The second lines are fitted to 720 calls (8 to 2500 such genomes, 1
+// to 24 tiles, 1 to 10 sweeps). Row capacities say nothing of the genomes: in 256
+// rows the same 300 take 81 us for 300 observations, 235 on the LDS form.
 bool register_form_pays(const tn_population& p, int B, int T) {
   const int64_t tiles = ((int64_t)B + kWave - 1) / kWave;
   if (p.P <= 512 ? tiles * ((int64_t)T + 3) < 28 : tiles * ((int64_t)T - 1) < 32) return false;
-  if (p.n_in <= 10 && p.N_max <= 64) return true;
+  if (p.n_in <= 10) return true;
   const float units = (float)((tiles + kWaves - 1) / kWaves);
   const float places = units * kWaves / (float)tiles;
-  const float least = p.N_max > 64 ? 4.7f * places + 3.0f / units - 4.0f
-                      : p.P <= 512 ? 4.0f * places + 3.0f / units - 4.0f
-                                   : 3.5f * places + 14.0f / (float)tiles - 0.5f;
+  const float least = p.P <= 512 ? 4.0f * places + 3.0f / units - 4.0f
+                                 : 3.5f * places + 14.0f / (float)tiles - 0.5f;
   return (float)T >= least;
 }
 }  // namespace
