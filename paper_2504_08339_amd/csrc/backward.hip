@@ -124,7 +124,9 @@ constexpr int kRfWaves = 4;  // wavefronts per genome, at most
 // a group (20,240 bytes with the genome's tables: eight wavefronts fit a compute
 // unit, as many as the registers allow).
 constexpr int kRfGroups = 4, kRfRows = kRfSums + 4 * kRfSums / kWave;
-constexpr int kRfWide = 256;  // four tiles a step from this many observations on
+// More observations than this take four tiles a step: 300 observations of 1500
+// genomes 136 us with three steps of two tiles, 164 with two of four.
+constexpr int kRfWide = 384;
 
 // Whether genome g is backward_rf_kernel's; by one wavefront, lane = position.
 __device__ __forceinline__ bool rf_bwd_eligible(int st, int n, const int32_t* rp,
@@ -583,7 +585,9 @@ backward_rf_kernel(PopView pop, const int32_t* __restrict__ status,
       }
       return;
     }
-    for (int v = wave; v < kRfGroups && v * kStep < a.B; v += W) {
+    // one wavefront takes all groups in turn, else each its own and, back from
+    // the last, another
+    for (int v = wave; v < kRfGroups && v * kStep < a.B;) {
       float sse = 0.0f;
       for (int b0 = v * kStep; b0 < a.B; b0 += kRfGroups * kStep)
         sse += rf_step<K>(q, b0, xg, ug, a, acc);
@@ -591,12 +595,14 @@ backward_rf_kernel(PopView pop, const int32_t* __restrict__ status,
         const float total = wave_sum(sse);
         if (lane == 0) part[v] = total;
       }
-      if (v + W >= kRfGroups || (v + W) * kStep >= a.B) break;
+      const int next = W == 1 ? v + 1 : v < W ? 2 * W - 1 - v : kRfGroups;
+      if (next >= kRfGroups || next * kStep >= a.B) break;
       wave_sync();
       for (int i = lane; i < 4 * n_sums; i += kWave)
-        kept[i] = v >= W ? kept[i] + folded(acc, i) : folded(acc, i);
+        kept[i] = v > 0 && W == 1 ? kept[i] + folded(acc, i) : folded(acc, i);
       wave_sync();
       for (int r = 0; r < n_sums; ++r) acc[r * kWave + lane] = 0.0f;
+      v = next;
     }
   };
   const int file = n + q.nc;
@@ -612,8 +618,10 @@ backward_rf_kernel(PopView pop, const int32_t* __restrict__ status,
   for (int i = tid; i < 4 * n_sums; i += T) {
     float total = 0.0f;
     for (int v = kFold && W == 1 ? max(groups - 2, 0) : 0; v < groups; ++v) {
-      const float* rows = acc_all + (kFold ? v % W : v) * kRows * kWave;
-      total += kFold && v + W < groups ? rows[kRfSums * kWave + i] : folded(rows, i);
+      const int w = v < W ? v : 2 * W - 1 - v;  // the wavefront of group v
+      const float* rows = acc_all + (kFold ? W == 1 ? 0 : w : v) * kRows * kWave;
+      const bool before = W == 1 ? v + 1 < groups : v < W && 2 * W - 1 - v < groups;
+      total += kFold && before ? rows[kRfSums * kWave + i] : folded(rows, i);
     }
     const int of = sums_of[i >> 2];
     const int2 at = node[of & 0xff];
@@ -662,13 +670,14 @@ int launch_backward(const tn_population& p, const tn_transformed& t, const float
   // one for every tile, up to a group each. Else as many as the usual genomes
   // have steps (of two tiles, of four beyond kRfWide observations), the groups of
   // the others folded in turn: three wavefronts that share four groups took 227 us
-  // for 1000 genomes of 600 observations, four 159.
+  // for 1000 genomes of 600 observations, four 159. One where the genomes alone
+  // fill the chip's 2048 several times.
   const int tiles = std::max(1, (B + kWave - 1) / kWave);
   int waves = std::min(kRfWaves, tiles);
   if (p.P > 8192)
     waves = 1;
   else if (p.P > 512 && tiles <= (p.P > 4000 ? 12 : 8))
-    waves = tiles <= 2 ? 1 : 2;
+    waves = tiles <= 2 ? 1 : p.P <= 4000 && (tiles == 5 || tiles == 6) ? 3 : 2;
   const bool fold = waves < std::min(kRfGroups, tiles);
   const auto kern = fold ? backward_rf_kernel<true> : backward_rf_kernel<false>;
   const size_t rf_lds = sizeof(float) * (size_t)waves * (fold ? kRfRows : kRfSums) * kWave;
