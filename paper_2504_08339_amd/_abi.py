@@ -8,6 +8,7 @@ from __future__ import annotations
 import ctypes
 import functools
 import os
+import struct
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libtnhip.so")
@@ -26,14 +27,24 @@ def _address(ctype):
 
 
 @functools.lru_cache(maxsize=None)
-def _address_form(struct):
-    return type("_" + struct.__name__, (ctypes.Structure,),
-                {"_fields_": [(name, _address(ctype)) for name, ctype in struct._fields_]})
+def _packer(struct_type):
+    codes, at, nested = "=", 0, False
+    for name, ctype in struct_type._fields_:
+        field = getattr(struct_type, name)
+        code = "Q" if ctype in _ARRAYS else {ctypes.c_int32: "i", ctypes.c_int64: "q"}.get(ctype)
+        nested |= code is None
+        codes += "x" * (field.offset - at) + (code or f"{field.size}s")
+        at = field.offset + field.size
+    return struct.Struct(codes + "x" * (ctypes.sizeof(struct_type) - at)).pack, nested
 
 
-def filled(struct, *values):
-    """A ``struct`` of these values, array pointers given as plain addresses."""
-    return struct.from_buffer(_address_form(struct)(*values))
+def filled(struct_type, *values):
+    """A ``struct_type`` of these values, array pointers given as plain addresses
+    (1 to 2 us of host time; 40 with a typed pointer object for each)."""
+    pack, nested = _packer(struct_type)
+    if nested:
+        values = [bytes(v) if isinstance(v, ctypes.Structure) else v for v in values]
+    return struct_type.from_buffer_copy(pack(*[0 if v is None else v for v in values]))
 
 
 TN_OK, TN_EINVAL, TN_ESHAPE, TN_EUNSUPPORTED, TN_EHIP, TN_ENOMEM = range(6)
