@@ -3,14 +3,17 @@
 // by their marking (in-key, out-key) in lexicographic order.
 //
 // Two launches:
-//   prep  one wavefront per genome: gather the valid connection rows into LDS,
-//         bitonic-sort them by marking, flag repeated markings, and store the
+//   prep  one wavefront per genome, up to eight of them a workgroup: gather the
+//         valid connection rows into LDS, sort them by marking (up to 256 by
+//         counting, more bitonically), flag repeated markings, and store the
 //         sorted list position-major (keysT[k][g]) so that 64 genomes' k-th
 //         genes are 64 consecutive words.
-//   pairs block = up to kMaxRows "row" genomes x 256 "column" genomes (see
-//         pair_kernel): row genes in LDS hashes, each column gene read once
-//         and probed against every row; only the pairs on or above the
-//         diagonal are evaluated, each written to both halves.
+//   pairs C_max up to 512: pair_table_kernel, four row genomes (two above 256)
+//         x 512 column genomes, the row genes in one LDS table, each column
+//         gene read and looked up once for all rows. Above: pair_kernel, up to
+//         kMaxRows x 256, a hash per row genome and a probe of each. Either way
+//         only the pairs on or above the diagonal are evaluated, each written
+//         to both halves.
 #include <algorithm>
 #include <mutex>
 
@@ -141,7 +144,7 @@ __global__ __launch_bounds__(kPrepGenomes * kWave) void prep_kernel(PopView pop,
 constexpr int kPairBlock = 256;
 constexpr int kMaxRows = 2;  // row genomes per block (measured best of 1, 2, 4, 8)
 
-// Block = up to kMaxRows "row" genomes i0 .. i0+R-1 x 256 "column" genomes.
+// Capacities whose shared table does not fit (table_rows below gives 0). Block = up to kMaxRows "row" genomes i0 .. i0+R-1 x 256 "column" genomes.
 // Each row genome's genes go into an LDS hash (marking -> weight) plus its
 // sorted list. Each lane walks its column genome's sorted list once
 // (coalesced across the wavefront), hashes every marking once and probes all
@@ -276,10 +279,13 @@ __global__ __launch_bounds__(kPairBlock) void pair_kernel(Ws ws, int P, int HC, 
 // connection (the zero terms add exactly nothing).
 //
 // Same two-launch shape as the connection-gene distance: a prep wavefront per
-// genome sorts both gene lists (keys + the row they came from, bitonic in
-// LDS), checks repeated keys / markings, and stores them position-major with
-// their attributes; the pair kernel hashes R row genomes' genes in LDS and
-// walks each column genome's sorted lists once.
+// genome sorts both gene lists (keys + the row they came from) as above, checks
+// repeated keys / markings, and stores them position-major with their
+// attributes. The pairs take pair_nodes_table_kernel (node genes first, then
+// connections, each kind's row genes in one table) where its LDS allows four
+// rows (N_max up to 128, C_max up to 256) or two (512, 1024), else
+// pair_nodes_kernel: R row genomes' genes in LDS hashes, each column genome's
+// sorted lists walked once.
 
 struct Gene {
   float a0, a1;

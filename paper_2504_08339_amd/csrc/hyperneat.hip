@@ -414,8 +414,9 @@ __device__ __forceinline__ CppnItem cppn_item(const SubGeom& sg, int per, int it
 // wavefronts per SIMD. With this walk on a file of 48 rows for
 // four tiles (two wavefronts per SIMD) 1841 us, of 28 rows (three) 1493 us.
 constexpr int kMapRows = 32, kMapWaves = 4;
-// targets per wavefront (64 measured 1348 us where 128 take 1420: the last
-// round is shorter); table rows
+// Targets per wavefront, at most, and the wavefronts that make it fewer: 200 CPPNs
+// over a 32 x 32 grid run 64 each (1420 us with 128, 1348 with 64: the last round
+// is shorter). Rows of the table.
 constexpr int kMapRun = 128, kMapWavesWanted = 32768, kMapSlots = 16;
 
 template <int K>

@@ -75,14 +75,15 @@ Layout make_layout(int N, int C) {
   L.c_cap = C;
   L.n_prev = L.c_prev = -1;
   L.last = true;
-  // Tables half empty and 4-byte marking entries: the largest genomes of 535
-  // nodes and 1983 connections then take 68 KB, two workgroups per compute unit
-  // (84 KB and one with the 8-byte marking itself as the entry): 10,000 uneven
-  // genomes 785 -> 655 us. Smaller tables, at two thirds and 80 % of their size,
-  // let three workgroups in and lost more to longer probes: 695 us, and 710
-  // against 635 us where C_max is 1894.
+  // Powers of two: the key table 25 to 50 % full, the marking table 40 to 80 %
+  // (48 % at 1983 connections, 46 % at 1894, 78 % at 1600). 4-byte marking
+  // entries: the largest genomes of 535 nodes and 1983 connections take 68 KB, two
+  // workgroups per compute unit (84 KB and one with the 8-byte marking itself as
+  // the entry): 10,000 uneven genomes 785 -> 655 us. Tables cut to fit there, 67 and
+  // 80 % full, let three workgroups in and lost more to longer probes: 695 us, and
+  // 710 against 635 us where C_max is 1894.
   L.HN = next_pow2(2 * N);
-  L.HC = next_pow2(C + C / 4 + 1);  // marking hash at most 80 % full
+  L.HC = next_pow2(C + C / 4 + 1);
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
