@@ -324,11 +324,12 @@ __global__ __launch_bounds__(kWave) void backward_kernel(
 // 16 lanes, added to one LDS row. That is a quarter of the LDS traffic and of
 // the LDS itself of one slot per sum and lane, so the registers (two wavefronts
 // per SIMD) and not the LDS limit occupancy, and genomes of up to 192 in-edges
-// fit. At the end of a group of steps each sum's 16 lanes are added, then the groups
-// in order: the same bits however the launch splits a genome. Bound by instruction issue. 4096 genomes (4 -> 2, 22 positions, 45
-// in-edges), 1024 samples: 264 us; 569 us with a slot per sum and lane, two
-// tiles a step. 1000 genomes (17 -> 6, 39 positions, 126 in-edges), 256
-// observations: 47 us; 148 us in backward_kernel.
+// fit. At the end of a group of steps each sum's 16 lanes are added, then the
+// groups in order: the same bits however the launch splits a genome. Bound by
+// instruction issue. 4096 genomes (4 -> 2, 22 positions, 45 in-edges), 1024
+// samples: 243 us; 569 us with a slot per sum and lane, two tiles a step. 1000
+// genomes (17 -> 6, 39 positions, 126 in-edges), 256 observations: 51 us; 148 us in
+// backward_kernel.
 
 // What a step reads of its genome, and this lane's share of it (computed node
 // i in lane i).

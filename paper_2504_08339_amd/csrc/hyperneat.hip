@@ -980,8 +980,9 @@ __global__ __launch_bounds__(256) void substrate_grad_out_kernel(
 // bfloat16 and keeps it, transposed, in LDS; then for each tile of s the rows
 // of x come through registers into LDS transposed (the next tile is requested
 // before this one's MFMAs). So H is read once, and neither dz nor x^T passes
-// through memory. Bound by the stores of dw1t and the reads of H and x: 200 genomes (32 x 32 grids, 128 rows; 840 MB written, 160 MB read)
-// 284 us, against 445 us in three kernels that wrote dz and x^T out.
+// through memory. Bound by the stores of dw1t and the reads of H and x: 200 genomes
+// (32 x 32 grids, 128 rows; 840 MB written, 160 MB read) 284 us, against 445 us in
+// three kernels that wrote dz and x^T out.
 constexpr int kFusedBatch = 128;
 constexpr int kFusedRow = kFusedBatch + 8;  // bf16 per LDS row
 constexpr size_t kFusedLds = sizeof(uint16_t) * 2 * kGemmTile * kFusedRow;
